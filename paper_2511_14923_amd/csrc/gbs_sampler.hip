@@ -1,4 +1,6 @@
 // Stage-2 sampler: click patterns drawn bit by bit from the parity cumulants.
+// Single elision, double elision of few modes, and the batches of both; double
+// elision of more modes runs in gbs_sampler_double.hip.
 //
 // The chain rule p(x_n | x_{n-1}, .., x_1) = p(x_n, .., x_1) / p(x_{n-1}, .., x_1)
 // with the joint probability expanded in the parity cumulants kappa(S) up to
@@ -33,7 +35,10 @@
 // workgroup barriers between the phases of a step.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "gbs_internal.h"
+#include "gbs_sampler.h"
 
 namespace gbs {
 
@@ -52,24 +57,17 @@ constexpr int kIB = 8;
 //   p1(a, e)     1 <= e < a                                (a-1)(a-2)/2 + e - 1
 //   p+(b, a)     1 <= a <= b                               b(b-1)/2 + a - 1
 //   p2(a, e, d)  1 <= d < e < a                            C(a-1,3) + C(e-1,2) + d - 1
-__host__ __device__ constexpr uint32_t c2(uint32_t x) { return x * (x - 1) / 2; }
-__host__ __device__ constexpr uint32_t c3(uint32_t x) { return x < 3 ? 0u : x * (x - 1) * (x - 2) / 6; }
-
 struct SampLayout {
   uint32_t n0, n1, npp, n2;  // entries of p, p1, p+, p2
   __host__ __device__ static SampLayout make(int M, int K) {
     SampLayout L;
     L.n0 = (uint32_t)M + 1;
-    L.n1 = c2((uint32_t)M) + 1;
-    L.npp = c2((uint32_t)M + 1) + 1;
-    L.n2 = K == 5 ? c3((uint32_t)M) + 1 : 0;
+    L.n1 = samp_c2((uint32_t)M) + 1;
+    L.npp = samp_c2((uint32_t)M + 1) + 1;
+    L.n2 = K == 5 ? samp_c3((uint32_t)M) + 1 : 0;
     return L;
   }
   __host__ __device__ uint32_t entries() const { return n0 + n1 + npp + n2; }
-};
-
-struct KapOffsets {
-  uint32_t off[6];  // start of the order-d block of the cumulant array
 };
 
 // Per-lane view of one sample's tables.
@@ -88,13 +86,13 @@ struct Tables {
   }
   __device__ __forceinline__ double p(int a) const { return at(P0, (uint32_t)a); }
   __device__ __forceinline__ double p1(int a, int e) const {
-    return e == a ? p(a - 1) : at(P1, c2((uint32_t)a - 1) + (uint32_t)e - 1);
+    return e == a ? p(a - 1) : at(P1, samp_c2((uint32_t)a - 1) + (uint32_t)e - 1);
   }
   __device__ __forceinline__ double p2(int a, int e, int d) const {
-    return e == a ? p1(a - 1, d) : at(P2, c3((uint32_t)a - 1) + c2((uint32_t)e - 1) + (uint32_t)d - 1);
+    return e == a ? p1(a - 1, d) : at(P2, samp_c3((uint32_t)a - 1) + samp_c2((uint32_t)e - 1) + (uint32_t)d - 1);
   }
   __device__ __forceinline__ double pp(int b, int a) const {
-    return b < a ? 1.0 : at(PP, c2((uint32_t)b) + (uint32_t)a - 1);
+    return b < a ? 1.0 : at(PP, samp_c2((uint32_t)b) + (uint32_t)a - 1);
   }
 };
 
@@ -114,19 +112,6 @@ struct Bits {
 };
 
 __device__ __forceinline__ double flip(double v, uint32_t parity) { return parity ? -v : v; }
-
-// C(x - 1, k) for the colex rank of 1-based bits
-__device__ __forceinline__ uint32_t r1(int x) { return (uint32_t)x - 1; }
-__device__ __forceinline__ uint32_t r2(int x) { return c2((uint32_t)x - 1); }
-__device__ __forceinline__ uint32_t r3(int x) { return c3((uint32_t)x - 1); }
-__device__ __forceinline__ uint32_t r4(int x) {
-  const uint32_t y = (uint32_t)x - 1;
-  return y < 4 ? 0u : y * (y - 1) * (y - 2) * (y - 3) / 24;
-}
-__device__ __forceinline__ uint32_t r5(int x) {
-  const uint64_t y = (uint64_t)x - 1;
-  return y < 5 ? 0u : (uint32_t)(y * (y - 1) * (y - 2) * (y - 3) * (y - 4) / 120);
-}
 
 template <int K, int kSampWaves = samp_waves<K>()>
 __global__ __launch_bounds__(64 * kSampWaves) void sampler_kernel(
@@ -150,32 +135,32 @@ __global__ __launch_bounds__(64 * kSampWaves) void sampler_kernel(
   __syncthreads();
 
   for (int n = 1; n <= M; ++n) {
-    const uint32_t o2 = ko.off[2] + r2(n), o3 = ko.off[3] + r3(n);
+    const uint32_t o2 = ko.off[2] + samp_r2(n), o3 = ko.off[3] + samp_r3(n);
     // ---- phase A: this wave's part of D_n ----
     // order 2 by i, orders 3-5 by the pairs (i > j), each dealt round-robin to
     // the waves (pair (i, j) has index C(i-1, 2) + j - 1)
     double D = 0.0;
     const double pprev = t.p(n - 1);
-    if (w == 0) D = 0.5 * kap[ko.off[1] + r1(n)] * pprev;
+    if (w == 0) D = 0.5 * kap[ko.off[1] + samp_r1(n)] * pprev;
     for (int i = 1 + w; i < n; i += kSampWaves)
-      D += flip(0.25 * kap[o2 + r1(i)] * t.p1(n - 1, i), x.get(i));
+      D += flip(0.25 * kap[o2 + samp_r1(i)] * t.p1(n - 1, i), x.get(i));
     for (int i = 2; i < n; ++i) {
       const uint32_t xi = x.get(i);
-      const int j0 = 1 + (w + kSampWaves - (int)(c2((uint32_t)i - 1) % kSampWaves)) % kSampWaves;
+      const int j0 = 1 + (w + kSampWaves - (int)(samp_c2((uint32_t)i - 1) % kSampWaves)) % kSampWaves;
       if (j0 >= i) continue;
       const double A = t.pp(n - 1, i + 1);  // the same for every j of this i
       for (int j = j0; j < i; j += kSampWaves) {
         const uint32_t sij = xi ^ x.get(j);
         if constexpr (K == 3) {
-          D += flip(0.125 * kap[o3 + r2(i) + r1(j)] * A * t.p1(i - 1, j), sij);
+          D += flip(0.125 * kap[o3 + samp_r2(i) + samp_r1(j)] * A * t.p1(i - 1, j), sij);
         } else {
-          const uint32_t o4 = ko.off[4] + r4(n);
-          double v = 0.125 * kap[o3 + r2(i) + r1(j)] * t.p2(n - 1, i, j);
+          const uint32_t o4 = ko.off[4] + samp_r4(n);
+          double v = 0.125 * kap[o3 + samp_r2(i) + samp_r1(j)] * t.p2(n - 1, i, j);
           double a4 = 0.0;
-          const uint32_t ok4 = o4 + r3(i) + r2(j);
+          const uint32_t ok4 = o4 + samp_r3(i) + samp_r2(j);
 #pragma unroll 4
           for (int k = 1; k < j; ++k)
-            a4 += flip(kap[ok4 + r1(k)] * t.p2(i - 1, j, k), x.get(k));
+            a4 += flip(kap[ok4 + samp_r1(k)] * t.p2(i - 1, j, k), x.get(k));
           v += A * a4 * (1.0 / 16.0);
           D += flip(v, sij);
         }
@@ -186,7 +171,7 @@ __global__ __launch_bounds__(64 * kSampWaves) void sampler_kernel(
       // Units (j, block of kIB consecutive i > j) are dealt round-robin; a unit
       // keeps chi_i p+(n-1..i+1) p+(i-1..j+1) of its i in registers and reads
       // every p2(j-1; k, l) once for all of them.
-      const uint32_t o5 = ko.off[5] + r5(n);
+      const uint32_t o5 = ko.off[5] + samp_r5(n);
       int unit = 0;
       for (int j = 3; j < n - 1; ++j) {
         const int nblk = (n - 1 - j + kIB - 1) / kIB;
@@ -199,18 +184,18 @@ __global__ __launch_bounds__(64 * kSampWaves) void sampler_kernel(
             const int i = j + 1 + b * kIB + ib;
             const bool in = i < n;
             const int ic = in ? i : n - 1;  // a valid cumulant index; its weight is 0
-            kb[ib] = o5 + r4(ic) + r3(j);
+            kb[ib] = o5 + samp_r4(ic) + samp_r3(j);
             wv[ib] = in ? flip(t.pp(n - 1, i + 1) * t.pp(i - 1, j + 1), x.get(i)) : 0.0;
           }
           double acc = 0.0;
           for (int k = 2; k < j; ++k) {
             double ak = 0.0;
-            const uint32_t rk = r2(k);
+            const uint32_t rk = samp_r2(k);
 #pragma unroll 4
             for (int l = 1; l < k; ++l) {
               double kw = 0.0;
 #pragma unroll
-              for (int ib = 0; ib < kIB; ++ib) kw = fma(kap[kb[ib] + rk + r1(l)], wv[ib], kw);
+              for (int ib = 0; ib < kIB; ++ib) kw = fma(kap[kb[ib] + rk + samp_r1(l)], wv[ib], kw);
               ak += flip(kw * t.p2(j - 1, k, l), x.get(l));
             }
             acc += flip(ak, x.get(k));
@@ -240,37 +225,37 @@ __global__ __launch_bounds__(64 * kSampWaves) void sampler_kernel(
     }
 
     // ---- phase B: the tables of top n (entries split between the waves) ----
-    const double h = 0.5 + flip(0.5 * kap[ko.off[1] + r1(n)], xn);
+    const double h = 0.5 + flip(0.5 * kap[ko.off[1] + samp_r1(n)], xn);
     if constexpr (K == 3) {
       for (int e = 1 + w; e < n; e += kSampWaves) {
         // terms i < e share the factor p+(n-1..e+1); terms i > e carry p+(n-1..i+1)
         double below = 0.0, above = 0.0;
         for (int i = 1; i < e; ++i)
-          below += flip(kap[o2 + r1(i)] * t.p1(e - 1, i), x.get(i) ^ xn);
+          below += flip(kap[o2 + samp_r1(i)] * t.p1(e - 1, i), x.get(i) ^ xn);
         for (int i = e + 1; i < n; ++i)
-          above += flip(kap[o2 + r1(i)] * t.pp(n - 1, i + 1) * t.p1(i - 1, e), x.get(i) ^ xn);
+          above += flip(kap[o2 + samp_r1(i)] * t.pp(n - 1, i + 1) * t.p1(i - 1, e), x.get(i) ^ xn);
         const double v = h * t.p1(n - 1, e) + 0.25 * fma(t.pp(n - 1, e + 1), below, above);
-        t.put(t.P1, c2((uint32_t)n - 1) + (uint32_t)e - 1, v);
+        t.put(t.P1, samp_c2((uint32_t)n - 1) + (uint32_t)e - 1, v);
       }
       for (int l = 1 + w; l <= n; l += kSampWaves) {
         double v = h * t.pp(n - 1, l);
         for (int i = l; i < n; ++i)
-          v += flip(0.25 * kap[o2 + r1(i)] * t.pp(n - 1, i + 1) * t.pp(i - 1, l), x.get(i) ^ xn);
-        t.put(t.PP, c2((uint32_t)n) + (uint32_t)l - 1, v);
+          v += flip(0.25 * kap[o2 + samp_r1(i)] * t.pp(n - 1, i + 1) * t.pp(i - 1, l), x.get(i) ^ xn);
+        t.put(t.PP, samp_c2((uint32_t)n) + (uint32_t)l - 1, v);
       }
     } else {
       for (int l = 1 + w; l <= n; l += kSampWaves) {
         double v = h * t.pp(n - 1, l);
         for (int i = l; i < n; ++i) {
           const double Ai = t.pp(n - 1, i + 1);  // shared by the order-3 and order-4 terms of i
-          double ai = 0.25 * kap[o2 + r1(i)] * t.pp(i - 1, l);
+          double ai = 0.25 * kap[o2 + samp_r1(i)] * t.pp(i - 1, l);
           double a3 = 0.0;
           for (int j = l; j < i; ++j)
-            a3 += flip(kap[o3 + r2(i) + r1(j)] * t.pp(i - 1, j + 1) * t.pp(j - 1, l), x.get(j));
+            a3 += flip(kap[o3 + samp_r2(i) + samp_r1(j)] * t.pp(i - 1, j + 1) * t.pp(j - 1, l), x.get(j));
           ai = fma(0.125, a3, ai);
           v += flip(Ai * ai, x.get(i) ^ xn);
         }
-        t.put(t.PP, c2((uint32_t)n) + (uint32_t)l - 1, v);
+        t.put(t.PP, samp_c2((uint32_t)n) + (uint32_t)l - 1, v);
       }
       for (int e = 1 + w; e < n; e += kSampWaves) {
         // Loops are split where the order of the elided bits changes, so
@@ -278,48 +263,48 @@ __global__ __launch_bounds__(64 * kSampWaves) void sampler_kernel(
         double v3 = 0.0;
 #pragma unroll 4
         for (int i = 1; i < e; ++i)
-          v3 += flip(kap[o2 + r1(i)] * t.p2(n - 1, e, i), x.get(i) ^ xn);
+          v3 += flip(kap[o2 + samp_r1(i)] * t.p2(n - 1, e, i), x.get(i) ^ xn);
 #pragma unroll 4
         for (int i = e + 1; i < n; ++i)
-          v3 += flip(kap[o2 + r1(i)] * t.p2(n - 1, i, e), x.get(i) ^ xn);
+          v3 += flip(kap[o2 + samp_r1(i)] * t.p2(n - 1, i, e), x.get(i) ^ xn);
         double v = fma(0.25, v3, h * t.p1(n - 1, e));
         for (int i = 2; i < n; ++i) {
           if (i == e) continue;
           // (a, b, c): i, j, e in decreasing order; a = max(i, e) does not depend on j
           const int a = e > i ? e : i;
           const double A = t.pp(n - 1, a + 1);
-          const uint32_t ki = o3 + r2(i);
+          const uint32_t ki = o3 + samp_r2(i);
           double ai = 0.0;
           if (i < e) {
 #pragma unroll 4
-            for (int j = 1; j < i; ++j) ai += flip(kap[ki + r1(j)] * t.p2(e - 1, i, j), x.get(j));
+            for (int j = 1; j < i; ++j) ai += flip(kap[ki + samp_r1(j)] * t.p2(e - 1, i, j), x.get(j));
           } else {
 #pragma unroll 4
-            for (int j = 1; j < e; ++j) ai += flip(kap[ki + r1(j)] * t.p2(i - 1, e, j), x.get(j));
+            for (int j = 1; j < e; ++j) ai += flip(kap[ki + samp_r1(j)] * t.p2(i - 1, e, j), x.get(j));
 #pragma unroll 4
-            for (int j = e + 1; j < i; ++j) ai += flip(kap[ki + r1(j)] * t.p2(i - 1, j, e), x.get(j));
+            for (int j = e + 1; j < i; ++j) ai += flip(kap[ki + samp_r1(j)] * t.p2(i - 1, j, e), x.get(j));
           }
           v += flip(0.125 * A * ai, x.get(i) ^ xn);
         }
-        t.put(t.P1, c2((uint32_t)n - 1) + (uint32_t)e - 1, v);
+        t.put(t.P1, samp_c2((uint32_t)n - 1) + (uint32_t)e - 1, v);
       }
       for (int e = 2; e < n; ++e) {
-        const int d0 = 1 + (w + kSampWaves - (int)(c2((uint32_t)e - 1) % kSampWaves)) % kSampWaves;
+        const int d0 = 1 + (w + kSampWaves - (int)(samp_c2((uint32_t)e - 1) % kSampWaves)) % kSampWaves;
         for (int d = d0; d < e; d += kSampWaves) {
           // (a, b, c): i, e, d in decreasing order.  Terms i < e have a = e and
           // share the factor p+(n-1..e+1); terms i > e have (a, b, c) = (i, e, d).
           double below = 0.0, above = 0.0;
 #pragma unroll 4
           for (int i = 1; i < d; ++i)
-            below += flip(kap[o2 + r1(i)] * t.p2(e - 1, d, i), x.get(i) ^ xn);
+            below += flip(kap[o2 + samp_r1(i)] * t.p2(e - 1, d, i), x.get(i) ^ xn);
 #pragma unroll 4
           for (int i = d + 1; i < e; ++i)
-            below += flip(kap[o2 + r1(i)] * t.p2(e - 1, i, d), x.get(i) ^ xn);
+            below += flip(kap[o2 + samp_r1(i)] * t.p2(e - 1, i, d), x.get(i) ^ xn);
 #pragma unroll 4
           for (int i = e + 1; i < n; ++i)
-            above += flip(kap[o2 + r1(i)] * t.pp(n - 1, i + 1) * t.p2(i - 1, e, d), x.get(i) ^ xn);
+            above += flip(kap[o2 + samp_r1(i)] * t.pp(n - 1, i + 1) * t.p2(i - 1, e, d), x.get(i) ^ xn);
           const double v = h * t.p2(n - 1, e, d) + 0.25 * fma(t.pp(n - 1, e + 1), below, above);
-          t.put(t.P2, c3((uint32_t)n - 1) + c2((uint32_t)e - 1) + (uint32_t)d - 1, v);
+          t.put(t.P2, samp_c3((uint32_t)n - 1) + samp_c2((uint32_t)e - 1) + (uint32_t)d - 1, v);
         }
       }
     }
@@ -330,11 +315,12 @@ __global__ __launch_bounds__(64 * kSampWaves) void sampler_kernel(
 
 }  // namespace
 
-// Samples per launch for a table budget of `bytes`.
-static int64_t samp_batch(int M, int K, size_t bytes) {
-  const uint64_t per = (uint64_t)SampLayout::make(M, K).entries() * sizeof(double);
-  return (int64_t)((bytes / per) / 64 * 64);
-}
+// Modes from which double elision runs step by step over all samples
+// (gbs_sampler_double.hip, about four launches per bit) instead of one workgroup
+// per 64 samples here: 1,000 samples take 0.34 ms either way at M = 12, 0.13
+// (here) against 0.23 ms at M = 8, 0.69 against 0.44 ms at M = 16, 102 against
+// 4.1 ms at M = 60.
+constexpr int kStepMinModes = 12;
 
 hipError_t run_sampler(int M, int K, const double* kap, int64_t nsamples, const double* u,
                        uint8_t* bits, double* prob, double* cond, int64_t batch, hipStream_t s) {
@@ -344,32 +330,42 @@ hipError_t run_sampler(int M, int K, const double* kap, int64_t nsamples, const 
   ko.off[1] = 0;
   for (int d = 2; d <= 5; ++d)
     ko.off[d] = ko.off[d - 1] + (d - 1 <= K ? (uint32_t)host_binom(M, d - 1) : 0u);
+  const bool steps = K == 5 && M >= kStepMinModes;
+  const uint64_t lane_bytes = (uint64_t)L.entries() * sizeof(double);
+  const uint64_t per = steps ? double_sampler_bytes(M) : lane_bytes;
   if (batch <= 0) {
     size_t free_b = 0, total_b = 0;
     hipError_t e = hipMemGetInfo(&free_b, &total_b);
     if (e != hipSuccess) return e;
-    batch = samp_batch(M, K, free_b / 4);
+    batch = (int64_t)(free_b / 4 / per);
+  } else if (steps) {
+    // a batch stands for the memory of one table set per sample; the step tables are about twice that
+    batch = (int64_t)((double)batch * (double)lane_bytes / (double)per);
   }
-  batch = std::max<int64_t>(64, std::min<int64_t>(batch, (nsamples + 63) / 64 * 64));
+  batch = std::max<int64_t>(64, batch / 64 * 64);
+  batch = std::min<int64_t>(batch, (nsamples + 63) / 64 * 64);
   // equal launches: a small last launch would run for as long as a full one
   const int64_t nlaunch = (nsamples + batch - 1) / batch;
   batch = ((nsamples + nlaunch - 1) / nlaunch + 63) / 64 * 64;
-  const uint64_t ldt = (uint64_t)(batch + 63) / 64 * 64;  // table columns: 64 per workgroup
   void* scratch = nullptr;
-  hipError_t e = hipMallocAsync(&scratch, (size_t)L.entries() * ldt * sizeof(double), s);
+  hipError_t e = hipMallocAsync(&scratch, (size_t)(per * (uint64_t)batch), s);
   if (e != hipSuccess) return e;
   double* tab = static_cast<double*>(scratch);
   for (int64_t s0 = 0; s0 < nsamples && e == hipSuccess; s0 += batch) {
     const int64_t nb = std::min<int64_t>(batch, nsamples - s0);
     const unsigned grid = (unsigned)((nb + 63) / 64);
+    double* pr = prob ? prob + s0 : nullptr;
+    double* cd = cond ? cond + s0 : nullptr;
+    if (steps) {
+      e = launch_double_sampler(M, kap, ko, nb, u + s0, (uint64_t)nsamples, tab, bits + s0 * M, pr, cd, s);
+      continue;
+    }
     if (K == 3)
       hipLaunchKernelGGL(sampler_kernel<3>, dim3(grid), dim3(64 * samp_waves<3>()), 0, s, kap, ko, M,
-                         u + s0, (uint64_t)nsamples, nb, tab, L, bits + s0 * M,
-                         prob ? prob + s0 : nullptr, cond ? cond + s0 : nullptr);
+                         u + s0, (uint64_t)nsamples, nb, tab, L, bits + s0 * M, pr, cd);
     else
       hipLaunchKernelGGL(sampler_kernel<5>, dim3(grid), dim3(64 * samp_waves<5>()), 0, s, kap, ko, M,
-                         u + s0, (uint64_t)nsamples, nb, tab, L, bits + s0 * M,
-                         prob ? prob + s0 : nullptr, cond ? cond + s0 : nullptr);
+                         u + s0, (uint64_t)nsamples, nb, tab, L, bits + s0 * M, pr, cd);
     e = hipGetLastError();
   }
   hipError_t f = hipFreeAsync(scratch, s);
