@@ -348,6 +348,20 @@ GBS_API gbs_status gbs_sample(int32_t M, const double* kappa, int32_t max_order,
                               const double* uniforms, uint8_t* bits, double* prob, double* cond,
                               int64_t batch, int32_t flags, void* stream);
 
+/* gbs_sample on scratch memory of the caller, for callers that keep a workspace
+ * (memory that the library allocates goes back to the device after the call, and
+ * several GiB of it take longer to come by than the samples).
+ * gbs_sample_scratch (host): the bytes that gbs_sample would allocate for
+ * `batch`, or -1 for arguments that it would refuse.  gbs_sample_in: the same
+ * samples from scratch_bytes bytes at `scratch` (device, 256-byte aligned, not
+ * used by other work until the call's kernels have run), in as many parts as they
+ * need; GBS_E_OUT_OF_MEMORY if fewer than 64 samples' tables fit. */
+GBS_API int64_t gbs_sample_scratch(int32_t M, int32_t max_order, int64_t nsamples, int64_t batch);
+GBS_API gbs_status gbs_sample_in(int32_t M, const double* kappa, int32_t max_order,
+                                 int64_t nsamples, const double* uniforms, uint8_t* bits,
+                                 double* prob, double* cond, void* scratch, int64_t scratch_bytes,
+                                 int32_t flags, void* stream);
+
 /* Click cumulants estimated from samples (App. F, "Click cumulants, Pearson and
  * Spearman coefficients", Eq. cumulants_test_def): for every S with
  * 1 <= |S| <= max_order, the unbiased estimate of kappa~(S) in which each
@@ -366,6 +380,14 @@ GBS_API gbs_status gbs_sample(int32_t M, const double* kappa, int32_t max_order,
 GBS_API gbs_status gbs_sample_cumulants(int32_t M, int64_t nsamples, const uint8_t* bits,
                                         int32_t max_order, double* cum, int32_t flags,
                                         void* stream);
+
+/* gbs_sample_cumulants on scratch memory of the caller (as gbs_sample_in).
+ * gbs_sample_cumulants_scratch (host): the bytes it needs, or -1 for arguments
+ * that gbs_sample_cumulants would refuse; fewer give GBS_E_OUT_OF_MEMORY. */
+GBS_API int64_t gbs_sample_cumulants_scratch(int32_t M, int64_t nsamples, int32_t max_order);
+GBS_API gbs_status gbs_sample_cumulants_in(int32_t M, int64_t nsamples, const uint8_t* bits,
+                                           int32_t max_order, double* cum, void* scratch,
+                                           int64_t scratch_bytes, int32_t flags, void* stream);
 
 /* Pearson correlation coefficient of x and y (Eq. pearson_correlation):
  * sum (x - <x>)(y - <y>) / sqrt(sum (x - <x>)^2 sum (y - <y>)^2), two passes

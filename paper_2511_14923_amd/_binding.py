@@ -52,6 +52,8 @@ EXPORTS = (
     "gbs_cumulants_batched", "gbs_autotune_batched", "gbs_set_tuning", "gbs_sample",
     "gbs_sample_cumulants", "gbs_pearson", "gbs_last_error",
     "gbs_last_timings", "gbs_status_string", "gbs_cumulants_noalloc",
+    "gbs_sample_scratch", "gbs_sample_in", "gbs_sample_cumulants_scratch",
+    "gbs_sample_cumulants_in",
 )
 
 
@@ -124,6 +126,14 @@ def lib() -> ctypes.CDLL:
     L.gbs_sample.restype = i32
     L.gbs_sample_cumulants.argtypes = [i32, i64, vp, i32, vp, i32, vp]
     L.gbs_sample_cumulants.restype = i32
+    L.gbs_sample_scratch.argtypes = [i32, i32, i64, i64]
+    L.gbs_sample_scratch.restype = i64
+    L.gbs_sample_in.argtypes = [i32, vp, i32, i64, vp, vp, vp, vp, vp, i64, i32, vp]
+    L.gbs_sample_in.restype = i32
+    L.gbs_sample_cumulants_scratch.argtypes = [i32, i64, i32]
+    L.gbs_sample_cumulants_scratch.restype = i64
+    L.gbs_sample_cumulants_in.argtypes = [i32, i64, vp, i32, vp, vp, i64, i32, vp]
+    L.gbs_sample_cumulants_in.restype = i32
     L.gbs_pearson.argtypes = [i64, vp, vp, vp, i32, vp]
     L.gbs_pearson.restype = i32
     L.gbs_last_error.argtypes = [ctypes.POINTER(i32), ctypes.POINTER(i64)]
@@ -210,6 +220,26 @@ def _stream(stream, device):
     if isinstance(stream, torch.cuda.Stream):
         return ctypes.c_void_p(stream.cuda_stream)
     return ctypes.c_void_p(int(stream))
+
+
+def _scratch(nbytes, stream, device):
+    """nbytes of device memory for the library to work in during one call on
+    `stream`, or None (the library then allocates its own).  From torch's caching
+    allocator: it keeps the memory for the next call, gives it back when other
+    tensors need it (or on torch.cuda.empty_cache), and hands it out again only
+    to work that runs after this call's on the same stream."""
+    if nbytes <= 0:
+        return None
+    if stream is None:
+        stream = torch.cuda.current_stream(device)
+    elif not isinstance(stream, torch.cuda.Stream):
+        stream = (torch.cuda.ExternalStream(int(stream), device) if int(stream)
+                  else torch.cuda.default_stream(device))
+    try:
+        with torch.cuda.stream(stream):
+            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None
 
 
 # ---- host helpers -----------------------------------------------------------
@@ -389,8 +419,14 @@ def gbs_sample(M: int, kappa: torch.Tensor, max_order: int, uniforms: torch.Tens
     _same_device(("kappa", kappa), ("uniforms", uniforms), ("bits", bits), ("prob", prob),
                  ("cond", cond))
     with torch.cuda.device(dev):
-        st = lib().gbs_sample(M, _ptr(kappa), max_order, n, _ptr(uniforms), _ptr_u8(bits),
-                              _ptr(prob), _ptr(cond), batch, flags, _stream(stream, dev))
+        work = _scratch(lib().gbs_sample_scratch(M, max_order, n, batch), stream, dev)
+        if work is None:
+            st = lib().gbs_sample(M, _ptr(kappa), max_order, n, _ptr(uniforms), _ptr_u8(bits),
+                                  _ptr(prob), _ptr(cond), batch, flags, _stream(stream, dev))
+        else:
+            st = lib().gbs_sample_in(M, _ptr(kappa), max_order, n, _ptr(uniforms), _ptr_u8(bits),
+                                     _ptr(prob), _ptr(cond), _ptr_u8(work), work.numel(), flags,
+                                     _stream(stream, dev))
     _check(st, "gbs_sample")
     return bits, prob, cond
 
@@ -407,8 +443,14 @@ def gbs_sample_cumulants(bits: torch.Tensor, max_order: int, cum=None, flags: in
     _need(cum, "cum", nout)
     _same_device(("bits", bits), ("cum", cum))
     with torch.cuda.device(bits.device):
-        st = lib().gbs_sample_cumulants(M, n, _ptr_u8(bits), max_order, _ptr(cum), flags,
-                                        _stream(stream, bits.device))
+        work = _scratch(lib().gbs_sample_cumulants_scratch(M, n, max_order), stream, bits.device)
+        if work is None:
+            st = lib().gbs_sample_cumulants(M, n, _ptr_u8(bits), max_order, _ptr(cum), flags,
+                                            _stream(stream, bits.device))
+        else:
+            st = lib().gbs_sample_cumulants_in(M, n, _ptr_u8(bits), max_order, _ptr(cum),
+                                               _ptr_u8(work), work.numel(), flags,
+                                               _stream(stream, bits.device))
     _check(st, "gbs_sample_cumulants")
     return cum
 

@@ -504,20 +504,78 @@ gbs_status gbs_cumulant_grad(int32_t M, const double* sigma, int32_t max_order, 
   return run_adjoint(M, sigma, max_order, flags, grad_corr, grad_cum, grad_sigma, stream);
 }
 
-gbs_status gbs_sample(int32_t M, const double* kappa, int32_t max_order, int64_t nsamples,
-                      const double* uniforms, uint8_t* bits, double* prob, double* cond,
-                      int64_t batch, int32_t flags, void* stream) {
+// Argument checks of the sampler; GBS_OK for a valid call.
+static gbs_status check_sample(int32_t M, const double* kappa, int32_t max_order, int64_t nsamples,
+                               const double* uniforms, const uint8_t* bits, int64_t batch,
+                               int32_t flags) {
   if (M < 1 || max_order < 1 || max_order > M || nsamples < 0 || batch < 0) return GBS_E_INVALID_ARG;
   if (flags & ~(GBS_ASYNC | GBS_TIMING)) return GBS_E_INVALID_ARG;
   if (!kappa || (nsamples > 0 && (!uniforms || !bits))) return GBS_E_INVALID_ARG;
   if (max_order != 3 && max_order != 5) return GBS_E_UNSUPPORTED;
   if (M > (max_order == 3 ? 256 : 200)) return GBS_E_INVALID_ARG;
+  return GBS_OK;
+}
+
+static gbs_status sample_call(int32_t M, const double* kappa, int32_t max_order, int64_t nsamples,
+                              const double* uniforms, uint8_t* bits, double* prob, double* cond,
+                              int64_t batch, void* lent, size_t lent_bytes, int32_t flags,
+                              void* stream) {
   if (nsamples == 0) return GBS_OK;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   timing_start_call((flags & GBS_TIMING) != 0);
   hipError_t e = timing_begin(s, GBS_STAGE_SAMPLE, max_order);
   if (e == hipSuccess)
-    e = run_sampler(M, max_order, kappa, nsamples, uniforms, bits, prob, cond, batch, s);
+    e = run_sampler(M, max_order, kappa, nsamples, uniforms, bits, prob, cond, batch, lent,
+                    lent_bytes, s);
+  if (e == hipSuccess) e = timing_end(s);
+  if (e != hipSuccess) return to_status(e);
+  if (flags & GBS_ASYNC) return GBS_OK;
+  return to_status(hipStreamSynchronize(s));
+}
+
+gbs_status gbs_sample(int32_t M, const double* kappa, int32_t max_order, int64_t nsamples,
+                      const double* uniforms, uint8_t* bits, double* prob, double* cond,
+                      int64_t batch, int32_t flags, void* stream) {
+  const gbs_status st = check_sample(M, kappa, max_order, nsamples, uniforms, bits, batch, flags);
+  if (st != GBS_OK) return st;
+  return sample_call(M, kappa, max_order, nsamples, uniforms, bits, prob, cond, batch, nullptr, 0,
+                     flags, stream);
+}
+
+int64_t gbs_sample_scratch(int32_t M, int32_t max_order, int64_t nsamples, int64_t batch) {
+  if (M < 1 || max_order > M || nsamples < 0 || batch < 0) return -1;
+  if ((max_order != 3 && max_order != 5) || M > (max_order == 3 ? 256 : 200)) return -1;
+  if (nsamples == 0) return 0;
+  size_t bytes = 0;
+  return sampler_scratch(M, max_order, nsamples, batch, &bytes) == hipSuccess ? (int64_t)bytes : -1;
+}
+
+gbs_status gbs_sample_in(int32_t M, const double* kappa, int32_t max_order, int64_t nsamples,
+                         const double* uniforms, uint8_t* bits, double* prob, double* cond,
+                         void* scratch, int64_t scratch_bytes, int32_t flags, void* stream) {
+  const gbs_status st = check_sample(M, kappa, max_order, nsamples, uniforms, bits, 0, flags);
+  if (st != GBS_OK) return st;
+  if (nsamples > 0 && (!scratch || scratch_bytes < 0)) return GBS_E_INVALID_ARG;
+  return sample_call(M, kappa, max_order, nsamples, uniforms, bits, prob, cond, 0, scratch,
+                     (size_t)scratch_bytes, flags, stream);
+}
+
+static bool valid_estimate(int32_t M, int64_t nsamples, int32_t max_order) {
+  return M >= 1 && M <= 256 && max_order >= 1 && max_order <= GBS_MAX_ORDER && max_order <= M &&
+         nsamples >= max_order && nsamples < (int64_t)1 << 32;
+}
+
+static gbs_status estimate_call(int32_t M, int64_t nsamples, const uint8_t* bits,
+                                int32_t max_order, double* cum, void* lent, int32_t flags,
+                                void* stream) {
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  hipError_t e;
+  DeviceContext* ctx = current_context(&e);
+  if (!ctx) return to_status(e);
+  timing_start_call((flags & GBS_TIMING) != 0);
+  e = timing_begin(s, GBS_STAGE_ESTIMATE, max_order);
+  if (e == hipSuccess)
+    e = run_sample_cumulants(M, nsamples, bits, max_order, ctx->binom, cum, lent, s);
   if (e == hipSuccess) e = timing_end(s);
   if (e != hipSuccess) return to_status(e);
   if (flags & GBS_ASYNC) return GBS_OK;
@@ -526,21 +584,23 @@ gbs_status gbs_sample(int32_t M, const double* kappa, int32_t max_order, int64_t
 
 gbs_status gbs_sample_cumulants(int32_t M, int64_t nsamples, const uint8_t* bits,
                                 int32_t max_order, double* cum, int32_t flags, void* stream) {
-  if (M < 1 || M > 256 || max_order < 1 || max_order > GBS_MAX_ORDER || max_order > M)
-    return GBS_E_INVALID_ARG;
-  if (nsamples < max_order || nsamples >= (int64_t)1 << 32 || !bits || !cum) return GBS_E_INVALID_ARG;
+  if (!valid_estimate(M, nsamples, max_order) || !bits || !cum) return GBS_E_INVALID_ARG;
   if (flags & ~(GBS_ASYNC | GBS_TIMING)) return GBS_E_INVALID_ARG;
-  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  hipError_t e;
-  DeviceContext* ctx = current_context(&e);
-  if (!ctx) return to_status(e);
-  timing_start_call((flags & GBS_TIMING) != 0);
-  e = timing_begin(s, GBS_STAGE_ESTIMATE, max_order);
-  if (e == hipSuccess) e = run_sample_cumulants(M, nsamples, bits, max_order, ctx->binom, cum, s);
-  if (e == hipSuccess) e = timing_end(s);
-  if (e != hipSuccess) return to_status(e);
-  if (flags & GBS_ASYNC) return GBS_OK;
-  return to_status(hipStreamSynchronize(s));
+  return estimate_call(M, nsamples, bits, max_order, cum, nullptr, flags, stream);
+}
+
+int64_t gbs_sample_cumulants_scratch(int32_t M, int64_t nsamples, int32_t max_order) {
+  return valid_estimate(M, nsamples, max_order) ? (int64_t)estimator_scratch(M, nsamples, max_order) : -1;
+}
+
+gbs_status gbs_sample_cumulants_in(int32_t M, int64_t nsamples, const uint8_t* bits,
+                                   int32_t max_order, double* cum, void* scratch,
+                                   int64_t scratch_bytes, int32_t flags, void* stream) {
+  if (!valid_estimate(M, nsamples, max_order) || !bits || !cum || !scratch) return GBS_E_INVALID_ARG;
+  if (flags & ~(GBS_ASYNC | GBS_TIMING)) return GBS_E_INVALID_ARG;
+  if (scratch_bytes < 0 || (size_t)scratch_bytes < estimator_scratch(M, nsamples, max_order))
+    return GBS_E_OUT_OF_MEMORY;
+  return estimate_call(M, nsamples, bits, max_order, cum, scratch, flags, stream);
 }
 
 gbs_status gbs_pearson(int64_t n, const double* x, const double* y, double* r, int32_t flags,

@@ -12,19 +12,19 @@
 // with coefficients c_N(tau) that depend only on the block structure of tau
 // and on N (computed on the host).  The work is therefore the power sums of
 // every subset of orders <= K:
-//   * the samples are packed into one bit column per mode, 64 samples a word;
-//   * s_S = sum_w popcount(AND_{k in S} column_k[w]) is a bit-matrix product:
-//     S = L + H with L its lowest one or two modes and H the rest; for a fixed
-//     c = min(H) the valid L are exactly the subsets of [0, c), so the products
-//     run over rectangles (C(c, |L|) x C(M-1-c, |H|-1)) cut into 64 x 64 tiles
-//     planned on the host; a tile streams word chunks of its row and column
-//     operands through LDS, each thread keeping a 4 x 4 block of counts;
+//   * the samples are packed into bit columns, 64 samples a word, in chunks of
+//     512 samples that hold every mode's 64 bytes next to each other;
+//   * s_S = sum over the samples of AND_{k in S} is a product of 0/1 matrices:
+//     S = L + H with L its lowest one or two modes and H the rest, rows H,
+//     columns L, inner index the samples, on the matrix units in FP4, whose 1.0
+//     is one bit of a nibble: masking a word of the ANDed columns with every
+//     fourth bit gives eight operands at once (count_kernel below);
 //   * k(S) gathers the power sums of the 2^|S| - 1 subsets of S from the count
 //     tables of the lower orders (colex ranks) and evaluates the sum over the
 //     partitions of S.
 #include <hip/hip_runtime.h>
 
-#include <cstring>
+#include <algorithm>
 #include <functional>
 #include <vector>
 
@@ -34,21 +34,36 @@ namespace gbs {
 
 namespace {
 
-constexpr int kEstTile = 64;     // rows and columns of a count tile
-constexpr int kEstChunk = 32;    // words per LDS chunk
 constexpr int kEstThreads = 256;
 constexpr int kEstMaxModes = 256;
+constexpr int kChunkWords = 8;                    // 64-bit words per mode and chunk
+constexpr int kChunkBytes = 8 * kChunkWords;      // 512 samples
+constexpr int kPackSamples = 256;                 // samples per workgroup of the packing
 
-// ---- pack: bits (N x M bytes, sample-major) -> columns C[k][w] ----
-__global__ void pack_columns_kernel(const uint8_t* __restrict__ bits, int64_t N, int M, int64_t W,
-                                    uint64_t* __restrict__ cols) {
-  // one wavefront per word: lane = sample within the word
+// Bit columns: word w of mode k at (w / 8 * M + k) * 8 + w % 8; samples past N are 0.
+__global__ __launch_bounds__(kPackSamples) void pack_columns_kernel(const uint8_t* __restrict__ bits, int64_t N,
+                                                                    int M, int64_t words, int wide,
+                                                                    uint64_t* __restrict__ cols) {
+  extern __shared__ uint8_t rows[];  // kPackSamples x M
+  const int64_t s0 = (int64_t)blockIdx.x * kPackSamples;
+  const int64_t have = min((int64_t)kPackSamples, N - s0);
+  const int64_t bytes = have > 0 ? have * M : 0;
+  const uint8_t* src = bits + s0 * M;
+  if (wide) {  // the caller's buffer starts on a 4-byte boundary, and s0 * M is a multiple of 4
+    const int64_t q = bytes >> 2;
+    for (int64_t i = threadIdx.x; i < q; i += kPackSamples)
+      reinterpret_cast<uint32_t*>(rows)[i] = reinterpret_cast<const uint32_t*>(src)[i];
+    for (int64_t i = q * 4 + threadIdx.x; i < bytes; i += kPackSamples) rows[i] = src[i];
+  } else {
+    for (int64_t i = threadIdx.x; i < bytes; i += kPackSamples) rows[i] = src[i];
+  }
+  __syncthreads();
   const int lane = threadIdx.x & 63;
-  const int64_t w = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (w >= W) return;
-  const int64_t s = w * 64 + lane;
-  const bool live = s < N;
-  const uint8_t* row = bits + (live ? s : 0) * (int64_t)M;
+  const int64_t w = (int64_t)blockIdx.x * (kPackSamples / 64) + (threadIdx.x >> 6);
+  if (w >= words) return;
+  const bool live = w * 64 + lane < N;
+  const uint8_t* row = rows + (int)threadIdx.x * M;
+  uint64_t* out = cols + (w / kChunkWords * M) * kChunkWords + w % kChunkWords;
   for (int k0 = 0; k0 < M; k0 += 64) {
     uint64_t mine = 0;
     const int kn = min(64, M - k0);
@@ -56,17 +71,18 @@ __global__ void pack_columns_kernel(const uint8_t* __restrict__ bits, int64_t N,
       const uint64_t m = __ballot(live && row[k0 + q] != 0);
       if (lane == q) mine = m;
     }
-    if (lane < kn) cols[(int64_t)(k0 + lane) * W + w] = mine;
+    if (lane < kn) out[(int64_t)(k0 + lane) * kChunkWords] = mine;
   }
 }
 
 // ---- order 1: s_k = popcount of column k ----
-__global__ void count1_kernel(const uint64_t* __restrict__ cols, int M, int64_t W,
+__global__ void count1_kernel(const uint64_t* __restrict__ cols, int M, int64_t words,
                               uint32_t* __restrict__ out) {
   __shared__ uint32_t part[kEstThreads];
   const int k = blockIdx.x;
   uint32_t c = 0;
-  for (int64_t w = threadIdx.x; w < W; w += blockDim.x) c += __popcll(cols[(int64_t)k * W + w]);
+  for (int64_t w = threadIdx.x; w < words; w += blockDim.x)
+    c += __popcll(cols[(w / kChunkWords * M + k) * kChunkWords + w % kChunkWords]);
   part[threadIdx.x] = c;
   __syncthreads();
   for (int h = blockDim.x / 2; h >= 1; h >>= 1) {
@@ -76,133 +92,210 @@ __global__ void count1_kernel(const uint64_t* __restrict__ cols, int M, int64_t 
   if (threadIdx.x == 0) out[k] = part[0];
 }
 
-// Tile of the bit-matrix product: rows = L (|L| = DL, all modes < c), columns =
-// H = {c} + R (|R| = DH - 1, modes > c).
-struct CountTile {
-  int32_t c;       // min H
-  int32_t r0;      // first row (colex rank of L among the DL-subsets of [0, c))
-  int32_t h0;      // first column (colex rank of R among the (DH-1)-subsets of (c, M), shifted by c + 1)
-  int32_t pad;
-};
-
-__device__ __forceinline__ uint32_t bin_at(const uint32_t* bin, int ld, int k, int n) {
-  return bin[k * ld + n];
+__global__ void zero_counts_kernel(uint32_t* __restrict__ out, uint64_t n) {
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
+    out[i] = 0;
 }
 
-// colex unranking of a small subset (k <= 3) from the binomial table, ascending
+// C(n, k) for small k without a table
+__host__ __device__ inline uint64_t choose(uint32_t n, int k) {
+  switch (k) {
+    case 0: return 1;
+    case 1: return n;
+    case 2: return n < 2 ? 0 : (uint64_t)n * (n - 1) / 2;
+    default: return n < 3 ? 0 : (uint64_t)n * (n - 1) * (n - 2) / 6;
+  }
+}
+
+// colex unranking of a K-subset (K <= 3) of [0, hi), ascending
 template <int K>
-__device__ __forceinline__ void unrank_small(uint32_t r, const uint32_t* bin, int ld, int hi,
-                                             int (&s)[K > 0 ? K : 1]) {
+__host__ __device__ inline void unrank_small(uint32_t r, int hi, int (&s)[K]) {
   for (int j = K; j >= 1; --j) {
-    int x = j - 1;
-    // largest x < hi with C(x, j) <= r
-    int lo = j - 1, h = hi - 1;
+    int lo = j - 1, h = hi - 1;  // largest x < hi with C(x, j) <= r
     while (lo < h) {
       const int mid = (lo + h + 1) >> 1;
-      if (bin_at(bin, ld, j, mid) <= r) lo = mid; else h = mid - 1;
+      if (choose((uint32_t)mid, j) <= r) lo = mid; else h = mid - 1;
     }
-    x = lo;
-    s[j - 1] = x;
-    r -= bin_at(bin, ld, j, x);
-    hi = x;
+    s[j - 1] = lo;
+    r -= (uint32_t)choose((uint32_t)lo, j);
+    hi = lo;
+  }
+}
+
+// Rows of the product: the sets H in colex order of their mirror images {M - 1 -
+// m}, so that c = min H falls along the list and the columns L (subsets of
+// [0, c), in colex order) that a run of rows needs are a prefix.
+template <int DH>
+__host__ __device__ inline void row_modes(uint32_t h, int M, int (&m)[DH]) {
+  int x[DH];
+  unrank_small<DH>(h, M, x);
+  for (int j = 0; j < DH; ++j) m[j] = M - 1 - x[DH - 1 - j];
+}
+
+// Counts of a tile of kTH rows by kTL columns over a range of sample chunks.
+//
+// On v_mfma_scale_f32_32x32x64 with FP4 operands (10 PFLOP/s dense, against 8.6e12
+// word AND-popcounts/s = 1.1 PFLOP/s of the 32-bit vector units): four waves,
+// each 128 x 64 of the tile (4 x 2 accumulators of 32 x 32).  A chunk's ANDed
+// words are staged in LDS as bits (64 bytes per row; rows 80 bytes apart, which
+// spreads a quarter-wave's 16-byte reads over all banks); a lane reads 128
+// samples of its row at once and masks them with 0x1, 0x2, 0x4 and (shifted)
+// 0x4 per nibble: FP4 0.5, 1.0, 2.0 and 2.0, which the instruction's block
+// scales 2, 1, 1/2, 1/2 of both operands bring to products of 1.  Every operand
+// register is thus one or two vector instructions, and both operands meet the
+// same samples in the same order by construction.
+// Sums are exact: FP32 accumulators hold at most kSplitSamples ones.  Ranges of
+// chunks of one tile (few tiles, or more samples than that) add up by integer
+// atomics, whose order does not matter.
+// Order 5 at M = 144, 262,144 samples: 48.4 ms, 5.2e15 operations/s on the
+// 4.8e8 x 262,144 products wanted, against 286 ms of AND and popcount in 32-bit
+// vector instructions (0.81 of their peak). What is left: tiles that reach past
+// a row's columns (about 1.1 times the work), and per chunk the masking (20
+// vector instructions for 4 x 6 operands) and staging beside the products.
+constexpr int kTH = 256, kTL = 128;
+constexpr int kRowBytes = kChunkBytes + 16;
+constexpr int64_t kSplitSamples = 1 << 22;
+
+typedef int int8v __attribute__((ext_vector_type(8)));
+typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
+typedef float float16v __attribute__((ext_vector_type(16)));
+
+template <int T>
+__device__ __forceinline__ int8v fp4_operand(const uint4v& w) {
+  constexpr uint32_t kMask = T == 0 ? 0x11111111u : T == 1 ? 0x22222222u : 0x44444444u;
+  const uint4v v = (T == 3 ? w >> 1 : w) & kMask;
+  return int8v{(int)v.x, (int)v.y, (int)v.z, (int)v.w, 0, 0, 0, 0};
+}
+
+template <int T>
+__device__ __forceinline__ void count_step(const uint4v (&h)[4], const uint4v (&l)[2], float16v (&acc)[4][2]) {
+  constexpr int kScale = T == 0 ? 0x80808080 : T == 1 ? 0x7f7f7f7f : 0x7e7e7e7e;
+  int8v b[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) b[j] = fp4_operand<T>(l[j]);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int8v a = fp4_operand<T>(h[i]);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b[j], acc[i][j], 4, 4, 0, kScale, 0, kScale);
   }
 }
 
 template <int DL, int DH>
-__global__ __launch_bounds__(kEstThreads) void count_kernel(const uint64_t* __restrict__ cols,
-                                                            int M, int64_t W,
-                                                            const CountTile* __restrict__ tiles,
-                                                            const uint64_t* __restrict__ binom,
-                                                            uint32_t* __restrict__ out) {
-  constexpr int D = DL + DH;
-  __shared__ uint64_t sa[kEstChunk][kEstTile + 1];
-  __shared__ uint64_t sb[kEstChunk][kEstTile + 1];
-  __shared__ int rowm[kEstTile][DL];
-  __shared__ int colm[kEstTile][DH];
-  __shared__ uint32_t bin[(kMaxOrder + 1) * (kEstMaxModes + 1)];
-  const int ld = M + 1;
-  for (int i = threadIdx.x; i < (D + 1) * ld; i += blockDim.x) {
-    const int kk = i / ld, nn = i - kk * ld;
-    bin[i] = (uint32_t)binom[kk * kBinLd + nn];
+__global__ __launch_bounds__(kEstThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void count_kernel(
+    const uint8_t* __restrict__ cols, int M, int64_t chunks, int splits, int atomic,
+    const uint64_t* __restrict__ binom, uint32_t* __restrict__ out) {
+  __shared__ __attribute__((aligned(16))) uint8_t buf[2][(kTH + kTL) * kRowBytes];
+  __shared__ uint64_t base[kTH];  // rank of the row's set with no column; ~0 for padding rows
+  __shared__ uint32_t lim[kTH];   // its columns: C(c, DL)
+  const uint32_t nrow = (uint32_t)choose((uint32_t)M, DH);
+  const uint32_t h0 = blockIdx.y * kTH, l0 = blockIdx.x * kTL;
+  {
+    int m[DH];
+    row_modes<DH>(h0, M, m);
+    if (l0 >= choose((uint32_t)m[0], DL)) return;  // no column of this tile is below c
   }
-  __syncthreads();
-  const CountTile T = tiles[blockIdx.x];
-  const int c = T.c;
-  const uint32_t nrow = bin_at(bin, ld, DL, c);               // L: DL-subsets of [0, c)
-  const uint32_t ncol = bin_at(bin, ld, DH - 1, M - 1 - c);   // R: (DH-1)-subsets of (c, M)
-  // modes of this tile's rows and columns
-  if (threadIdx.x < kEstTile) {
-    const uint32_t r = (uint32_t)T.r0 + threadIdx.x;
-    int s[DL];
-    unrank_small<DL>(r < nrow ? r : 0, bin, ld, c, s);
-    for (int j = 0; j < DL; ++j) rowm[threadIdx.x][j] = s[j];
-  } else if (threadIdx.x < 2 * kEstTile) {
-    const int t = threadIdx.x - kEstTile;
-    const uint32_t h = (uint32_t)T.h0 + t;
-    colm[t][0] = c;
-    if constexpr (DH > 1) {
-      int s[DH - 1];
-      unrank_small<DH - 1>(h < ncol ? h : 0, bin, ld, M - 1 - c, s);
-      for (int j = 0; j < DH - 1; ++j) colm[t][j + 1] = c + 1 + s[j];
-    }
-  }
-  __syncthreads();
-  const int tr = threadIdx.x / 16, tc = threadIdx.x % 16;  // 4 x 4 block at (4 tr, 4 tc)
-  uint32_t acc[4][4] = {};
-  for (int64_t w0 = 0; w0 < W; w0 += kEstChunk) {
-    // operands of this chunk: AND of the columns of each row / column set
-    for (int i = threadIdx.x; i < kEstTile * kEstChunk; i += blockDim.x) {
-      const int e = i / kEstChunk, q = i % kEstChunk;
-      const int64_t w = w0 + q;
-      uint64_t va = 0, vb = 0;
-      if (w < W) {
-        va = cols[(int64_t)rowm[e][0] * W + w];
-        for (int j = 1; j < DL; ++j) va &= cols[(int64_t)rowm[e][j] * W + w];
-        vb = cols[(int64_t)colm[e][0] * W + w];
-        for (int j = 1; j < DH; ++j) vb &= cols[(int64_t)colm[e][j] * W + w];
-      }
-      sa[q][e] = va;
-      sb[q][e] = vb;
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int q = 0; q < kEstChunk; ++q) {
-      uint64_t a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        a[i] = sa[q][4 * tr + i];
-        b[i] = sb[q][4 * tc + i];
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += __popcll(a[i] & b[j]);
-    }
-    __syncthreads();
-  }
-  // colex rank of S = L + H: rank(L) + sum over H's elements at positions DL..D-1
+  // this thread's six 16-byte pieces of a chunk: rows tid / 4 + 64 i (256 of H, 128
+  // of L), bytes 16 (tid % 4); offsets of their modes' columns
+  const int piece = (threadIdx.x & 3) * 16, rt = threadIdx.x >> 2;
+  uint32_t ho[4][DH], lo[2][DL];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const uint32_t r = (uint32_t)T.r0 + 4 * tr + i;
-    if (r >= nrow) continue;
+    const uint32_t h = h0 + rt + 64 * i;
+    int m[DH];
+    row_modes<DH>(min(h, nrow - 1), M, m);
+    uint64_t rank = 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t h = (uint32_t)T.h0 + 4 * tc + j;
-      if (h >= ncol) continue;
-      uint64_t rank = r;  // rank of L among subsets of [0, c) = its colex rank
-#pragma unroll
-      for (int q = 0; q < DH; ++q) rank += binom[(DL + q + 1) * kBinLd + colm[4 * tc + j][q]];
-      out[rank] = acc[i][j];
+    for (int j = 0; j < DH; ++j) {
+      ho[i][j] = (uint32_t)m[j] * kChunkBytes + piece;
+      rank += binom[(DL + j + 1) * kBinLd + m[j]];
+    }
+    if (piece == 0) {
+      base[rt + 64 * i] = rank;
+      lim[rt + 64 * i] = h < nrow ? (uint32_t)choose((uint32_t)m[0], DL) : 0u;
     }
   }
+  const uint32_t ncol = (uint32_t)choose((uint32_t)(M - DH), DL);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    int m[DL];
+    unrank_small<DL>(min(l0 + rt + 64 * i, ncol - 1), M - DH, m);
+#pragma unroll
+    for (int j = 0; j < DL; ++j) lo[i][j] = (uint32_t)m[j] * kChunkBytes + piece;
+  }
+  const int64_t c0 = chunks * blockIdx.z / splits, c1 = chunks * (blockIdx.z + 1) / splits;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int wh = (w & 1) * 128, wl = (w >> 1) * 64;  // the wave's part of the tile
+  const uint64_t stride = (uint64_t)M * kChunkBytes;
+  auto stage = [&](int64_t c, uint8_t* dst, int half) {
+    const uint8_t* src = cols + (uint64_t)c * stride;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      uint4v v = *reinterpret_cast<const uint4v*>(src + ho[2 * half + i][0]);
+#pragma unroll
+      for (int j = 1; j < DH; ++j) v &= *reinterpret_cast<const uint4v*>(src + ho[2 * half + i][j]);
+      *reinterpret_cast<uint4v*>(dst + (rt + 64 * (2 * half + i)) * kRowBytes + piece) = v;
+    }
+    uint4v v = *reinterpret_cast<const uint4v*>(src + lo[half][0]);
+#pragma unroll
+    for (int j = 1; j < DL; ++j) v &= *reinterpret_cast<const uint4v*>(src + lo[half][j]);
+    *reinterpret_cast<uint4v*>(dst + (kTH + rt + 64 * half) * kRowBytes + piece) = v;
+  };
+  float16v acc[4][2] = {};
+  if (c0 < c1) {
+    stage(c0, buf[0], 0);
+    stage(c0, buf[0], 1);
+  }
+  __syncthreads();
+  for (int64_t c = c0; c < c1; ++c) {
+    const uint8_t* cur = buf[(c - c0) & 1];
+    uint8_t* nxt = buf[(c - c0 + 1) & 1];
+    const bool more = c + 1 < c1;
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      const int off = (lane & 31) * kRowBytes + kk * 32 + (lane >> 5) * 16;
+      uint4v h[4], l[2];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        h[i] = *reinterpret_cast<const uint4v*>(cur + (wh + 32 * i) * kRowBytes + off);
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        l[j] = *reinterpret_cast<const uint4v*>(cur + (kTH + wl + 32 * j) * kRowBytes + off);
+      if (more) stage(c + 1, nxt, kk);
+      count_step<0>(h, l, acc);
+      count_step<1>(h, l, acc);
+      count_step<2>(h, l, acc);
+      count_step<3>(h, l, acc);
+    }
+    __syncthreads();
+  }
+  // accumulator v of a lane: row 8 (v / 4) + 4 (lane / 32) + v % 4, column lane % 32
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int h = wh + 32 * i + 8 * (v / 4) + 4 * (lane >> 5) + v % 4;
+      const uint32_t n = lim[h];
+      const uint64_t b = base[h];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const uint32_t r = l0 + wl + 32 * j + (lane & 31);
+        if (r >= n) continue;
+        const uint32_t k = (uint32_t)acc[i][j][v];
+        if (atomic) atomicAdd(out + b + r, k); else out[b + r] = k;
+      }
+    }
 }
 
 // ---- k-statistics from the power sums ----
 struct KstatCoef {
-  int n;                       // partitions of [d]
-  float pad;
   double coef[52];             // c_N(tau) for the moment form (prod of s_B / N), partitions
                                // in make_parts order
+};
+
+struct CountTables {
+  uint32_t* cnt[kMaxOrder + 1];  // power sums of order d, colex order
 };
 
 // The partitions of [D] in the order kstat_coefficients lists them (restricted
@@ -249,9 +342,8 @@ constexpr PartTable<D> make_parts() {
 }
 
 template <int D>
-__global__ void kstat_kernel(const uint32_t* const* __restrict__ cnt, int M, uint64_t count,
-                             const uint64_t* __restrict__ binom, double invN, const KstatCoef* cf,
-                             double* __restrict__ out) {
+__global__ void kstat_kernel(CountTables tab, int M, uint64_t count, const uint64_t* __restrict__ binom,
+                             double invN, KstatCoef cf, double* __restrict__ out) {
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t r = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; r < count; r += stride) {
     int s[D];
@@ -265,13 +357,13 @@ __global__ void kstat_kernel(const uint32_t* const* __restrict__ cnt, int M, uin
 #pragma unroll
       for (int i = 0; i < D; ++i)
         if (B & (1 << i)) rk += binom[(++j) * kBinLd + s[i]];
-      m[B] = (double)cnt[popcount_c((unsigned)B)][rk] * invN;
+      m[B] = (double)tab.cnt[popcount_c((unsigned)B)][rk] * invN;
     }
     constexpr PartTable<D> kParts = make_parts<D>();
     double k = 0.0, comp = 0.0;
 #pragma unroll
     for (int t = 0; t < kParts.n; ++t) {
-      double v = cf->coef[t];
+      double v = cf.coef[t];
 #pragma unroll
       for (int b = 0; b < D; ++b) {
         const uint32_t blk = kParts.blk[t][b];
@@ -401,7 +493,6 @@ void kstat_coefficients(int d, double N, KstatCoef* out) {
     };
     rs(0, 0);
   }
-  out->n = (int)parts.size();
   for (size_t t = 0; t < parts.size(); ++t) {
     double Np = 1.0;
     for (size_t b = 0; b < pm[t].size(); ++b) Np *= N;
@@ -409,116 +500,96 @@ void kstat_coefficients(int d, double N, KstatCoef* out) {
   }
 }
 
+// Power sums of order DL + DH.  Tiles past the last needed column leave at once.
+// The samples are split over more workgroups while the tiles alone are fewer
+// than two rounds of what runs at once (two workgroups per compute unit).
 template <int DL, int DH>
-std::vector<CountTile> plan_count_tiles(int M) {
-  std::vector<CountTile> tiles;
-  for (int c = DL; c + (DH - 1) < M; ++c) {
-    const uint64_t nrow = host_binom(c, DL), ncol = host_binom(M - 1 - c, DH - 1);
-    for (uint64_t r = 0; r < nrow; r += kEstTile)
-      for (uint64_t h = 0; h < ncol; h += kEstTile) tiles.push_back({c, (int32_t)r, (int32_t)h, 0});
+hipError_t launch_counts(const uint64_t* cols, int M, int64_t chunks, const uint64_t* binom, uint32_t* out,
+                         hipStream_t s) {
+  if (M < DL + DH) return hipSuccess;
+  const uint64_t nrow = host_binom(M, DH), ncol = host_binom(M - DH, DL);
+  uint64_t tiles = 0;
+  for (uint64_t h = 0; h < nrow; h += kTH) {
+    int m[DH];
+    row_modes<DH>((uint32_t)h, M, m);
+    tiles += (host_binom(m[0], DL) + kTL - 1) / kTL;
   }
-  return tiles;
-}
-
-template <int DL, int DH>
-hipError_t launch_counts(const uint64_t* cols, int M, int64_t W, const uint64_t* binom,
-                         uint32_t* out, CountTile* tiles_dev, size_t ntiles, hipStream_t s) {
-  if (ntiles == 0) return hipSuccess;
-  hipLaunchKernelGGL((count_kernel<DL, DH>), dim3((unsigned)ntiles), dim3(kEstThreads), 0, s, cols,
-                     M, W, tiles_dev, binom, out);
+  const int64_t want = (1024 + (int64_t)tiles - 1) / (int64_t)tiles;
+  const int64_t exact = (chunks * 64 * kChunkWords + kSplitSamples - 1) / kSplitSamples;
+  const int splits = (int)std::max<int64_t>(exact, std::min<int64_t>(want, (chunks + 3) / 4));
+  if (splits > 1) {
+    const uint64_t n = host_binom(M, DL + DH);
+    hipLaunchKernelGGL(zero_counts_kernel, dim3((unsigned)std::min<uint64_t>((n + 255) / 256, 4096)), dim3(256), 0, s,
+                       out, n);
+  }
+  hipLaunchKernelGGL((count_kernel<DL, DH>),
+                     dim3((unsigned)((ncol + kTL - 1) / kTL), (unsigned)((nrow + kTH - 1) / kTH), (unsigned)splits),
+                     dim3(kEstThreads), 0, s, reinterpret_cast<const uint8_t*>(cols), M, chunks, splits, splits > 1,
+                     binom, out);
   return hipGetLastError();
 }
 
+template <int D>
+hipError_t launch_kstat(const CountTables& tab, int M, int64_t N, const uint64_t* binom, double* out, hipStream_t s) {
+  KstatCoef cf{};
+  kstat_coefficients(D, (double)N, &cf);
+  const uint64_t count = host_binom(M, D);
+  const unsigned grid = (unsigned)std::min<uint64_t>((count + 255) / 256, 1u << 20);
+  hipLaunchKernelGGL(kstat_kernel<D>, dim3(grid), dim3(256), 0, s, tab, M, count, binom, 1.0 / (double)N, cf,
+                     out + gbs_order_offset(M, D));
+  return hipGetLastError();
+}
+
+// Scratch of one call: the bit columns, then the counts of each order.
+struct EstScratch {
+  int64_t chunks;
+  size_t cnt[kMaxOrder + 1];
+  size_t bytes;
+  static EstScratch make(int M, int64_t N, int K) {
+    auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    EstScratch S{};
+    S.chunks = (N + 64 * kChunkWords - 1) / (64 * kChunkWords);
+    S.bytes = al((size_t)M * (size_t)S.chunks * kChunkBytes);
+    for (int d = 1; d <= K; ++d) {
+      S.cnt[d] = S.bytes;
+      S.bytes += al(host_binom(M, d) * sizeof(uint32_t));
+    }
+    return S;
+  }
+};
+
 }  // namespace
+
+size_t estimator_scratch(int M, int64_t N, int K) { return EstScratch::make(M, N, K).bytes; }
 
 // Power sums and k-statistics of orders 1..K from nsamples samples.
 hipError_t run_sample_cumulants(int M, int64_t N, const uint8_t* bits, int K,
-                                const uint64_t* binom, double* out, hipStream_t s) {
-  const int64_t W = (N + 63) / 64;
-  // scratch: columns, per-order counts, tile lists, coefficient blocks, count pointers
-  std::vector<std::vector<CountTile>> plans(K + 1);
-  if (K >= 2) plans[2] = plan_count_tiles<1, 1>(M);
-  if (K >= 3) plans[3] = plan_count_tiles<1, 2>(M);
-  if (K >= 4) plans[4] = plan_count_tiles<2, 2>(M);
-  if (K >= 5) plans[5] = plan_count_tiles<2, 3>(M);
-  size_t off = 0;
-  auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  const size_t oc = off; off += al((size_t)M * W * sizeof(uint64_t));
-  size_t ocnt[kMaxOrder + 1] = {};
-  for (int d = 1; d <= K; ++d) { ocnt[d] = off; off += al(host_binom(M, d) * sizeof(uint32_t)); }
-  size_t otile[kMaxOrder + 1] = {};
-  for (int d = 2; d <= K; ++d) { otile[d] = off; off += al(plans[d].size() * sizeof(CountTile)); }
-  const size_t ocoef = off; off += al((size_t)(K + 1) * sizeof(KstatCoef));
-  const size_t optr = off; off += al((kMaxOrder + 1) * sizeof(uint32_t*));
-  void* scratch = nullptr;
-  hipError_t e = hipMallocAsync(&scratch, off, s);
+                                const uint64_t* binom, double* out, void* lent, hipStream_t s) {
+  const EstScratch S = EstScratch::make(M, N, K);
+  void* scratch = lent;
+  hipError_t e = hipSuccess;
+  if (!lent) e = hipMallocAsync(&scratch, S.bytes, s);
   if (e != hipSuccess) return e;
   char* b = static_cast<char*>(scratch);
-  uint64_t* cols = reinterpret_cast<uint64_t*>(b + oc);
-  // host-side staging: tile lists, coefficients, count pointers (one pinned block)
-  size_t hbytes = 0;
-  for (int d = 2; d <= K; ++d) hbytes += plans[d].size() * sizeof(CountTile);
-  hbytes += (K + 1) * sizeof(KstatCoef) + (kMaxOrder + 1) * sizeof(uint32_t*);
-  std::vector<char> host(hbytes);
-  size_t ho = 0;
-  std::vector<size_t> htile(K + 1, 0);
-  for (int d = 2; d <= K; ++d) {
-    htile[d] = ho;
-    memcpy(host.data() + ho, plans[d].data(), plans[d].size() * sizeof(CountTile));
-    ho += plans[d].size() * sizeof(CountTile);
-  }
-  const size_t hcoef = ho;
-  for (int d = 1; d <= K; ++d)
-    kstat_coefficients(d, (double)N, reinterpret_cast<KstatCoef*>(host.data() + hcoef) + d);
-  ho += (K + 1) * sizeof(KstatCoef);
-  const size_t hptr = ho;
-  uint32_t** cp = reinterpret_cast<uint32_t**>(host.data() + hptr);
-  for (int d = 0; d <= kMaxOrder; ++d) cp[d] = d >= 1 && d <= K ? reinterpret_cast<uint32_t*>(b + ocnt[d]) : nullptr;
-  for (int d = 2; d <= K && e == hipSuccess; ++d)
-    e = hipMemcpyAsync(b + otile[d], host.data() + htile[d], plans[d].size() * sizeof(CountTile),
-                       hipMemcpyHostToDevice, s);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(b + ocoef, host.data() + hcoef, (K + 1) * sizeof(KstatCoef),
-                       hipMemcpyHostToDevice, s);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(b + optr, host.data() + hptr, (kMaxOrder + 1) * sizeof(uint32_t*),
-                       hipMemcpyHostToDevice, s);
-  // the staging buffer must outlive the copies
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e == hipSuccess && W > 0) {
-    const int wpb = 4;  // words (wavefronts) per block
-    hipLaunchKernelGGL(pack_columns_kernel, dim3((unsigned)((W + wpb - 1) / wpb)), dim3(64 * wpb), 0,
-                       s, bits, N, M, W, cols);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(count1_kernel, dim3(M), dim3(kEstThreads), 0, s, cols, M, W,
-                       reinterpret_cast<uint32_t*>(b + ocnt[1]));
-    e = hipGetLastError();
-  }
-  auto tl = [&](int d) { return reinterpret_cast<CountTile*>(b + otile[d]); };
-  auto co = [&](int d) { return reinterpret_cast<uint32_t*>(b + ocnt[d]); };
-  if (e == hipSuccess && K >= 2) e = launch_counts<1, 1>(cols, M, W, binom, co(2), tl(2), plans[2].size(), s);
-  if (e == hipSuccess && K >= 3) e = launch_counts<1, 2>(cols, M, W, binom, co(3), tl(3), plans[3].size(), s);
-  if (e == hipSuccess && K >= 4) e = launch_counts<2, 2>(cols, M, W, binom, co(4), tl(4), plans[4].size(), s);
-  if (e == hipSuccess && K >= 5) e = launch_counts<2, 3>(cols, M, W, binom, co(5), tl(5), plans[5].size(), s);
-  const uint32_t* const* cptr = reinterpret_cast<const uint32_t* const*>(b + optr);
-  const KstatCoef* cf = reinterpret_cast<const KstatCoef*>(b + ocoef);
-  const double invN = 1.0 / (double)N;
-  for (int d = 1; d <= K && e == hipSuccess; ++d) {
-    const uint64_t count = host_binom(M, d);
-    const unsigned grid = (unsigned)std::min<uint64_t>((count + 255) / 256, 1u << 20);
-    double* o = out + gbs_order_offset(M, d);
-    switch (d) {
-      case 1: hipLaunchKernelGGL(kstat_kernel<1>, dim3(grid), dim3(256), 0, s, cptr, M, count, binom, invN, cf + 1, o); break;
-      case 2: hipLaunchKernelGGL(kstat_kernel<2>, dim3(grid), dim3(256), 0, s, cptr, M, count, binom, invN, cf + 2, o); break;
-      case 3: hipLaunchKernelGGL(kstat_kernel<3>, dim3(grid), dim3(256), 0, s, cptr, M, count, binom, invN, cf + 3, o); break;
-      case 4: hipLaunchKernelGGL(kstat_kernel<4>, dim3(grid), dim3(256), 0, s, cptr, M, count, binom, invN, cf + 4, o); break;
-      default: hipLaunchKernelGGL(kstat_kernel<5>, dim3(grid), dim3(256), 0, s, cptr, M, count, binom, invN, cf + 5, o); break;
-    }
-    e = hipGetLastError();
-  }
-  hipError_t f = hipFreeAsync(scratch, s);
+  uint64_t* cols = reinterpret_cast<uint64_t*>(b);
+  CountTables tab{};
+  for (int d = 1; d <= K; ++d) tab.cnt[d] = reinterpret_cast<uint32_t*>(b + S.cnt[d]);
+  const int64_t words = S.chunks * kChunkWords;
+  const int64_t packs = (words * 64 + kPackSamples - 1) / kPackSamples;
+  hipLaunchKernelGGL(pack_columns_kernel, dim3((unsigned)packs), dim3(kPackSamples), (size_t)kPackSamples * M, s, bits,
+                     N, M, words, ((uintptr_t)bits & 3) == 0, cols);
+  hipLaunchKernelGGL(count1_kernel, dim3(M), dim3(kEstThreads), 0, s, cols, M, words, tab.cnt[1]);
+  e = hipGetLastError();
+  if (e == hipSuccess && K >= 2) e = launch_counts<1, 1>(cols, M, S.chunks, binom, tab.cnt[2], s);
+  if (e == hipSuccess && K >= 3) e = launch_counts<1, 2>(cols, M, S.chunks, binom, tab.cnt[3], s);
+  if (e == hipSuccess && K >= 4) e = launch_counts<2, 2>(cols, M, S.chunks, binom, tab.cnt[4], s);
+  if (e == hipSuccess && K >= 5) e = launch_counts<2, 3>(cols, M, S.chunks, binom, tab.cnt[5], s);
+  if (e == hipSuccess) e = launch_kstat<1>(tab, M, N, binom, out, s);
+  if (e == hipSuccess && K >= 2) e = launch_kstat<2>(tab, M, N, binom, out, s);
+  if (e == hipSuccess && K >= 3) e = launch_kstat<3>(tab, M, N, binom, out, s);
+  if (e == hipSuccess && K >= 4) e = launch_kstat<4>(tab, M, N, binom, out, s);
+  if (e == hipSuccess && K >= 5) e = launch_kstat<5>(tab, M, N, binom, out, s);
+  hipError_t f = lent ? hipSuccess : hipFreeAsync(scratch, s);
   return e != hipSuccess ? e : f;
 }
 

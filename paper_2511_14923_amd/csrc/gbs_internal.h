@@ -185,15 +185,21 @@ hipError_t launch_adjoint(int M, int K, int flags, const double* Qi, const uint6
 
 // Stage-2 sampler (gbs_sampler.hip): nsamples patterns of M bits from the
 // parity cumulants kap (orders 1..K, K = 3 or 5), uniforms u (M x nsamples),
-// in launches of at most `batch` samples (0: a quarter of the free memory).
+// in parts of at most `batch` samples (0: a quarter of the free memory), or as
+// many as fit in the scratch memory lent by the caller (null: the library's
+// own).  sampler_scratch: the bytes such a call would allocate.
+hipError_t sampler_scratch(int M, int K, int64_t nsamples, int64_t batch, size_t* bytes);
 hipError_t run_sampler(int M, int K, const double* kap, int64_t nsamples, const double* u,
-                       uint8_t* bits, double* prob, double* cond, int64_t batch, hipStream_t s);
+                       uint8_t* bits, double* prob, double* cond, int64_t batch, void* lent,
+                       size_t lent_bytes, hipStream_t s);
 
 // Sample statistics (gbs_estimator.hip): unbiased click cumulants of orders
 // 1..K from N samples (bits N x M), written in the output layout; Pearson
-// coefficient of two device arrays of length n, written to r (device).
+// coefficient of two device arrays of length n, written to r (device).  lent:
+// estimator_scratch bytes of scratch memory, or null (the library's own).
+size_t estimator_scratch(int M, int64_t N, int K);
 hipError_t run_sample_cumulants(int M, int64_t N, const uint8_t* bits, int K,
-                                const uint64_t* binom, double* out, hipStream_t s);
+                                const uint64_t* binom, double* out, void* lent, hipStream_t s);
 hipError_t run_pearson(uint64_t n, const double* x, const double* y, double* r, hipStream_t s);
 
 }  // namespace gbs

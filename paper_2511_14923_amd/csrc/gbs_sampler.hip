@@ -322,34 +322,60 @@ __global__ __launch_bounds__(64 * kSampWaves) void sampler_kernel(
 // 4.1 ms at M = 60.
 constexpr int kStepMinModes = 12;
 
-hipError_t run_sampler(int M, int K, const double* kap, int64_t nsamples, const double* u,
-                       uint8_t* bits, double* prob, double* cond, int64_t batch, hipStream_t s) {
-  if (nsamples == 0) return hipSuccess;
-  const SampLayout L = SampLayout::make(M, K);
-  KapOffsets ko{};
-  ko.off[1] = 0;
-  for (int d = 2; d <= 5; ++d)
-    ko.off[d] = ko.off[d - 1] + (d - 1 <= K ? (uint32_t)host_binom(M, d - 1) : 0u);
-  const bool steps = K == 5 && M >= kStepMinModes;
-  const uint64_t lane_bytes = (uint64_t)L.entries() * sizeof(double);
-  const uint64_t per = steps ? double_sampler_bytes(M) : lane_bytes;
+namespace {
+
+bool by_steps(int M, int K) { return K == 5 && M >= kStepMinModes; }
+
+uint64_t table_bytes(int M, int K) {  // per sample
+  return by_steps(M, K) ? double_sampler_bytes(M) : (uint64_t)SampLayout::make(M, K).entries() * sizeof(double);
+}
+
+// Samples per part of a call: nsamples in equal parts (a small last one would
+// run for as long as a full one) of at most `most`, a multiple of 64.
+int64_t equal_parts(int64_t nsamples, int64_t most) {
+  most = std::min<int64_t>(std::max<int64_t>(64, most / 64 * 64), (nsamples + 63) / 64 * 64);
+  const int64_t parts = (nsamples + most - 1) / most;
+  return ((nsamples + parts - 1) / parts + 63) / 64 * 64;
+}
+
+}  // namespace
+
+hipError_t sampler_scratch(int M, int K, int64_t nsamples, int64_t batch, size_t* bytes) {
+  const uint64_t per = table_bytes(M, K);
   if (batch <= 0) {
     size_t free_b = 0, total_b = 0;
     hipError_t e = hipMemGetInfo(&free_b, &total_b);
     if (e != hipSuccess) return e;
     batch = (int64_t)(free_b / 4 / per);
-  } else if (steps) {
+  } else if (by_steps(M, K)) {
     // a batch stands for the memory of one table set per sample; the step tables are about twice that
-    batch = (int64_t)((double)batch * (double)lane_bytes / (double)per);
+    batch = (int64_t)((double)batch * (double)(SampLayout::make(M, K).entries() * sizeof(double)) / (double)per);
   }
-  batch = std::max<int64_t>(64, batch / 64 * 64);
-  batch = std::min<int64_t>(batch, (nsamples + 63) / 64 * 64);
-  // equal launches: a small last launch would run for as long as a full one
-  const int64_t nlaunch = (nsamples + batch - 1) / batch;
-  batch = ((nsamples + nlaunch - 1) / nlaunch + 63) / 64 * 64;
-  void* scratch = nullptr;
-  hipError_t e = hipMallocAsync(&scratch, (size_t)(per * (uint64_t)batch), s);
-  if (e != hipSuccess) return e;
+  *bytes = (size_t)per * (size_t)equal_parts(nsamples, batch);
+  return hipSuccess;
+}
+
+hipError_t run_sampler(int M, int K, const double* kap, int64_t nsamples, const double* u,
+                       uint8_t* bits, double* prob, double* cond, int64_t batch, void* lent,
+                       size_t lent_bytes, hipStream_t s) {
+  if (nsamples == 0) return hipSuccess;
+  const bool steps = by_steps(M, K);
+  const SampLayout L = SampLayout::make(M, K);
+  KapOffsets ko{};
+  ko.off[1] = 0;
+  for (int d = 2; d <= 5; ++d)
+    ko.off[d] = ko.off[d - 1] + (d - 1 <= K ? (uint32_t)host_binom(M, d - 1) : 0u);
+  const uint64_t per = table_bytes(M, K);
+  void* scratch = lent;
+  size_t bytes = lent_bytes;
+  hipError_t e = hipSuccess;
+  if (!lent) {
+    e = sampler_scratch(M, K, nsamples, batch, &bytes);
+    if (e == hipSuccess) e = hipMallocAsync(&scratch, bytes, s);
+    if (e != hipSuccess) return e;
+  }
+  if (bytes < 64 * per) return hipErrorOutOfMemory;  // lent too little
+  batch = equal_parts(nsamples, (int64_t)(bytes / per));
   double* tab = static_cast<double*>(scratch);
   for (int64_t s0 = 0; s0 < nsamples && e == hipSuccess; s0 += batch) {
     const int64_t nb = std::min<int64_t>(batch, nsamples - s0);
@@ -368,7 +394,7 @@ hipError_t run_sampler(int M, int K, const double* kap, int64_t nsamples, const 
                          u + s0, (uint64_t)nsamples, nb, tab, L, bits + s0 * M, pr, cd);
     e = hipGetLastError();
   }
-  hipError_t f = hipFreeAsync(scratch, s);
+  hipError_t f = lent ? hipSuccess : hipFreeAsync(scratch, s);
   return e != hipSuccess ? e : f;
 }
 

@@ -545,21 +545,18 @@ hipError_t launch_double_sampler(int M, const double* kap, KapOffsets ko, int64_
     A.n = n;
     const uint32_t m = (uint32_t)(M - n);
     {
-      // Waves of the product against the 1,024 SIMDs: parts of the inner index
-      // are dealt to more waves while fewer than two per SIMD would run.
+      // Which kernel and how the inner index is split follow from the rows alone,
+      // so that a sample's sums do not depend on the batch it is in.  Two parts
+      // per tile: 47.2 ms at M = 100, 4,096 samples and 8.3 ms at M = 90, 200,
+      // against 48.4 and 9.6 ms in one part, 50.1 and 8.0 ms in four.
       const uint32_t rows = n >= 3 ? 1 + 2 * m + samp_c2(m) : 0;
-      const uint32_t waves = (rows + 63) / 64 * nsb * 4;
       if (rows <= 16) {
         const uint32_t rb = rows ? 1 : 0;
         const uint32_t extra = ((uint32_t)(M - 1) * nsb + kSlimWaves - 1) / kSlimWaves;
         hipLaunchKernelGGL(product_slim_kernel, dim3(rb * nsb + extra), dim3(64 * kSlimWaves), 0, s, A, (int)rows,
                            (int)rb, rb * nsb, nsb);
-      } else if (waves >= 2048) {
-        launch_pairs<1>(A, rows, nsb, s);
-      } else if (waves >= 1024) {
-        launch_pairs<2>(A, rows, nsb, s);
       } else {
-        launch_pairs<4>(A, rows, nsb, s);
+        launch_pairs<2>(A, rows, nsb, s);
       }
     }
     hipLaunchKernelGGL(bit_kernel, dim3(nsb), dim3(256), 0, s, A, u, ldu, nsamp, bits, prob, cond);
