@@ -36,5 +36,10 @@ size_t double_sampler_bytes(int M);
 hipError_t launch_double_sampler(int M, const double* kap, KapOffsets ko, int64_t nsamp, const double* u,
                                  uint64_t ldu, double* tab, uint8_t* bits, double* prob, double* cond,
                                  hipStream_t s);
+// The same for single elision (gbs_sampler_single.hip).
+size_t single_sampler_bytes(int M);
+hipError_t launch_single_sampler(int M, const double* kap, KapOffsets ko, int64_t nsamp, const double* u,
+                                 uint64_t ldu, double* tab, uint8_t* bits, double* prob, double* cond,
+                                 hipStream_t s);
 
 }  // namespace gbs

@@ -1,6 +1,6 @@
 // Stage-2 sampler: click patterns drawn bit by bit from the parity cumulants.
-// Single elision, double elision of few modes, and the batches of both; double
-// elision of more modes runs in gbs_sampler_double.hip.
+// This file runs few modes, and the batches of all; more modes run step by step
+// over all samples in gbs_sampler_single.hip and gbs_sampler_double.hip.
 //
 // The chain rule p(x_n | x_{n-1}, .., x_1) = p(x_n, .., x_1) / p(x_{n-1}, .., x_1)
 // with the joint probability expanded in the parity cumulants kappa(S) up to
@@ -321,13 +321,19 @@ __global__ __launch_bounds__(64 * kSampWaves) void sampler_kernel(
 // (here) against 0.23 ms at M = 8, 0.69 against 0.44 ms at M = 16, 102 against
 // 4.1 ms at M = 60.
 constexpr int kStepMinModes = 12;
+// The same for single elision (gbs_sampler_single.hip, three launches per bit):
+// 1,000 samples take 0.38 (here) against 0.41 ms at M = 20, 1.04 against 0.67 ms
+// at M = 30; 200 samples 37 against 4.2 ms at M = 100; 10,000 samples 12.6
+// against 2.8 ms at M = 60.
+constexpr int kSingleStepMinModes = 24;
 
 namespace {
 
-bool by_steps(int M, int K) { return K == 5 && M >= kStepMinModes; }
+bool by_steps(int M, int K) { return M >= (K == 5 ? kStepMinModes : kSingleStepMinModes); }
 
 uint64_t table_bytes(int M, int K) {  // per sample
-  return by_steps(M, K) ? double_sampler_bytes(M) : (uint64_t)SampLayout::make(M, K).entries() * sizeof(double);
+  if (by_steps(M, K)) return K == 5 ? double_sampler_bytes(M) : single_sampler_bytes(M);
+  return (uint64_t)SampLayout::make(M, K).entries() * sizeof(double);
 }
 
 // Samples per part of a call: nsamples in equal parts (a small last one would
@@ -383,7 +389,8 @@ hipError_t run_sampler(int M, int K, const double* kap, int64_t nsamples, const 
     double* pr = prob ? prob + s0 : nullptr;
     double* cd = cond ? cond + s0 : nullptr;
     if (steps) {
-      e = launch_double_sampler(M, kap, ko, nb, u + s0, (uint64_t)nsamples, tab, bits + s0 * M, pr, cd, s);
+      e = (K == 5 ? launch_double_sampler : launch_single_sampler)(
+          M, kap, ko, nb, u + s0, (uint64_t)nsamples, tab, bits + s0 * M, pr, cd, s);
       continue;
     }
     if (K == 3)

@@ -33,7 +33,11 @@
 //
 // Per sample the order-5 sum is C(M, 5) multiply-adds and reads C(M, 3) table
 // entries once in all; the U update reads C(n - 1, 3) entries at step n, C(M, 4)
-// in all, and is bound by memory bandwidth.
+// in all, halved by taking two steps in a pass (update_kernel), and is bound by
+// memory bandwidth (4.8 TB/s; a large copy reaches 4.6).
+// M = 100, 4,096 samples: 45.4 ms (21 of them U updates, 17 products over pairs,
+// 7 products over j) against 1,090 ms of one workgroup per 64 samples, which
+// reads every U entry several times per bit.
 //
 // Storage: per block of 64 samples one contiguous block, entry-major, the 64
 // samples of an entry consecutive, so every access of a wavefront is 512
@@ -46,17 +50,11 @@
 
 #include "gbs_internal.h"
 #include "gbs_sampler.h"
+#include "gbs_sampler_product.h"
 
 namespace gbs {
 
 namespace {
-
-typedef double double4 __attribute__((ext_vector_type(4)));
-typedef double double2v __attribute__((ext_vector_type(2)));
-
-constexpr int kSB = 64;        // samples per block of the tables
-constexpr int kKC = 16;        // inner indices per operand chunk
-constexpr int kLdB = kSB + 4;  // LDS row of an operand chunk (rows 4 apart fall on other banks)
 
 // Entries of one sample's storage (each kSB doubles in a block).
 struct Store {
@@ -200,12 +198,7 @@ __device__ __forceinline__ void partial_item(const StepArgs& A, uint32_t item, u
         blk[(uint64_t)(A.st.chi + (uint32_t)l - 1) * kSB] * v;
 }
 
-// 64 rows x 64 samples of a product per workgroup of 4 KS waves: wave w owns
-// rows 16 (w % 4).. + 15, all 64 samples (four 16 x 16 FP64 tiles) and every
-// KS-th chunk of the inner index; the KS partial tiles are added in a fixed
-// order through LDS.  The rows' cumulants go from memory straight to registers
-// (a lane's four inner indices are consecutive); the samples' operand is shared
-// by the waves through LDS, double-buffered.
+// A product of step n, 64 rows x 64 samples per workgroup (gbs_sampler_product.h).
 // SINGLE: the product over j at fixed e, else the product over pairs.
 // Workgroups past the product's carry the sums that are independent of it: w
 // and ZR beside the product over pairs, p+ beside the product over j.
@@ -213,111 +206,32 @@ template <bool SINGLE, int KS>
 __global__ __launch_bounds__(256 * KS) void product_kernel(StepArgs A, int rows, int row_blocks,
                                                            uint32_t nprod, uint32_t nsb) {
   __shared__ double Bs[2][KS][kKC][kLdB];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   if (blockIdx.x >= nprod) {
-    const uint32_t item = (blockIdx.x - nprod) * (4 * KS) + (uint32_t)w;
-    if constexpr (SINGLE) partial_item(A, item, nsb, lane);
-    else reduce_item(A, item, nsb, lane);
+    const uint32_t item = (blockIdx.x - nprod) * (4 * KS) + (threadIdx.x >> 6);
+    if constexpr (SINGLE) partial_item(A, item, nsb, threadIdx.x & 63);
+    else reduce_item(A, item, nsb, threadIdx.x & 63);
     return;
   }
-  const int g = lane >> 4, c16 = lane & 15, wr = w & 3, wk = w >> 2;
-  const int n = A.n;
-  const int rb = (int)(blockIdx.x % (uint32_t)row_blocks);
+  const int n = A.n, rb = (int)(blockIdx.x % (uint32_t)row_blocks);
   uint32_t sb = blockIdx.x / (uint32_t)row_blocks;
-  int e = 0;
   if constexpr (SINGLE) {
-    e = 1 + (int)(sb % (uint32_t)(n - 1));
-    sb /= (uint32_t)(n - 1);
-  }
-  const int L = SINGLE ? n - 1 : (int)samp_r2(n);
-  double* blk = block_of(A, sb);
-  const double* V = blk + (uint64_t)(A.st.U + samp_r3(n)) * kSB;
-  const int r0 = rb * 64 + wr * 16;
-  const bool busy = r0 < rows;  // a wave of padding rows only shares the loads
-  const int ra = min(r0 + c16, rows - 1);
-  const double* ka = A.kap + (SINGLE ? single_row(A, ra, e) : pair_row(A, ra)).kap;
-  // this thread's share of an operand chunk: row kr, columns kc..kc + 3 of chunk wk
-  const int kr = (threadIdx.x & 255) >> 4, kc = (threadIdx.x & 15) * 4;
-  auto load_b = [&](int k0, double2v& b0, double2v& b1) {
-    const int k = k0 + kr;
-    b0 = double2v{0.0, 0.0};
-    b1 = b0;
-    const double* p;
-    if constexpr (SINGLE) {
-      const int j = k + 1;
-      if (j >= n || j == e) return;
-      p = V + (uint64_t)(samp_r2(max(j, e)) + (uint32_t)min(j, e) - 1) * kSB + kc;
-    } else {
-      if (k >= L) return;
-      p = V + (uint64_t)k * kSB + kc;
-    }
-    b0 = *reinterpret_cast<const double2v*>(p);
-    b1 = *reinterpret_cast<const double2v*>(p + 2);
-  };
-  auto load_a = [&](int k0, double (&a)[4]) {
-    const int k = k0 + 4 * g;
-    if (k0 + kKC <= L) {
-#pragma unroll
-      for (int t = 0; t < 4; ++t) a[t] = ka[k + t];
-    } else {
-#pragma unroll
-      for (int t = 0; t < 4; ++t) a[t] = k + t < L ? ka[k + t] : 0.0;
-    }
-  };
-  double4 acc[4] = {};
-  double a[4], an[4] = {};
-  double2v b0, b1;
-  load_b(wk * kKC, b0, b1);
-  load_a(wk * kKC, a);
-  const int nch = (L + kKC * KS - 1) / (kKC * KS);
-  for (int c = 0; c < nch; ++c) {
-    double (&S)[kKC][kLdB] = Bs[c & 1][wk];
-    *reinterpret_cast<double2v*>(&S[kr][kc]) = b0;
-    *reinterpret_cast<double2v*>(&S[kr][kc + 2]) = b1;
-    __syncthreads();
-    if (c + 1 < nch) {
-      load_b(((c + 1) * KS + wk) * kKC, b0, b1);
-      load_a(((c + 1) * KS + wk) * kKC, an);
-    }
-    if (busy) {
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct)
-          acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], S[4 * g + t][ct * 16 + c16], acc[ct], 0, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int t = 0; t < 4; ++t) a[t] = an[t];
-  }
-  if constexpr (KS > 1) {
-    double* red = &Bs[0][0][0][0];  // KS / 2 x 64 x 64 fits the operand buffers
-    for (int half = KS / 2; half >= 1; half /= 2) {
-      __syncthreads();
-      if (wk >= half && wk < 2 * half) {
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            red[(((wk - half) * 4 + wr) * 16 + ct * 4 + v) * 64 + lane] = acc[ct][v];
-      }
-      __syncthreads();
-      if (wk < half) {
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) acc[ct][v] += red[((wk * 4 + wr) * 16 + ct * 4 + v) * 64 + lane];
-      }
-    }
-    if (wk != 0) return;
-  }
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int r = r0 + g + 4 * v;
-    if (r >= rows) continue;
-    double* o = blk + (uint64_t)(SINGLE ? single_row(A, r, e) : pair_row(A, r)).dest * kSB + c16;
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) o[ct * 16] = acc[ct][v];
+    const int e = 1 + (int)(sb % (uint32_t)(n - 1));
+    double* blk = block_of(A, sb / (uint32_t)(n - 1));
+    const double* V = blk + (uint64_t)(A.st.U + samp_r3(n)) * kSB;
+    product_block<KS>(
+        rb, rows, n - 1, [&](int r) { return A.kap + single_row(A, r, e).kap; },
+        [&](int k) -> const double* {
+          const int j = k + 1;
+          return j == e ? nullptr : V + (uint64_t)(samp_r2(max(j, e)) + (uint32_t)min(j, e) - 1) * kSB;
+        },
+        [&](int r) { return blk + (uint64_t)single_row(A, r, e).dest * kSB; }, Bs);
+  } else {
+    double* blk = block_of(A, sb);
+    const double* V = blk + (uint64_t)(A.st.U + samp_r3(n)) * kSB;
+    product_block<KS>(
+        rb, rows, (int)samp_r2(n), [&](int r) { return A.kap + pair_row(A, r).kap; },
+        [&](int k) { return V + (uint64_t)k * kSB; },
+        [&](int r) { return blk + (uint64_t)pair_row(A, r).dest * kSB; }, Bs);
   }
 }
 
