@@ -377,15 +377,118 @@ __global__ void kstat_kernel(CountTables tab, int M, uint64_t count, const uint6
   }
 }
 
-// ---- Pearson coefficient: two passes of FP64 block reductions ----
-__global__ void sums_kernel(const double* __restrict__ x, const double* __restrict__ y, uint64_t n,
-                            const double* __restrict__ mean, double* __restrict__ part) {
-  __shared__ double sh[3][kEstThreads];
-  const bool centered = mean != nullptr;
-  const double mx = centered ? mean[0] : 0.0, my = centered ? mean[1] : 0.0;
-  double a = 0.0, b = 0.0, c = 0.0;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (uint64_t)gridDim.x * blockDim.x) {
+// The same with the subsets {a} + B of one B (a < min B, consecutive ranks)
+// sharing what does not depend on a.  Every partition of {a} + B is a block
+// {a} + V, V a subset of B, and a partition of B \ V, so
+//   k({a} + B) = sum_V m({a} + V) G_V(B),
+//   G_V(B) = sum over the partitions tau whose block of a is {a} + V of
+//            c_N(tau) prod of the other blocks' moments:
+// 2^(D-1) loads and products per subset instead of 2^D - 1 and one product per
+// partition (52 at D = 5).  A workgroup takes kStatB consecutive B's: their G_V
+// and the ranks of V go to LDS, then half waves walk a for one
+// B each.  All sums are compensated, as in kstat_kernel.
+// D = 5, M = 144 (4.8e8 subsets): KSTAT_TIME
+constexpr int kStatB = 64;
+template <int D>
+__global__ __launch_bounds__(256) void kstat_shared_kernel(CountTables tab, int M, uint64_t nb,
+                                                           const uint64_t* __restrict__ binom, double invN,
+                                                           KstatCoef cf, double* __restrict__ out) {
+  constexpr int NV = 1 << (D - 1);
+  constexpr PartTable<D> kParts = make_parts<D>();
+  __shared__ double g[NV][kStatB];
+  __shared__ uint64_t rank[NV][kStatB];  // of {a} + V is a + this, V non-empty; [0]: of {a} + B
+  __shared__ int amax[kStatB];
+  const int qb = threadIdx.x & (kStatB - 1), part = threadIdx.x / kStatB;  // four waves share the V's of a B
+  {
+    const uint64_t rb = (uint64_t)blockIdx.x * kStatB + qb;
+    int s[D - 1];
+    s[0] = 0;
+    if (rb < nb) colex_unrank<D - 1>(rb, M, binom, kBinLd, s);
+    if (part == 0) amax[qb] = rb < nb ? s[0] : 0;
+    if (rb < nb && s[0] > 0) {
+      double m[NV];
+      m[0] = 1.0;
+#pragma unroll
+      for (int B = 1; B < NV; ++B) {
+        uint64_t lo = 0, up = 0;  // ranks of B's subset alone and with a below it
+        int j = 0;
+#pragma unroll
+        for (int i = 0; i < D - 1; ++i)
+          if (B & (1 << i)) {
+            ++j;
+            lo += binom[j * kBinLd + s[i]];
+            up += binom[(j + 1) * kBinLd + s[i]];
+          }
+        m[B] = (double)tab.cnt[popcount_c((unsigned)B)][lo] * invN;
+        if (B % 4 == part) rank[B < NV - 1 ? B : 0][qb] = up;
+      }
+#pragma unroll
+      for (int V = 0; V < NV; ++V) {
+        if (V / (NV / 4) != part) continue;
+        double k = 0.0, comp = 0.0;
+#pragma unroll
+        for (int t = 0; t < kParts.n; ++t) {
+          bool has = false;
+          double v = cf.coef[t];
+#pragma unroll
+          for (int b = 0; b < D; ++b) {
+            const uint32_t blk = kParts.blk[t][b];  // element 0 is a, element i + 1 is s[i]
+            if (blk == (uint32_t)(2 * V + 1)) has = true;
+            else if (blk) v *= m[blk >> 1];
+          }
+          if (!has) continue;
+          const double y = k + v;
+          comp += (fabs(k) >= fabs(v)) ? ((k - y) + v) : ((v - y) + k);
+          k = y;
+        }
+        g[V][qb] = k + comp;
+      }
+    }
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 31;
+  for (int q = threadIdx.x >> 5; q < kStatB; q += 8) {
+    const int na = amax[q];
+    if (na == 0) continue;
+    const uint64_t full = rank[0][q];
+    for (int a = lane; a < na; a += 32) {
+      double k = 0.0, comp = 0.0;
+#pragma unroll
+      for (int V = 0; V < NV; ++V) {
+        const uint64_t rk = V == 0 ? 0 : V == NV - 1 ? full : rank[V][q];
+        const double v = g[V][q] * ((double)tab.cnt[popcount_c((unsigned)V) + 1][rk + a] * invN);
+        const double y = k + v;
+        comp += (fabs(k) >= fabs(v)) ? ((k - y) + v) : ((v - y) + k);
+        k = y;
+      }
+      out[full + a] = k + comp;
+    }
+  }
+}
+
+// ---- Pearson coefficient: two passes of FP64 block reductions, fixed order ----
+
+// Sum of v over the workgroup: lanes by the butterfly, then the waves in order;
+// valid in every thread.
+template <int WAVES>
+__device__ __forceinline__ double block_total(double v, double (&sh)[WAVES]) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  __syncthreads();  // the previous call's sums have been read
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double t = 0.0;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) t += sh[w];
+  return t;
+}
+
+// Sums over this workgroup's elements: x and y, or with means the centred
+// products.  part[q * gridDim.x + block].
+__device__ __forceinline__ void pearson_sums(const double* __restrict__ x, const double* __restrict__ y, uint64_t n,
+                                             uint64_t first, uint64_t step, double mx, double my, bool centered,
+                                             double& a, double& b, double& c) {
+  for (uint64_t i = first; i < n; i += step) {
     if (centered) {
       const double dx = x[i] - mx, dy = y[i] - my;
       a = fma(dx, dy, a);
@@ -396,33 +499,74 @@ __global__ void sums_kernel(const double* __restrict__ x, const double* __restri
       b += y[i];
     }
   }
-  sh[0][threadIdx.x] = a;
-  sh[1][threadIdx.x] = b;
-  sh[2][threadIdx.x] = c;
-  __syncthreads();
-  for (int h = blockDim.x / 2; h >= 1; h >>= 1) {
-    if ((int)threadIdx.x < h)
-      for (int q = 0; q < 3; ++q) sh[q][threadIdx.x] += sh[q][threadIdx.x + h];
-    __syncthreads();
-  }
-  if (threadIdx.x < 3) part[blockIdx.x * 3 + threadIdx.x] = sh[threadIdx.x][0];
 }
 
-__global__ void finish_kernel(const double* __restrict__ part, int nblk, uint64_t n, int stage,
-                              double* __restrict__ mean, double* __restrict__ r) {
-  if (threadIdx.x != 0) return;
+// Few elements: everything in one workgroup.  Up to kPearsonOne elements a
+// second launch costs more than the one compute unit's bandwidth.
+constexpr int kPearsonThreads = 1024;
+constexpr uint64_t kPearsonOne = 16384;
+__global__ __launch_bounds__(kPearsonThreads) void pearson_one_kernel(const double* __restrict__ x,
+                                                                      const double* __restrict__ y, uint64_t n,
+                                                                      double* __restrict__ r) {
+  __shared__ double sh[kPearsonThreads / 64];
   double a = 0.0, b = 0.0, c = 0.0;
-  for (int i = 0; i < nblk; ++i) {  // fixed order: deterministic
-    a += part[3 * i];
-    b += part[3 * i + 1];
-    c += part[3 * i + 2];
+  pearson_sums(x, y, n, threadIdx.x, kPearsonThreads, 0.0, 0.0, false, a, b, c);
+  const double mx = block_total(a, sh) / (double)n, my = block_total(b, sh) / (double)n;
+  a = b = c = 0.0;
+  pearson_sums(x, y, n, threadIdx.x, kPearsonThreads, mx, my, true, a, b, c);
+  a = block_total(a, sh);
+  b = block_total(b, sh);
+  c = block_total(c, sh);
+  if (threadIdx.x == 0) r[0] = a / sqrt(b * c);
+}
+
+__global__ __launch_bounds__(kEstThreads) void pearson_means_kernel(const double* __restrict__ x,
+                                                                    const double* __restrict__ y, uint64_t n,
+                                                                    double* __restrict__ part) {
+  __shared__ double sh[kEstThreads / 64];
+  double a = 0.0, b = 0.0, c = 0.0;
+  pearson_sums(x, y, n, (uint64_t)blockIdx.x * kEstThreads + threadIdx.x, (uint64_t)gridDim.x * kEstThreads, 0.0, 0.0,
+               false, a, b, c);
+  a = block_total(a, sh);
+  b = block_total(b, sh);
+  if (threadIdx.x == 0) {
+    part[blockIdx.x] = a;
+    part[gridDim.x + blockIdx.x] = b;
   }
-  if (stage == 0) {
-    mean[0] = a / (double)n;
-    mean[1] = b / (double)n;
-  } else {
-    r[0] = a / sqrt(b * c);
+}
+
+// The total of m partial sums, in the same order in every workgroup.
+__device__ __forceinline__ double total_of(const double* __restrict__ part, int m, double (&sh)[kEstThreads / 64]) {
+  double t = 0.0;
+  for (int i = threadIdx.x; i < m; i += kEstThreads) t += part[i];
+  return block_total(t, sh);
+}
+
+// part: 2 x gridDim.x sums of the first pass, then 3 x gridDim.x of this one.
+__global__ __launch_bounds__(kEstThreads) void pearson_centred_kernel(const double* __restrict__ x,
+                                                                      const double* __restrict__ y, uint64_t n,
+                                                                      double* __restrict__ part) {
+  __shared__ double sh[kEstThreads / 64];
+  const int m = (int)gridDim.x;
+  const double mx = total_of(part, m, sh) / (double)n, my = total_of(part + m, m, sh) / (double)n;
+  double a = 0.0, b = 0.0, c = 0.0;
+  pearson_sums(x, y, n, (uint64_t)blockIdx.x * kEstThreads + threadIdx.x, (uint64_t)m * kEstThreads, mx, my, true, a,
+               b, c);
+  a = block_total(a, sh);
+  b = block_total(b, sh);
+  c = block_total(c, sh);
+  if (threadIdx.x == 0) {
+    part[2 * m + blockIdx.x] = a;
+    part[3 * m + blockIdx.x] = b;
+    part[4 * m + blockIdx.x] = c;
   }
+}
+
+__global__ __launch_bounds__(kEstThreads) void pearson_finish_kernel(const double* __restrict__ part, int m,
+                                                                     double* __restrict__ r) {
+  __shared__ double sh[kEstThreads / 64];
+  const double a = total_of(part + 2 * m, m, sh), b = total_of(part + 3 * m, m, sh), c = total_of(part + 4 * m, m, sh);
+  if (threadIdx.x == 0) r[0] = a / sqrt(b * c);
 }
 
 // Coefficients c_N(tau) N^|tau| of k(S) = sum_tau coef(tau) prod_{B in tau} (s_B / N).
@@ -533,10 +677,15 @@ template <int D>
 hipError_t launch_kstat(const CountTables& tab, int M, int64_t N, const uint64_t* binom, double* out, hipStream_t s) {
   KstatCoef cf{};
   kstat_coefficients(D, (double)N, &cf);
-  const uint64_t count = host_binom(M, D);
-  const unsigned grid = (unsigned)std::min<uint64_t>((count + 255) / 256, 1u << 20);
-  hipLaunchKernelGGL(kstat_kernel<D>, dim3(grid), dim3(256), 0, s, tab, M, count, binom, 1.0 / (double)N, cf,
-                     out + gbs_order_offset(M, D));
+  if constexpr (D >= 4) {
+    const uint64_t nb = host_binom(M, D - 1);
+    hipLaunchKernelGGL(kstat_shared_kernel<D>, dim3((unsigned)((nb + kStatB - 1) / kStatB)), dim3(256), 0, s, tab, M,
+                       nb, binom, 1.0 / (double)N, cf, out + gbs_order_offset(M, D));
+  } else {
+    const uint64_t count = host_binom(M, D);
+    hipLaunchKernelGGL(kstat_kernel<D>, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, tab, M, count, binom,
+                       1.0 / (double)N, cf, out + gbs_order_offset(M, D));
+  }
   return hipGetLastError();
 }
 
@@ -594,16 +743,18 @@ hipError_t run_sample_cumulants(int M, int64_t N, const uint8_t* bits, int K,
 }
 
 hipError_t run_pearson(uint64_t n, const double* x, const double* y, double* r, hipStream_t s) {
+  if (n <= kPearsonOne) {
+    hipLaunchKernelGGL(pearson_one_kernel, dim3(1), dim3(kPearsonThreads), 0, s, x, y, n, r);
+    return hipGetLastError();
+  }
   const int nblk = (int)std::min<uint64_t>((n + kEstThreads - 1) / kEstThreads, 1024);
   void* scratch = nullptr;
-  hipError_t e = hipMallocAsync(&scratch, (size_t)(3 * nblk + 2) * sizeof(double), s);
+  hipError_t e = hipMallocAsync(&scratch, (size_t)(5 * nblk) * sizeof(double), s);
   if (e != hipSuccess) return e;
   double* part = static_cast<double*>(scratch);
-  double* mean = part + 3 * nblk;
-  hipLaunchKernelGGL(sums_kernel, dim3(nblk), dim3(kEstThreads), 0, s, x, y, n, (const double*)nullptr, part);
-  hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(64), 0, s, part, nblk, n, 0, mean, r);
-  hipLaunchKernelGGL(sums_kernel, dim3(nblk), dim3(kEstThreads), 0, s, x, y, n, (const double*)mean, part);
-  hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(64), 0, s, part, nblk, n, 1, mean, r);
+  hipLaunchKernelGGL(pearson_means_kernel, dim3(nblk), dim3(kEstThreads), 0, s, x, y, n, part);
+  hipLaunchKernelGGL(pearson_centred_kernel, dim3(nblk), dim3(kEstThreads), 0, s, x, y, n, part);
+  hipLaunchKernelGGL(pearson_finish_kernel, dim3(1), dim3(kEstThreads), 0, s, part, nblk, r);
   e = hipGetLastError();
   hipError_t f = hipFreeAsync(scratch, s);
   return e != hipSuccess ? e : f;
