@@ -147,11 +147,12 @@ __host__ __device__ inline void row_modes(uint32_t h, int M, int (&m)[DH]) {
 // Sums are exact: FP32 accumulators hold at most kSplitSamples ones.  Ranges of
 // chunks of one tile (few tiles, or more samples than that) add up by integer
 // atomics, whose order does not matter.
-// Order 5 at M = 144, 262,144 samples: 48.4 ms, 5.2e15 operations/s on the
+// Order 5 at M = 144, 262,144 samples: 44.0 ms, 5.7e15 operations/s on the
 // 4.8e8 x 262,144 products wanted, against 286 ms of AND and popcount in 32-bit
-// vector instructions (0.81 of their peak). What is left: tiles that reach past
-// a row's columns (about 1.1 times the work), and per chunk the masking (20
-// vector instructions for 4 x 6 operands) and staging beside the products.
+// vector instructions (0.81 of their peak); 48.6 ms with the loads of the next
+// chunk waited for where they are issued. What is left: tiles that reach past a
+// row's columns (about 1.1 times the work), and per chunk the masking (20 vector
+// instructions for 4 x 6 operands) beside the products.
 constexpr int kTH = 256, kTL = 128;
 constexpr int kRowBytes = kChunkBytes + 16;
 constexpr int64_t kSplitSamples = 1 << 22;
@@ -228,32 +229,53 @@ __global__ __launch_bounds__(kEstThreads) __attribute__((amdgpu_waves_per_eu(2, 
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int wh = (w & 1) * 128, wl = (w >> 1) * 64;  // the wave's part of the tile
   const uint64_t stride = (uint64_t)M * kChunkBytes;
-  auto stage = [&](int64_t c, uint8_t* dst, int half) {
+  // One of the thread's six pieces at a time: loaded ahead of the products that
+  // run meanwhile, ANDed and written after them.
+  uint4v rh[DH], rl[DL];
+  auto fetch_h = [&](int64_t c, int i) {
     const uint8_t* src = cols + (uint64_t)c * stride;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      uint4v v = *reinterpret_cast<const uint4v*>(src + ho[2 * half + i][0]);
+    for (int j = 0; j < DH; ++j) rh[j] = *reinterpret_cast<const uint4v*>(src + ho[i][j]);
+  };
+  auto fetch_l = [&](int64_t c, int i) {
+    const uint8_t* src = cols + (uint64_t)c * stride;
 #pragma unroll
-      for (int j = 1; j < DH; ++j) v &= *reinterpret_cast<const uint4v*>(src + ho[2 * half + i][j]);
-      *reinterpret_cast<uint4v*>(dst + (rt + 64 * (2 * half + i)) * kRowBytes + piece) = v;
-    }
-    uint4v v = *reinterpret_cast<const uint4v*>(src + lo[half][0]);
+    for (int j = 0; j < DL; ++j) rl[j] = *reinterpret_cast<const uint4v*>(src + lo[i][j]);
+  };
+  auto commit_h = [&](uint8_t* dst, int i) {
+    uint4v v = rh[0];
 #pragma unroll
-    for (int j = 1; j < DL; ++j) v &= *reinterpret_cast<const uint4v*>(src + lo[half][j]);
-    *reinterpret_cast<uint4v*>(dst + (kTH + rt + 64 * half) * kRowBytes + piece) = v;
+    for (int j = 1; j < DH; ++j) v &= rh[j];
+    *reinterpret_cast<uint4v*>(dst + (rt + 64 * i) * kRowBytes + piece) = v;
+  };
+  auto commit_l = [&](uint8_t* dst, int i) {
+    uint4v v = rl[0];
+#pragma unroll
+    for (int j = 1; j < DL; ++j) v &= rl[j];
+    *reinterpret_cast<uint4v*>(dst + (kTH + rt + 64 * i) * kRowBytes + piece) = v;
   };
   float16v acc[4][2] = {};
   if (c0 < c1) {
-    stage(c0, buf[0], 0);
-    stage(c0, buf[0], 1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      fetch_h(c0, i);
+      commit_h(buf[0], i);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      fetch_l(c0, i);
+      commit_l(buf[0], i);
+    }
   }
   __syncthreads();
   for (int64_t c = c0; c < c1; ++c) {
     const uint8_t* cur = buf[(c - c0) & 1];
     uint8_t* nxt = buf[(c - c0 + 1) & 1];
-    const bool more = c + 1 < c1;
+    const int64_t cn = min(c + 1, c1 - 1);  // the last chunk stages itself again, unread
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
+      fetch_h(cn, 2 * kk);
+      fetch_l(cn, kk);
       const int off = (lane & 31) * kRowBytes + kk * 32 + (lane >> 5) * 16;
       uint4v h[4], l[2];
 #pragma unroll
@@ -262,11 +284,14 @@ __global__ __launch_bounds__(kEstThreads) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
       for (int j = 0; j < 2; ++j)
         l[j] = *reinterpret_cast<const uint4v*>(cur + (kTH + wl + 32 * j) * kRowBytes + off);
-      if (more) stage(c + 1, nxt, kk);
       count_step<0>(h, l, acc);
       count_step<1>(h, l, acc);
+      commit_h(nxt, 2 * kk);
+      commit_l(nxt, kk);
+      fetch_h(cn, 2 * kk + 1);
       count_step<2>(h, l, acc);
       count_step<3>(h, l, acc);
+      commit_h(nxt, 2 * kk + 1);
     }
     __syncthreads();
   }
