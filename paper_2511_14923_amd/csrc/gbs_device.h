@@ -310,4 +310,9 @@ __device__ __forceinline__ void store_at(double* __restrict__ base, uint64_t idx
   base[idx] = v;
 }
 
+// The same past the caches: results that no later launch of the call reads.
+__device__ __forceinline__ void stream_at(double* __restrict__ base, uint32_t idx, double v) {
+  __builtin_nontemporal_store(v, reinterpret_cast<double*>(reinterpret_cast<char*>(base) + (idx << 3)));
+}
+
 }  // namespace gbs
