@@ -268,11 +268,8 @@ gbs_status run_forward(int32_t M, const double* sigma, const double* mu, int32_t
   t_err.order = 0;
   t_err.rank = -1;
   timing_start_call((flags & GBS_TIMING) != 0);
-  e = launch_clear_status(sc.st, s);
-  if (e == hipSuccess) e = timing_begin(s, GBS_STAGE_BUILD_Q, 0);
-  if (e == hipSuccess) e = launch_build_q(sigma, M, sc.Qi, s);
-  if (e == hipSuccess) e = launch_build_qdiag(sc.Qi, M, sc.Qd, s);
-  if (e == hipSuccess && mu) e = launch_build_mean(mu, M, sc.mi, s);
+  e = timing_begin(s, GBS_STAGE_BUILD_Q, 0);
+  if (e == hipSuccess) e = launch_prepare(sigma, mu, M, sc.Qi, sc.Qd, sc.mi, sc.st, s);
   if (e == hipSuccess) e = timing_end(s);
   if (e == hipSuccess && mixed) {
     e = timing_begin(s, GBS_STAGE_NORMALISE, 0);
@@ -282,6 +279,9 @@ gbs_status run_forward(int32_t M, const double* sigma, const double* mu, int32_t
   const double* p_tab[kMaxOrder + 1] = {};
   const double* m_tab[kMaxOrder + 1] = {};
   const double* k_tab[kMaxOrder + 1] = {};
+  // orders 1 and 2 in one launch (timed as order 2) where the pairs kernel applies
+  const bool pairs = rec && K >= 2 && !mixed && !mu;
+  double *m12[2] = {}, *k12[2] = {}, *p12[2] = {};
   for (int d = 1; d <= K && e == hipSuccess; ++d) {
     const int64_t off = gbs_order_offset(M, d);
     e = timing_begin(s, GBS_STAGE_FORWARD, d);
@@ -290,7 +290,13 @@ gbs_status run_forward(int32_t M, const double* sigma, const double* mu, int32_t
       double* m_out = (corr || d < K) ? mtab + off : nullptr;
       double* k_out = cum ? cum + off : nullptr;
       double* p_out = d < K ? ptab + off : nullptr;
-      e = launch_forward_rec(d, M, flags, sc.Qi, sc.Qd, sc.mi, sc.pk, sc.E, ctx->binom, p_tab, m_tab,
+      if (pairs && d <= 2) {
+        m12[d - 1] = m_out;
+        k12[d - 1] = k_out;
+        p12[d - 1] = p_out;
+        if (d == 2) e = launch_forward_pairs(M, flags, sc.Qi, sc.Qd, m12, k12, p12, sc.st, s);
+      } else
+        e = launch_forward_rec(d, M, flags, sc.Qi, sc.Qd, sc.mi, sc.pk, sc.E, ctx->binom, p_tab, m_tab,
                              k_tab, m_out, k_out, p_out, sc.st, s);
       p_tab[d] = ptab + off;
       m_tab[d] = mtab + off;
@@ -324,9 +330,8 @@ gbs_status run_shard(int32_t M, const double* sigma, int32_t d, int64_t rank0, i
   t_err.order = 0;
   t_err.rank = -1;
   timing_start_call((flags & GBS_TIMING) != 0);
-  e = launch_clear_status(st, s);
-  if (e == hipSuccess) e = timing_begin(s, GBS_STAGE_BUILD_Q, 0);
-  if (e == hipSuccess) e = launch_build_q(sigma, M, Qi, s);
+  e = timing_begin(s, GBS_STAGE_BUILD_Q, 0);
+  if (e == hipSuccess) e = launch_prepare(sigma, nullptr, M, Qi, nullptr, nullptr, st, s);
   if (e == hipSuccess) e = timing_end(s);
   if (e == hipSuccess) e = timing_begin(s, GBS_STAGE_FORWARD, d);
   // orders >= 3: the T-shared kernel; orders 1, 2 and GBS_ALL_MINORS: the all-minors kernel
@@ -378,10 +383,8 @@ gbs_status run_adjoint(int32_t M, const double* sigma, int32_t K, int32_t flags,
   t_err.order = 0;
   t_err.rank = -1;
   timing_start_call((flags & GBS_TIMING) != 0);
-  e = launch_clear_status(st, s);
-  if (e == hipSuccess) e = timing_begin(s, GBS_STAGE_BUILD_Q, 0);
-  if (e == hipSuccess) e = launch_build_q(sigma, M, Qi, s);
-  if (e == hipSuccess) e = launch_build_qdiag(Qi, M, Qd, s);
+  e = timing_begin(s, GBS_STAGE_BUILD_Q, 0);
+  if (e == hipSuccess) e = launch_prepare(sigma, nullptr, M, Qi, Qd, nullptr, st, s);
   if (e == hipSuccess) e = timing_end(s);
   const double* p_tab[kMaxOrder + 1] = {};
   const double* m_tab[kMaxOrder + 1] = {};
@@ -389,7 +392,12 @@ gbs_status run_adjoint(int32_t M, const double* sigma, int32_t K, int32_t flags,
   for (int d = 1; d <= K && e == hipSuccess; ++d) {
     const int64_t o = gbs_order_offset(M, d);
     e = timing_begin(s, GBS_STAGE_FORWARD, d);
-    if (e == hipSuccess)
+    if (e == hipSuccess && K >= 2 && d <= 2) {  // one launch for both, timed as order 2
+      double* const mo[2] = {m, m + M};
+      double* const ko[2] = {};
+      double* const po[2] = {ptab, ptab + M};
+      if (d == 2) e = launch_forward_pairs(M, flags & GBS_PARITY, Qi, Qd, mo, ko, po, st, s);
+    } else if (e == hipSuccess)
       e = launch_forward_rec(d, M, flags & GBS_PARITY, Qi, Qd, nullptr, nullptr, nullptr, ctx->binom,
                              p_tab, m_tab, k_tab, m + o, nullptr, ptab + o, st, s);
     p_tab[d] = ptab + o;

@@ -73,66 +73,44 @@ __global__ __launch_bounds__(256) void forward_fp64_kernel(const double* __restr
 
 // ----------------------------------------------------------------------------
 
-__global__ void build_q_kernel(const double* __restrict__ sigma, int M, double* __restrict__ Qi) {
+// The operands of a call from sigma's lower triangle, in one launch (a small
+// problem is bound by its launches: M = 16, K = 3 took four here): Q, and where
+// asked for its diagonal blocks (x-x, p-x, p-p, 0 per mode, for coalesced access by
+// mode), the interleaved first moments and a cleared status word.
+__global__ void prepare_kernel(const double* __restrict__ sigma, const double* __restrict__ mu, int M,
+                               double* __restrict__ Qi, double* __restrict__ Qd, double* __restrict__ mi,
+                               DeviceStatus* __restrict__ st) {
   const int n = 2 * M;
   const size_t total = (size_t)n * n;
-  for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-       idx += (size_t)gridDim.x * blockDim.x) {
+  const size_t first = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (st && first == 0) {
+    st->flag = 0;
+    st->order = 0;
+    st->rank = -1;
+  }
+  for (size_t idx = first; idx < total; idx += (size_t)gridDim.x * blockDim.x) {
     const int row = (int)(idx / n), col = (int)(idx - (size_t)row * n);
     // interleaved index 2k + a  <->  xxpp index k + a M
     const int sr = (row >> 1) + (row & 1) * M;
     const int sc = (col >> 1) + (col & 1) * M;
-    const double v = (sr >= sc) ? sigma[(size_t)sr * n + sc] : sigma[(size_t)sc * n + sr];
-    Qi[idx] = v + (row == col ? 0.5 : 0.0);
+    double v = (sr >= sc) ? sigma[(size_t)sr * n + sc] : sigma[(size_t)sc * n + sr];
+    v += row == col ? 0.5 : 0.0;
+    Qi[idx] = v;
+    if ((row >> 1) == (col >> 1)) {
+      // entries (0, 0), (1, 0), (1, 1) of the block at 0, 1, 2; (0, 1) leaves the 0 at 3
+      const int at = (row & 1) + (col & 1);
+      if (Qd) Qd[2 * (size_t)(row & ~1) + (row >= col ? at : 3)] = row >= col ? v : 0.0;
+      if (mi && row == col) mi[row] = mu[(row >> 1) + (size_t)(row & 1) * M];
+    }
   }
 }
 
-// Per-mode diagonal blocks of Q (x-x, p-x, p-p, 0) for coalesced access by mode.
-__global__ void build_qdiag_kernel(const double* __restrict__ Qi, int M, double* __restrict__ Qd) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= M) return;
-  const size_t ldq = 2 * (size_t)M;
-  const double* q = Qi + (size_t)(2 * k) * ldq + 2 * k;
-  Qd[4 * (size_t)k + 0] = q[0];
-  Qd[4 * (size_t)k + 1] = q[ldq];
-  Qd[4 * (size_t)k + 2] = q[ldq + 1];
-  Qd[4 * (size_t)k + 3] = 0.0;
-}
-
-hipError_t launch_build_qdiag(const double* Qi, int M, double* Qd, hipStream_t s) {
-  hipLaunchKernelGGL(build_qdiag_kernel, dim3((M + 255) / 256), dim3(256), 0, s, Qi, M, Qd);
-  return hipGetLastError();
-}
-
-__global__ void clear_status_kernel(DeviceStatus* st) {
-  st->flag = 0;
-  st->order = 0;
-  st->rank = -1;
-}
-
-hipError_t launch_build_q(const double* sigma, int M, double* Qi, hipStream_t s) {
+hipError_t launch_prepare(const double* sigma, const double* mu, int M, double* Qi, double* Qd, double* mi,
+                          DeviceStatus* st, hipStream_t s) {
   const size_t total = 4 * (size_t)M * M;
   const int block = 256;
   const int grid = (int)((total + block - 1) / block < 4096 ? (total + block - 1) / block : 4096);
-  hipLaunchKernelGGL(build_q_kernel, dim3(grid), dim3(block), 0, s, sigma, M, Qi);
-  return hipGetLastError();
-}
-
-// First moments in interleaved order: mi[2k] = mu[k] (x_k), mi[2k+1] = mu[k+M] (p_k).
-__global__ void build_mean_kernel(const double* __restrict__ mu, int M, double* __restrict__ mi) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= M) return;
-  mi[2 * (size_t)k] = mu[k];
-  mi[2 * (size_t)k + 1] = mu[(size_t)k + M];
-}
-
-hipError_t launch_build_mean(const double* mu, int M, double* mi, hipStream_t s) {
-  hipLaunchKernelGGL(build_mean_kernel, dim3((M + 255) / 256), dim3(256), 0, s, mu, M, mi);
-  return hipGetLastError();
-}
-
-hipError_t launch_clear_status(DeviceStatus* st, hipStream_t s) {
-  hipLaunchKernelGGL(clear_status_kernel, dim3(1), dim3(1), 0, s, st);
+  hipLaunchKernelGGL(prepare_kernel, dim3(grid), dim3(block), 0, s, sigma, mu, M, Qi, Qd, mi, st);
   return hipGetLastError();
 }
 

@@ -27,15 +27,13 @@ struct DeviceContext {
 // Context of the current device (created on first use); nullptr on failure.
 DeviceContext* current_context(hipError_t* err);
 
-// Q = sigma + I/2 in interleaved (x_0 p_0 x_1 p_1 ...) order, full symmetric
-// 2M x 2M FP64, built from sigma's lower triangle.
-hipError_t launch_build_q(const double* sigma, int M, double* Qi, hipStream_t s);
-
-// First moments in interleaved order (mi[2k] = mu[k], mi[2k+1] = mu[k+M]).
-hipError_t launch_build_mean(const double* mu, int M, double* mi, hipStream_t s);
-
-// Per-mode diagonal blocks of Q, 4 doubles per mode (x-x, p-x, p-p, 0).
-hipError_t launch_build_qdiag(const double* Qi, int M, double* Qd, hipStream_t s);
+// The operands of a call in one launch: Q = sigma + I/2 in interleaved (x_0 p_0 x_1
+// p_1 ...) order, full symmetric 2M x 2M FP64, built from sigma's lower triangle;
+// per-mode diagonal blocks Qd, 4 doubles per mode (x-x, p-x, p-p, 0), or null;
+// first moments in interleaved order (mi[2k] = mu[k], mi[2k+1] = mu[k+M]), or null;
+// st cleared (by a kernel: safe inside graph capture), or null.
+hipError_t launch_prepare(const double* sigma, const double* mu, int M, double* Qi, double* Qd, double* mi,
+                          DeviceStatus* st, hipStream_t s);
 
 // Mixed-precision operands: per-mode block Cholesky factors of Q, the
 // single-mode vacuum probabilities pk (FP64) and the normalised off-diagonal
@@ -57,9 +55,6 @@ gbs_status finish_status(DeviceStatus* dev_status, int32_t flags, hipStream_t s)
 gbs_status finish_status_device(const DeviceStatus* dev_status, int32_t flags, hipStream_t s);
 // Argument check shared by the forward entry points (M, max_order, flag bits).
 bool valid_problem(int32_t M, int32_t K, int32_t flags);
-
-// Reset a status word (fill kernel, safe inside graph capture).
-hipError_t launch_clear_status(DeviceStatus* st, hipStream_t s);
 
 // Order-d forward pass over all C(M, d) subsets.
 // FP64 reads Qi (and the interleaved first moments mi of a displaced state,
@@ -169,6 +164,12 @@ hipError_t launch_forward_rec(int d, int M, int flags, const double* Qi, const d
                               const double* const* m_tab, const double* const* k_tab,
                               double* m_out, double* k_out, double* p_out, DeviceStatus* st,
                               hipStream_t s, const GroupPlanRef* plans = nullptr);
+
+// Orders 1 and 2 of a zero-mean state in FP64, one launch (M >= 2): the order-1
+// and order-2 blocks of the correlators, cumulants and probabilities (each
+// pointer may be null).
+hipError_t launch_forward_pairs(int M, int flags, const double* Qi, const double* Qd, double* const* m_out,
+                                double* const* k_out, double* const* p_out, DeviceStatus* st, hipStream_t s);
 
 // Vector-Jacobian product given the forward correlators m and vacuum
 // probabilities ptab of every subset (orders 1..K); d1, mbar, pbar are scratch

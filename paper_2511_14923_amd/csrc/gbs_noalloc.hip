@@ -164,19 +164,26 @@ extern "C" GBS_API gbs_status gbs_cumulants_noalloc(int32_t M, const double* sig
 
   double* ptab = rec ? reinterpret_cast<double*>(b + L.ptab) : nullptr;
   double* mtab = rec ? (corr ? corr : reinterpret_cast<double*>(b + L.mtab)) : nullptr;
-  e = launch_clear_status(st, s);
-  if (e == hipSuccess) e = launch_build_q(sigma, M, Qi, s);
-  if (e == hipSuccess) e = launch_build_qdiag(Qi, M, Qd, s);
+  e = launch_prepare(sigma, nullptr, M, Qi, Qd, nullptr, st, s);
   if (e == hipSuccess && (flags & GBS_MIXED)) e = launch_build_normalised(Qi, M, pk, E, s);
   const double* p_tab[kMaxOrder + 1] = {};
   const double* m_tab[kMaxOrder + 1] = {};
   const double* k_tab[kMaxOrder + 1] = {};
+  // the launches of gbs_cumulants: orders 1 and 2 together in FP64
+  const bool pairs = rec && max_order >= 2 && !(flags & GBS_MIXED);
+  double *m12[2] = {}, *k12[2] = {}, *p12[2] = {};
   for (int d = 1; d <= max_order && e == hipSuccess; ++d) {
     const int64_t off = gbs_order_offset(M, d);
     if (rec) {
       double* m_out = (corr || d < max_order) ? mtab + off : nullptr;
       double* p_out = d < max_order ? ptab + off : nullptr;
-      e = launch_forward_rec(d, M, flags, Qi, Qd, nullptr, pk, E, binom, p_tab, m_tab, k_tab,
+      if (pairs && d <= 2) {
+        m12[d - 1] = m_out;
+        k12[d - 1] = cum + off;
+        p12[d - 1] = p_out;
+        if (d == 2) e = launch_forward_pairs(M, flags, Qi, Qd, m12, k12, p12, st, s);
+      } else
+        e = launch_forward_rec(d, M, flags, Qi, Qd, nullptr, pk, E, binom, p_tab, m_tab, k_tab,
                              m_out, cum + off, p_out, st, s, plans);
       p_tab[d] = ptab + off;
       m_tab[d] = mtab + off;
