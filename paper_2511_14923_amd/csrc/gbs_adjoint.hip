@@ -14,9 +14,13 @@
 //   d p(T) / d Q_T = -p(T) Q_T^{-1} / 2   (d log det A = tr(A^{-1} dA)),
 //   so the 2x2 block (i, j) of dL/dsigma is
 //      G_ij = sum_{T containing i and j} -pbar(T) p(T) [Q_T^{-1}]_{ij} / 2.
-// Every sum is a gather owned by one wavefront (the superset sums by their
-// target subset, G_ij by its mode pair) reduced in a fixed order: no atomics,
-// results are bitwise reproducible.
+// pbar is a sum over all supersets: with S_n(T) the sum of mbar over the supersets
+// of T of size n, S_n(T) = sum_{x not in T} S_n(T + x) / (n - |T|), so each order
+// reads M - |T| values of the order above.  G_ij needs [Q_T^{-1}]_ij for every T
+// that holds i and j; the same factorisation gives the diagonal blocks ii and jj,
+// which T's |T| - 1 pairs with i share, so one pass over the pairs serves all
+// blocks.  Every sum is a gather owned by one workgroup or wavefront and reduced
+// in a fixed order: no atomics, results are bitwise reproducible.
 #include <hip/hip_runtime.h>
 
 #include "gbs_internal.h"
@@ -94,41 +98,72 @@ __device__ __forceinline__ void unrank_dyn(const uint64_t* __restrict__ bin, uin
   }
 }
 
-// Modes of a j-subset of the complement of B (sorted, size k): complement
-// index -> mode, skipping B's elements in increasing order.
-__device__ __forceinline__ void complement_modes(const int* xc, int j, const int* B, int k, int* x) {
-  for (int t = 0; t < j; ++t) {
-    int m = xc[t];
-    for (int i = 0; i < k; ++i)
-      if (B[i] <= m) ++m;
+// C(x, k) for the colex rank (k = 1..5): closed forms where they are cheap
+__device__ __forceinline__ uint64_t choose_k(const uint64_t* __restrict__ bin, int x, int k) {
+  if (k == 1) return (uint64_t)x;
+  if (k == 2) return (uint64_t)((uint32_t)x * (uint32_t)(x - 1) / 2);
+  return binom_at(bin, x, k);
+}
+
+// j-subset of [0, universe) with colex rank r, ascending.
+template <int J>
+__device__ __forceinline__ void unrank_small(const uint64_t* __restrict__ bin, uint64_t r, int universe,
+                                             int (&x)[J]) {
+  if constexpr (J == 1) {
+    x[0] = (int)r;
+  } else if constexpr (J == 2) {
+    const uint32_t q = (uint32_t)r;  // C(2048, 2) < 2^22
+    int b = (int)(0.5f * (1.0f + sqrtf(fmaf(8.0f, (float)q, 1.0f))));
+    while ((uint32_t)b * (uint32_t)(b - 1) / 2 > q) --b;
+    while ((uint32_t)b * (uint32_t)(b + 1) / 2 <= q) ++b;
+    x[1] = b;
+    x[0] = (int)(q - (uint32_t)b * (uint32_t)(b - 1) / 2);
+  } else {
+    unrank_dyn(bin, r, J, universe, x);
+  }
+}
+
+// Modes of a J-subset of the complement of B (sorted): complement index ->
+// mode, skipping B's elements in increasing order.
+template <int J, int KB>
+__device__ __forceinline__ void complement_modes(const int (&B)[KB], int (&x)[J]) {
+#pragma unroll
+  for (int t = 0; t < J; ++t) {
+    int m = x[t];
+#pragma unroll
+    for (int i = 0; i < KB; ++i) m += B[i] <= m ? 1 : 0;
     x[t] = m;
   }
 }
 
-// Sorted union of two sorted disjoint sets.
-__device__ __forceinline__ int merge_sorted(const int* a, int na, const int* b, int nb, int* out) {
-  int i = 0, j = 0, n = 0;
-  while (i < na || j < nb) {
-    if (j >= nb || (i < na && a[i] < b[j])) out[n++] = a[i++];
-    else out[n++] = b[j++];
+// Colex rank of the union of two disjoint sorted sets.
+template <int KB, int J>
+__device__ __forceinline__ uint64_t union_rank(const uint64_t* __restrict__ bin, const int (&B)[KB],
+                                               const int (&X)[J]) {
+  uint64_t r = 0;
+#pragma unroll
+  for (int i = 0; i < KB; ++i) {
+    int pos = i + 1;
+#pragma unroll
+    for (int j = 0; j < J; ++j) pos += X[j] < B[i] ? 1 : 0;
+    r += choose_k(bin, B[i], pos);
   }
-  return n;
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    int pos = j + 1;
+#pragma unroll
+    for (int i = 0; i < KB; ++i) pos += B[i] < X[j] ? 1 : 0;
+    r += choose_k(bin, X[j], pos);
+  }
+  return r;
 }
 
-// Flat index over all X of sizes jmin..jmax within a universe of u modes.
-__device__ __forceinline__ void flat_to_sized(const uint64_t* __restrict__ bin, uint64_t i, int jmin,
-                                              int jmax, int u, int* j, uint64_t* r) {
-  for (int t = jmin; t <= jmax; ++t) {
-    const uint64_t c = binom_at(bin, u, t);
-    if (i < c) {
-      *j = t;
-      *r = i;
-      return;
-    }
-    i -= c;
-  }
-  *j = -1;
-  *r = 0;
+template <int J>
+__device__ __forceinline__ uint64_t set_rank(const uint64_t* __restrict__ bin, const int (&X)[J]) {
+  uint64_t r = 0;
+#pragma unroll
+  for (int j = 0; j < J; ++j) r += choose_k(bin, X[j], j + 1);
+  return r;
 }
 
 __device__ __forceinline__ uint64_t count_sized(const uint64_t* __restrict__ bin, int jmin, int jmax,
@@ -212,32 +247,51 @@ __global__ void d1_kernel(const double* __restrict__ m, int M, int K, Offsets o,
   }
 }
 
-// mbar(B) for every B of order k (one workgroup per B, its threads striding
-// over the supersets).
-__global__ __launch_bounds__(kSumThreads) void mbar_kernel(int M, int K, int k, Offsets o,
-                                                     const uint64_t* __restrict__ bin,
-                                                     const double* __restrict__ gm,
-                                                     const double* __restrict__ gk,
-                                                     const double* __restrict__ d1,
-                                                     double* __restrict__ mbar,
-                                                     double* __restrict__ part) {
-  const uint64_t rb = blockIdx.x;
-  int B[kMaxOrder];
-  unrank_dyn(bin, rb, k, M, B);
+// The terms of mbar(B) with |X| = J, whose flat indices start at `first`.
+template <int KB, int J>
+__device__ __forceinline__ double mbar_terms(int M, const int (&B)[KB], uint64_t first, uint64_t lo, uint64_t hi,
+                                             const Offsets& o, const uint64_t* __restrict__ bin,
+                                             const double* __restrict__ gk, const double* __restrict__ d1) {
+  const uint64_t n = binom_at(bin, M - KB, J);
+  const uint64_t b = lo > first ? lo - first : 0, e = hi > first ? min(hi - first, n) : 0;
+  const double* g = gk + o.off[KB + J];
+  const double* d = d1 + o.off[J];
   double acc = 0.0;
-  if (gk && k < K) {
-    const int u = M - k;
-    uint64_t lo, hi;
-    chunk_range(count_sized(bin, 1, K - k, u), &lo, &hi);
-    for (uint64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
-      int j;
-      uint64_t rx;
-      flat_to_sized(bin, i, 1, K - k, u, &j, &rx);
-      int xc[kMaxOrder], X[kMaxOrder], U[kMaxOrder];
-      unrank_dyn(bin, rx, j, u, xc);
-      complement_modes(xc, j, B, k, X);
-      const int n = merge_sorted(B, k, X, j, U);
-      acc = fma(gk[o.off[n] + rank_sorted(bin, U, n)], d1[o.off[j] + rank_sorted(bin, X, j)], acc);
+  for (uint64_t q = b + threadIdx.x; q < e; q += blockDim.x) {
+    int X[J];
+    unrank_small<J>(bin, q, M - KB, X);
+    complement_modes<J, KB>(B, X);
+    acc = fma(g[union_rank<KB, J>(bin, B, X)], d[set_rank<J>(bin, X)], acc);
+  }
+  return acc;
+}
+
+// mbar(B) for every B of order KB (one workgroup per B and chunk of its supersets).
+template <int KB>
+__global__ __launch_bounds__(kSumThreads) void mbar_kernel(int M, int K, Offsets o, const uint64_t* __restrict__ bin,
+                                                           const double* __restrict__ gm,
+                                                           const double* __restrict__ gk,
+                                                           const double* __restrict__ d1, double* __restrict__ mbar,
+                                                           double* __restrict__ part) {
+  const uint64_t rb = blockIdx.x;
+  int B[KB];
+  unrank_small<KB>(bin, rb, M, B);
+  double acc = 0.0;
+  if (gk) {
+    uint64_t lo, hi, first = 0;
+    chunk_range(count_sized(bin, 1, K - KB, M - KB), &lo, &hi);
+    acc = mbar_terms<KB, 1>(M, B, first, lo, hi, o, bin, gk, d1);
+    first += binom_at(bin, M - KB, 1);
+    if constexpr (KB <= 3) {
+      if (K - KB >= 2) acc += mbar_terms<KB, 2>(M, B, first, lo, hi, o, bin, gk, d1);
+      first += binom_at(bin, M - KB, 2);
+    }
+    if constexpr (KB <= 2) {
+      if (K - KB >= 3) acc += mbar_terms<KB, 3>(M, B, first, lo, hi, o, bin, gk, d1);
+      first += binom_at(bin, M - KB, 3);
+    }
+    if constexpr (KB == 1) {
+      if (K - KB >= 4) acc += mbar_terms<KB, 4>(M, B, first, lo, hi, o, bin, gk, d1);
     }
   }
   acc = block_sum(acc);
@@ -246,7 +300,7 @@ __global__ __launch_bounds__(kSumThreads) void mbar_kernel(int M, int K, int k, 
       part[rb * gridDim.y + blockIdx.y] = acc;
       return;
     }
-    const int64_t at = o.off[k] + (int64_t)rb;
+    const int64_t at = o.off[KB] + (int64_t)rb;
     double v = acc;
     if (gk) v += gk[at];
     if (gm) v += gm[at];
@@ -285,168 +339,152 @@ __global__ void top_order_kernel(int64_t off, uint64_t count, int K, int parity,
   pbar[at] = coef * v;
 }
 
-// pbar(T) for every T of order t (one workgroup per T, its threads striding
-// over the supersets).
-__global__ __launch_bounds__(kSumThreads) void pbar_kernel(int M, int K, int t, int parity, Offsets o,
-                                                     const uint64_t* __restrict__ bin,
-                                                     const double* __restrict__ mbar,
-                                                     double* __restrict__ pbar,
-                                                     double* __restrict__ part) {
-  const uint64_t rt = blockIdx.x;
-  int T[kMaxOrder];
-  unrank_dyn(bin, rt, t, M, T);
-  const int u = M - t;
-  uint64_t lo, hi;
-  chunk_range(count_sized(bin, 0, K - t, u), &lo, &hi);
-  double acc = 0.0;
-  for (uint64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
-    int j;
-    uint64_t rx;
-    flat_to_sized(bin, i, 0, K - t, u, &j, &rx);
-    int xc[kMaxOrder], X[kMaxOrder], U[kMaxOrder];
-    unrank_dyn(bin, rx, j, u, xc);
-    complement_modes(xc, j, T, t, X);
-    const int n = merge_sorted(T, t, X, j, U);
-    const double v = mbar[o.off[n] + rank_sorted(bin, U, n)];
-    acc += (parity && (n & 1)) ? -v : v;
+// Superset sums of order t, one wavefront per T: S_n(T) for n = t + 1..K, from
+// mbar and the sums of order t + 1 (sup: for each order its K - t sums one array
+// after the other, see sup_at), and with them pbar(T).
+__host__ __device__ inline int64_t sup_at(const Offsets& o, int K, int t, int n) {
+  // orders K - 1, K - 2, .. first; order t holds n = t + 1..K
+  int64_t at = 0;
+  for (int u = K - 1; u > t; --u) at += (int64_t)(K - u) * (o.off[u + 1] - o.off[u]);
+  return at + (int64_t)(n - t - 1) * (o.off[t + 1] - o.off[t]);
+}
+
+template <int T>
+__global__ __launch_bounds__(256) void pbar_kernel(int M, int K, int parity, Offsets o,
+                                                   const uint64_t* __restrict__ bin, const double* __restrict__ mbar,
+                                                   double* __restrict__ sup, double* __restrict__ pbar) {
+  const int64_t rt = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (rt >= o.off[T + 1] - o.off[T]) return;
+  const int lane = threadIdx.x & 63;
+  int S[T];
+  unrank_small<T>(bin, (uint64_t)rt, M, S);
+  double acc[kMaxOrder - T] = {};
+  for (int q = lane; q < M - T; q += 64) {
+    int X[1] = {q};
+    complement_modes<1, T>(S, X);
+    const int64_t r = (int64_t)union_rank<T, 1>(bin, S, X);
+    acc[0] += mbar[o.off[T + 1] + r];
+#pragma unroll
+    for (int d = 1; d < kMaxOrder - T; ++d)
+      if (T + 1 + d <= K) acc[d] += sup[sup_at(o, K, T + 1, T + 1 + d) + r];
   }
-  acc = block_sum(acc);
-  if (threadIdx.x == 0) {
-    if (gridDim.y > 1) {
-      part[rt * gridDim.y + blockIdx.y] = acc;
-      return;
-    }
+  const double own = mbar[o.off[T] + rt];
+  double total = (parity && (T & 1)) ? -own : own;
+#pragma unroll
+  for (int d = 0; d < kMaxOrder - T; ++d) {
+    const int n = T + 1 + d;
+    if (n > K) break;
+    const double v = wave_sum(acc[d]) / (double)(d + 1);
+    if (lane == 0) sup[sup_at(o, K, T, n) + rt] = v;
+    total += (parity && (n & 1)) ? -v : v;
+  }
+  if (lane == 0) {
     // click: (-1)^t;  parity: (-2)^t (the (-1)^|B| factor is inside the sum)
-    double coef = (t & 1) ? -1.0 : 1.0;
-    if (parity) coef *= (double)(1 << t);
-    pbar[o.off[t] + (int64_t)rt] = coef * acc;
+    double coef = (T & 1) ? -1.0 : 1.0;
+    if (parity) coef *= (double)(1 << T);
+    pbar[o.off[T] + rt] = coef * total;
   }
 }
 
-// The split pbar sums of order t: partials in chunk order, then as pbar_kernel.
-__global__ void pbar_finish_kernel(int t, int parity, int nsplit, uint64_t count, Offsets o,
-                                   const double* __restrict__ part, double* __restrict__ pbar) {
-  const uint64_t rt = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (rt >= count) return;
-  double v = 0.0;
-  for (int y = 0; y < nsplit; ++y) v += part[rt * nsplit + y];
-  double coef = (t & 1) ? -1.0 : 1.0;
-  if (parity) coef *= (double)(1 << t);
-  pbar[o.off[t] + (int64_t)rt] = coef * v;
-}
-
-// Trailing (base) block of Q_T^{-1}: the first NX blocks of `modes` are
-// eliminated, the last NB (1 or 2) are the base modes.
-template <int NX, int NB>
-__device__ __forceinline__ void base_inverse(const double* __restrict__ Qi, int M, const int* modes,
-                                             double (&G)[4], bool& bad) {
-  constexpr int N = NX + NB;
-  Tri<2 * N> A;
-  gather_q<N>(Qi, M, modes, A);
-  double S[tri_size(2 * NB)];
+// The blocks of Q_T^{-1} at the last two of T's modes [X (NX of them), i, j]: X is
+// eliminated block by block, then the 4x4 Schur complement of (i, j) is inverted.
+// G: block (i, j); Di, Dj: blocks (i, i), (j, j) (x-x, p-x, p-p).
+template <int NX>
+__device__ __forceinline__ void pair_inverse(const double* __restrict__ Qi, const double* __restrict__ Qd, int M,
+                                             const int (&modes)[NX + 2], double (&G)[4], double (&Di)[3],
+                                             double (&Dj)[3], bool& bad) {
+  Tri<2 * NX + 4> A;
+  gather_q_coalesced<NX + 2, 0>(Qi, Qd, M, modes, A);
+  double S[tri_size(4)];
+  auto pivot = [&](double a, double b, double c) {
+    const double det = fma(a, c, -b * b);
+    bad |= !(det > 0.0);
+    return 1.0 / det;
+  };
   if constexpr (NX == 0) {
 #pragma unroll
-    for (int q = 0; q < tri_size(2 * NB); ++q) S[q] = A.a[q];
+    for (int q = 0; q < tri_size(4); ++q) S[q] = A.a[q];
   } else {
-    Tri<2 * N - 2> A1;
-    const double det0 = fma(A.a[0], A.a[2], -A.a[1] * A.a[1]);
-    bad |= !(det0 > 0.0);
-    schur_leading_block<2 * N>(A, 1.0 / det0, A1);
+    Tri<2 * NX + 2> A1;
+    schur_leading_block<2 * NX + 4>(A, pivot(A.a[0], A.a[1], A.a[2]), A1);
     if constexpr (NX == 1) {
 #pragma unroll
-      for (int q = 0; q < tri_size(2 * NB); ++q) S[q] = A1.a[q];
+      for (int q = 0; q < tri_size(4); ++q) S[q] = A1.a[q];
     } else {
-      Tri<2 * N - 4> A2;
-      const double det1 = fma(A1.a[0], A1.a[2], -A1.a[1] * A1.a[1]);
-      bad |= !(det1 > 0.0);
-      schur_leading_block<2 * N - 2>(A1, 1.0 / det1, A2);
+      Tri<2 * NX> A2;
+      schur_leading_block<2 * NX + 2>(A1, pivot(A1.a[0], A1.a[1], A1.a[2]), A2);
       if constexpr (NX == 2) {
 #pragma unroll
-        for (int q = 0; q < tri_size(2 * NB); ++q) S[q] = A2.a[q];
+        for (int q = 0; q < tri_size(4); ++q) S[q] = A2.a[q];
       } else {
-        Tri<2 * N - 6> A3;
-        const double det2 = fma(A2.a[0], A2.a[2], -A2.a[1] * A2.a[1]);
-        bad |= !(det2 > 0.0);
-        schur_leading_block<2 * N - 4>(A2, 1.0 / det2, A3);
-        if constexpr (NX == 3) {
+        static_assert(NX == 3, "at most three eliminated blocks");
+        Tri<2 * NX - 2> A3;
+        schur_leading_block<2 * NX>(A2, pivot(A2.a[0], A2.a[1], A2.a[2]), A3);
 #pragma unroll
-          for (int q = 0; q < tri_size(2 * NB); ++q) S[q] = A3.a[q];
-        } else {
-          static_assert(NX <= 4, "at most four eliminated blocks");
-          Tri<2 * N - 8> A4;
-          const double det3 = fma(A3.a[0], A3.a[2], -A3.a[1] * A3.a[1]);
-          bad |= !(det3 > 0.0);
-          schur_leading_block<2 * N - 6>(A3, 1.0 / det3, A4);
-#pragma unroll
-          for (int q = 0; q < tri_size(2 * NB); ++q) S[q] = A4.a[q];
-        }
+        for (int q = 0; q < tri_size(4); ++q) S[q] = A3.a[q];
       }
     }
   }
-  if constexpr (NB == 1) {
-    // inverse of the 2x2 Schur complement [[s00, s10], [s10, s11]]
-    const double det = fma(S[0], S[2], -S[1] * S[1]);
-    bad |= !(det > 0.0);
-    const double inv = 1.0 / det;
-    G[0] = S[2] * inv;
-    G[1] = -S[1] * inv;
-    G[2] = -S[1] * inv;
-    G[3] = S[0] * inv;
-  } else {
-    // [[A, Bm], [Bm^T, C]]^{-1} off-diagonal block = -A^{-1} Bm Sc^{-1},
-    // Sc = C - Bm^T A^{-1} Bm.  Packed 4x4: A = (0,0),(1,0),(1,1);
-    // Bm^T rows 2,3 cols 0,1; C = (2,2),(3,2),(3,3).
-    const double a00 = S[tri(0, 0)], a10 = S[tri(1, 0)], a11 = S[tri(1, 1)];
-    const double b00 = S[tri(2, 0)], b01 = S[tri(3, 0)], b10 = S[tri(2, 1)], b11 = S[tri(3, 1)];
-    // Bm = [[b00, b01], [b10, b11]] (rows: A's modes, cols: C's modes)
-    const double da = fma(a00, a11, -a10 * a10);
-    bad |= !(da > 0.0);
-    const double ia = 1.0 / da;
-    const double ai00 = a11 * ia, ai01 = -a10 * ia, ai11 = a00 * ia;
-    // Y = A^{-1} Bm
-    const double y00 = ai00 * b00 + ai01 * b10, y01 = ai00 * b01 + ai01 * b11;
-    const double y10 = ai01 * b00 + ai11 * b10, y11 = ai01 * b01 + ai11 * b11;
-    // Sc = C - Bm^T Y
-    const double c00 = S[tri(2, 2)] - (b00 * y00 + b10 * y10);
-    const double c01 = S[tri(3, 2)] - (b00 * y01 + b10 * y11);
-    const double c11 = S[tri(3, 3)] - (b01 * y01 + b11 * y11);
-    const double dc = fma(c00, c11, -c01 * c01);
-    bad |= !(dc > 0.0);
-    const double ic = 1.0 / dc;
-    const double si00 = c11 * ic, si01 = -c01 * ic, si11 = c00 * ic;
-    // -Y Sc^{-1}
-    G[0] = -(y00 * si00 + y01 * si01);
-    G[1] = -(y00 * si01 + y01 * si11);
-    G[2] = -(y10 * si00 + y11 * si01);
-    G[3] = -(y10 * si01 + y11 * si11);
-  }
+  // [[A, Bm], [Bm^T, C]]^{-1}: with Y = A^{-1} Bm and Sc = C - Bm^T Y, the blocks
+  // are Sc^{-1} at C, -Y Sc^{-1} off the diagonal, A^{-1} + Y Sc^{-1} Y^T at A.
+  const double a00 = S[tri(0, 0)], a10 = S[tri(1, 0)], a11 = S[tri(1, 1)];
+  const double b00 = S[tri(2, 0)], b01 = S[tri(3, 0)], b10 = S[tri(2, 1)], b11 = S[tri(3, 1)];
+  const double ia = pivot(a00, a10, a11);
+  const double ai00 = a11 * ia, ai01 = -a10 * ia, ai11 = a00 * ia;
+  const double y00 = ai00 * b00 + ai01 * b10, y01 = ai00 * b01 + ai01 * b11;
+  const double y10 = ai01 * b00 + ai11 * b10, y11 = ai01 * b01 + ai11 * b11;
+  const double c00 = S[tri(2, 2)] - (b00 * y00 + b10 * y10);
+  const double c01 = S[tri(3, 2)] - (b00 * y01 + b10 * y11);
+  const double c11 = S[tri(3, 3)] - (b01 * y01 + b11 * y11);
+  const double ic = pivot(c00, c01, c11);
+  const double si00 = c11 * ic, si01 = -c01 * ic, si11 = c00 * ic;
+  G[0] = -(y00 * si00 + y01 * si01);
+  G[1] = -(y00 * si01 + y01 * si11);
+  G[2] = -(y10 * si00 + y11 * si01);
+  G[3] = -(y10 * si01 + y11 * si11);
+  Dj[0] = si00;
+  Dj[1] = si01;
+  Dj[2] = si11;
+  Di[0] = ai00 - (G[0] * y00 + G[1] * y01);
+  Di[1] = ai01 - (G[2] * y00 + G[3] * y01);
+  Di[2] = ai11 - (G[2] * y10 + G[3] * y11);
 }
 
-template <int NB>
-__device__ __forceinline__ void base_inverse_dispatch(const double* __restrict__ Qi, int M,
-                                                      const int* modes, int nx, double (&G)[4],
-                                                      bool& bad) {
-  switch (nx) {
-    case 0: base_inverse<0, NB>(Qi, M, modes, G, bad); break;
-    case 1: base_inverse<1, NB>(Qi, M, modes, G, bad); break;
-    case 2: base_inverse<2, NB>(Qi, M, modes, G, bad); break;
-    case 3: base_inverse<3, NB>(Qi, M, modes, G, bad); break;
-    default: if constexpr (NB == 1) base_inverse<4, 1>(Qi, M, modes, G, bad); break;
+// The terms of a pair (i < j) with NX further modes.
+template <int NX>
+__device__ __forceinline__ void pair_terms(const double* __restrict__ Qi, const double* __restrict__ Qd, int M,
+                                           const int (&base)[2], const Offsets& o, const uint64_t* __restrict__ bin,
+                                           const double* __restrict__ ptab, const double* __restrict__ pbar,
+                                           double (&acc)[4], double (&di)[3], double (&dj)[3], bool& bad) {
+  const uint64_t n = NX == 0 ? 1 : binom_at(bin, M - 2, NX);
+  for (uint64_t q = threadIdx.x; q < n; q += blockDim.x) {
+    int modes[NX + 2];
+    uint64_t rank;
+    if constexpr (NX == 0) {
+      rank = set_rank<2>(bin, base);
+    } else {
+      int X[NX];
+      unrank_small<NX>(bin, q, M - 2, X);
+      complement_modes<NX, 2>(base, X);
+      rank = union_rank<2, NX>(bin, base, X);
+#pragma unroll
+      for (int t = 0; t < NX; ++t) modes[t] = X[t];
+    }
+    modes[NX] = base[0];
+    modes[NX + 1] = base[1];
+    const int64_t at = o.off[NX + 2] + (int64_t)rank;
+    const double w = -0.5 * pbar[at] * ptab[at];
+    double G[4], Di[3], Dj[3];
+    pair_inverse<NX>(Qi, Qd, M, modes, G, Di, Dj, bad);
+    const double wd = w / (double)(NX + 1);  // i's diagonal block is shared by T's NX + 1 pairs with i
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] = fma(w, G[e], acc[e]);
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+      di[e] = fma(wd, Di[e], di[e]);
+      dj[e] = fma(wd, Dj[e], dj[e]);
+    }
   }
-}
-
-// Mode pair of a sigma-bar item: the diagonal pairs (i, i), or the pairs i < j
-// in colex order (item j (j - 1) / 2 + i).
-__device__ __forceinline__ void pair_of(int64_t pid, int diag, int* pi_, int* pj_) {
-  if (diag) {
-    *pi_ = *pj_ = (int)pid;
-    return;
-  }
-  int j = (int)((1.0 + sqrt(8.0 * (double)pid + 1.0)) / 2.0);
-  while ((int64_t)j * (j - 1) / 2 > pid) --j;
-  while ((int64_t)(j + 1) * j / 2 <= pid) ++j;
-  *pi_ = (int)(pid - (int64_t)j * (j - 1) / 2);
-  *pj_ = j;
 }
 
 // The 2x2 block (i, j) of dL/dsigma (interleaved (2i + a, 2j + b) -> xxpp
@@ -467,78 +505,93 @@ __device__ __forceinline__ void store_sigma_block(double* __restrict__ gsig, int
   }
 }
 
-// One wavefront per mode pair (i <= j): the 2x2 block of dL/dsigma.
-// One workgroup per mode pair (i, j): the diagonal pairs (many more supersets,
-// wide workgroups) and the pairs i < j (colex, blockIdx = j (j - 1) / 2 + i)
-// are separate launches.
-__global__ __launch_bounds__(kSigmaThreads) void sigma_bar_kernel(const double* __restrict__ Qi,
-                                                                int M, int K, int diag, Offsets o,
-                                                                const uint64_t* __restrict__ bin,
-                                                                const double* __restrict__ ptab,
-                                                                const double* __restrict__ pbar,
-                                                                double* __restrict__ gsig,
-                                                                DeviceStatus* __restrict__ st,
-                                                                double* __restrict__ part) {
-  const int64_t pid = blockIdx.x;
-  int i, j;
-  pair_of(pid, diag, &i, &j);
-  int base[2] = {i, j};
-  const int nb = (i == j) ? 1 : 2;
-  const int u = M - nb;
-  uint64_t lo, hi;
-  chunk_range(count_sized(bin, 0, K - nb, u), &lo, &hi);
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+// One workgroup per pair i < j (colex): the block (i, j) of dL/dsigma, and the
+// pair's share of the blocks (i, i) and (j, j) in diag[(i M + j) 3], diag[(j M + i) 3].
+template <int KX>
+__global__ __launch_bounds__(kSigmaThreads) void sigma_pairs_kernel(const double* __restrict__ Qi,
+                                                                    const double* __restrict__ Qd, int M, Offsets o,
+                                                                    const uint64_t* __restrict__ bin,
+                                                                    const double* __restrict__ ptab,
+                                                                    const double* __restrict__ pbar,
+                                                                    double* __restrict__ gsig,
+                                                                    double* __restrict__ diag,
+                                                                    DeviceStatus* __restrict__ st) {
+  int base[2];
+  unrank_small<2>(bin, blockIdx.x, M, base);
+  double acc[4] = {}, di[3] = {}, dj[3] = {};
   bool bad = false;
-  for (uint64_t q = lo + threadIdx.x; q < hi; q += blockDim.x) {
-    int jx;
-    uint64_t rx;
-    flat_to_sized(bin, q, 0, K - nb, u, &jx, &rx);
-    int xc[kMaxOrder], X[kMaxOrder], T[kMaxOrder];
-    unrank_dyn(bin, rx, jx, u, xc);
-    complement_modes(xc, jx, base, nb, X);
-    const int n = merge_sorted(base, nb, X, jx, T);
-    const int64_t at = o.off[n] + (int64_t)rank_sorted(bin, T, n);
-    const double w = -0.5 * pbar[at] * ptab[at];
-    int modes[kMaxOrder];
-    for (int t = 0; t < jx; ++t) modes[t] = X[t];
-    for (int t = 0; t < nb; ++t) modes[jx + t] = base[t];
-    double G[4];
-    if (nb == 1) base_inverse_dispatch<1>(Qi, M, modes, jx, G, bad);
-    else base_inverse_dispatch<2>(Qi, M, modes, jx, G, bad);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) acc[e] = fma(w, G[e], acc[e]);
-  }
+  pair_terms<0>(Qi, Qd, M, base, o, bin, ptab, pbar, acc, di, dj, bad);
+  if constexpr (KX >= 1) pair_terms<1>(Qi, Qd, M, base, o, bin, ptab, pbar, acc, di, dj, bad);
+  if constexpr (KX >= 2) pair_terms<2>(Qi, Qd, M, base, o, bin, ptab, pbar, acc, di, dj, bad);
+  if constexpr (KX >= 3) pair_terms<3>(Qi, Qd, M, base, o, bin, ptab, pbar, acc, di, dj, bad);
+  const int i = base[0], j = base[1];
+  if (bad) latch_failure(st, 0, (int64_t)j * (j + 1) / 2 + i);  // pair index, i <= j
 #pragma unroll
   for (int e = 0; e < 4; ++e) acc[e] = block_sum(acc[e]);
-  if (bad) latch_failure(st, 0, (int64_t)j * (j + 1) / 2 + i);  // pair index, i <= j
-  if (threadIdx.x == 0 && gridDim.y > 1) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) part[((size_t)pid * gridDim.y + blockIdx.y) * 4 + e] = acc[e];
-  } else if (threadIdx.x == 0) {
-    store_sigma_block(gsig, M, i, j, acc);
+  for (int e = 0; e < 3; ++e) {
+    di[e] = block_sum(di[e]);
+    dj[e] = block_sum(dj[e]);
+  }
+  if (threadIdx.x != 0) return;
+  store_sigma_block(gsig, M, i, j, acc);
+#pragma unroll
+  for (int e = 0; e < 3; ++e) {
+    diag[((size_t)i * M + j) * 3 + e] = di[e];
+    diag[((size_t)j * M + i) * 3 + e] = dj[e];
   }
 }
 
-// The split sigma-bar sums: partials in chunk order, then as sigma_bar_kernel.
-__global__ void sigma_finish_kernel(int M, int diag, int nsplit, uint64_t count,
-                                    const double* __restrict__ part, double* __restrict__ gsig) {
-  const uint64_t pid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (pid >= count) return;
-  int i, j;
-  pair_of((int64_t)pid, diag, &i, &j);
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int y = 0; y < nsplit; ++y)
+// Order 1 alone reaches the diagonal blocks only: the others are 0.
+__global__ void zero_kernel(double* __restrict__ gsig, size_t n) {
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) gsig[i] = 0.0;
+}
+hipError_t launch_zero_offdiag(double* gsig, int M, hipStream_t s) {
+  const size_t n = 4 * (size_t)M * M;
+  hipLaunchKernelGGL(zero_kernel, dim3((unsigned)std::min<size_t>((n + 255) / 256, 4096)), dim3(256), 0, s, gsig, n);
+  return hipGetLastError();
+}
+
+// The blocks (i, i): the subset {i} alone and the pairs' shares, one wavefront per i.
+__global__ __launch_bounds__(256) void sigma_diag_kernel(const double* __restrict__ Qd, int M, int K,
+                                                         const double* __restrict__ ptab,
+                                                         const double* __restrict__ pbar,
+                                                         const double* __restrict__ diag, double* __restrict__ gsig,
+                                                         DeviceStatus* __restrict__ st) {
+  const int i = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (i >= M) return;
+  double d[3] = {};
+  if (K >= 2)
+    for (int j = lane; j < M; j += 64)
+      if (j != i)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) acc[e] += part[(pid * nsplit + y) * 4 + e];
-  store_sigma_block(gsig, M, i, j, acc);
+        for (int e = 0; e < 3; ++e) d[e] += diag[((size_t)i * M + j) * 3 + e];
+#pragma unroll
+  for (int e = 0; e < 3; ++e) d[e] = wave_sum(d[e]);
+  if (lane != 0) return;
+  const double a00 = Qd[4 * (size_t)i], a10 = Qd[4 * (size_t)i + 1], a11 = Qd[4 * (size_t)i + 2];
+  const double det = fma(a00, a11, -a10 * a10);
+  if (!(det > 0.0)) latch_failure(st, 0, (int64_t)i * (i + 1) / 2 + i);
+  const double w = -0.5 * pbar[i] * ptab[i] / det;
+  d[0] = fma(w, a11, d[0]);
+  d[1] = fma(w, -a10, d[1]);
+  d[2] = fma(w, a00, d[2]);
+  const double acc[4] = {d[0], d[1], d[1], d[2]};
+  store_sigma_block(gsig, M, i, i, acc);
 }
 
 }  // namespace
 
-hipError_t launch_adjoint(int M, int K, int flags, const double* Qi, const uint64_t* binom,
+size_t adjoint_sup_doubles(int M, int K) {
+  size_t n = 1;
+  for (int t = 1; t < K; ++t) n += (size_t)(K - t) * host_binom(M, t);
+  return n;
+}
+
+hipError_t launch_adjoint(int M, int K, int flags, const double* Qi, const double* Qd, const uint64_t* binom,
                           const double* m, const double* ptab, const double* gm, const double* gk,
                           double* d1, double* mbar, double* pbar, double* gsig, DeviceStatus* st,
-                          double* part, hipStream_t s) {
+                          double* part, double* sup, double* diag, hipStream_t s) {
   Offsets o{};
   o.off[1] = 0;
   for (int d = 1; d <= kMaxOrder; ++d) o.off[d + 1] = o.off[d] + (d <= K ? (int64_t)host_binom(M, d) : 0);
@@ -552,37 +605,39 @@ hipError_t launch_adjoint(int M, int K, int flags, const double* Qi, const uint6
     if (e == hipSuccess) e = hipGetLastError();
     if (e == hipSuccess) e = timing_end(s);
   }
-  // threads per workgroup for a sum over n supersets: whole wavefronts, at most kSumThreads
-  auto threads_for = [](uint64_t n, int cap = kSumThreads) {
+  // threads per workgroup for a sum over n terms: whole wavefronts, at most cap
+  auto threads_for = [](uint64_t n, int cap) {
     const uint64_t w = std::max<uint64_t>(1, std::min<uint64_t>((n + kWave - 1) / kWave,
                                                                 (uint64_t)(cap / kWave)));
     return (unsigned)(w * kWave);
   };
-  auto supersets = [&](int k, int jmin) {  // sum_{j = jmin}^{K-k} C(M - k, j)
-    uint64_t n = 0;
-    for (int j = jmin; j <= K - k; ++j) n += host_binom(M - k, j);
-    return n;
-  };
-  // workgroups per sum: a launch of fewer than kAdjointSplitItems long sums
-  // (the order-1 subsets, the diagonal mode pairs) would leave compute units
-  // idle, so each sum is split into chunks of at least 512 terms
+  // Workgroups per mbar sum: a launch of fewer than kAdjointSplitItems long sums
+  // (the order-1 subsets) would leave compute units idle, so each sum is split into
+  // chunks of at least 16,384 terms (16 rounds of a workgroup; at 10,296 terms, M =
+  // 144, K = 3, one workgroup per sum is faster than the partial sums' second launch).
   auto split_for = [](uint64_t items, uint64_t n) -> unsigned {
     if (items >= (uint64_t)kAdjointSplitItems) return 1u;
     const uint64_t want = ((uint64_t)kAdjointSplitItems + items - 1) / items;
-    return (unsigned)std::max<uint64_t>(1, std::min<uint64_t>({want, (uint64_t)kAdjointMaxSplit, n / 512}));
+    return (unsigned)std::max<uint64_t>(1, std::min<uint64_t>({want, (uint64_t)kAdjointMaxSplit, n / 16384}));
   };
-  auto finish_grid = [](uint64_t items) { return dim3((unsigned)((items + 255) / 256)); };
   for (int k = 1; k < K && e == hipSuccess; ++k) {
     e = timing_begin(s, GBS_STAGE_ADJOINT, k);
-    const uint64_t items = host_binom(M, k), n = supersets(k, 1);
+    const uint64_t items = host_binom(M, k);
+    uint64_t n = 0;
+    for (int j = 1; j <= K - k; ++j) n += host_binom(M - k, j);
     const unsigned ns = gk ? split_for(items, n) : 1u;
-    if (e == hipSuccess)
-      hipLaunchKernelGGL(mbar_kernel, dim3((unsigned)items, ns),
-                         dim3(gk ? threads_for((n + ns - 1) / ns) : kWave), 0, s, M, K, k, o,
-                         binom, gm, gk, d1, mbar, part);
-    if (e == hipSuccess) e = hipGetLastError();
+    const dim3 grid((unsigned)items, ns), wg(gk ? threads_for((n + ns - 1) / ns, kSumThreads) : kWave);
+    if (e == hipSuccess) {
+      switch (k) {
+        case 1: hipLaunchKernelGGL(mbar_kernel<1>, grid, wg, 0, s, M, K, o, binom, gm, gk, d1, mbar, part); break;
+        case 2: hipLaunchKernelGGL(mbar_kernel<2>, grid, wg, 0, s, M, K, o, binom, gm, gk, d1, mbar, part); break;
+        case 3: hipLaunchKernelGGL(mbar_kernel<3>, grid, wg, 0, s, M, K, o, binom, gm, gk, d1, mbar, part); break;
+        default: hipLaunchKernelGGL(mbar_kernel<4>, grid, wg, 0, s, M, K, o, binom, gm, gk, d1, mbar, part); break;
+      }
+      e = hipGetLastError();
+    }
     if (e == hipSuccess && ns > 1)
-      hipLaunchKernelGGL(mbar_finish_kernel, finish_grid(items), dim3(256), 0, s, k, (int)ns,
+      hipLaunchKernelGGL(mbar_finish_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, k, (int)ns,
                          items, o, gm, gk, part, mbar);
     if (e == hipSuccess) e = hipGetLastError();
     if (e == hipSuccess) e = timing_end(s);
@@ -596,41 +651,38 @@ hipError_t launch_adjoint(int M, int K, int flags, const double* Qi, const uint6
     if (e == hipSuccess) e = hipGetLastError();
     if (e == hipSuccess) e = timing_end(s);
   }
-  for (int t = 1; t < K && e == hipSuccess; ++t) {
+  for (int t = K - 1; t >= 1 && e == hipSuccess; --t) {  // each from the order above
     e = timing_begin(s, GBS_STAGE_ADJOINT, t);
-    const uint64_t items = host_binom(M, t), n = supersets(t, 0);
-    const unsigned ns = split_for(items, n);
-    if (e == hipSuccess)
-      hipLaunchKernelGGL(pbar_kernel, dim3((unsigned)items, ns), dim3(threads_for((n + ns - 1) / ns)),
-                         0, s, M, K, t, parity, o, binom, mbar, pbar, part);
-    if (e == hipSuccess) e = hipGetLastError();
-    if (e == hipSuccess && ns > 1)
-      hipLaunchKernelGGL(pbar_finish_kernel, finish_grid(items), dim3(256), 0, s, t, parity,
-                         (int)ns, items, o, part, pbar);
-    if (e == hipSuccess) e = hipGetLastError();
+    const dim3 grid((unsigned)((host_binom(M, t) + 3) / 4)), wg(256);
+    if (e == hipSuccess) {
+      switch (t) {
+        case 1: hipLaunchKernelGGL(pbar_kernel<1>, grid, wg, 0, s, M, K, parity, o, binom, mbar, sup, pbar); break;
+        case 2: hipLaunchKernelGGL(pbar_kernel<2>, grid, wg, 0, s, M, K, parity, o, binom, mbar, sup, pbar); break;
+        case 3: hipLaunchKernelGGL(pbar_kernel<3>, grid, wg, 0, s, M, K, parity, o, binom, mbar, sup, pbar); break;
+        default: hipLaunchKernelGGL(pbar_kernel<4>, grid, wg, 0, s, M, K, parity, o, binom, mbar, sup, pbar); break;
+      }
+      e = hipGetLastError();
+    }
     if (e == hipSuccess) e = timing_end(s);
   }
   if (e == hipSuccess) {
     e = timing_begin(s, GBS_STAGE_ADJOINT, 0);
-    // supersets of {i} (diagonal) and of {i, j}: sum_j C(M - nb, j), j <= K - nb
-    auto sets = [&](int nb) {
-      uint64_t n = 0;
-      for (int q = 0; q <= K - nb; ++q) n += host_binom(M - nb, q);
-      return n;
-    };
-    for (int diag = 1; diag >= 0 && e == hipSuccess; --diag) {
-      const uint64_t items = diag ? (uint64_t)M : (uint64_t)M * (M - 1) / 2;
-      if (items == 0) continue;
-      const uint64_t n = sets(diag ? 1 : 2);
-      const unsigned ns = split_for(items, n);
-      hipLaunchKernelGGL(sigma_bar_kernel, dim3((unsigned)items, ns),
-                         dim3(threads_for((n + ns - 1) / ns, kSigmaThreads)), 0, s, Qi, M, K, diag,
-                         o, binom, ptab, pbar, gsig, st, part);
+    const uint64_t pairs = (uint64_t)M * (M - 1) / 2;
+    if (e == hipSuccess && K >= 2 && pairs) {
+      const dim3 grid((unsigned)pairs), wg(threads_for(host_binom(M - 2, K - 2), kSigmaThreads));
+      switch (K) {
+        case 2: hipLaunchKernelGGL(sigma_pairs_kernel<0>, grid, wg, 0, s, Qi, Qd, M, o, binom, ptab, pbar, gsig, diag, st); break;
+        case 3: hipLaunchKernelGGL(sigma_pairs_kernel<1>, grid, wg, 0, s, Qi, Qd, M, o, binom, ptab, pbar, gsig, diag, st); break;
+        case 4: hipLaunchKernelGGL(sigma_pairs_kernel<2>, grid, wg, 0, s, Qi, Qd, M, o, binom, ptab, pbar, gsig, diag, st); break;
+        default: hipLaunchKernelGGL(sigma_pairs_kernel<3>, grid, wg, 0, s, Qi, Qd, M, o, binom, ptab, pbar, gsig, diag, st); break;
+      }
       e = hipGetLastError();
-      if (e == hipSuccess && ns > 1)
-        hipLaunchKernelGGL(sigma_finish_kernel, finish_grid(items), dim3(256), 0, s, M, diag,
-                           (int)ns, items, part, gsig);
-      if (e == hipSuccess) e = hipGetLastError();
+    }
+    if (e == hipSuccess && K == 1 && pairs) e = launch_zero_offdiag(gsig, M, s);
+    if (e == hipSuccess) {
+      hipLaunchKernelGGL(sigma_diag_kernel, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, s, Qd, M, K, ptab, pbar, diag,
+                         gsig, st);
+      e = hipGetLastError();
     }
     if (e == hipSuccess) e = timing_end(s);
   }

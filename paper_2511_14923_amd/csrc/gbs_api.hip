@@ -367,6 +367,8 @@ gbs_status run_adjoint(int32_t M, const double* sigma, int32_t K, int32_t flags,
   const size_t oPb = off; off += align256(N * sizeof(double));
   const size_t oSt = off; off += align256(sizeof(DeviceStatus));
   const size_t oPart = off; off += align256(kAdjointPartDoubles * sizeof(double));
+  const size_t oSup = off; off += align256(adjoint_sup_doubles(M, K) * sizeof(double));
+  const size_t oDiag = off; off += align256(3 * (size_t)M * M * sizeof(double));
   void* scratch = nullptr;
   e = hipMallocAsync(&scratch, off, s);
   if (e != hipSuccess) return to_status(e);
@@ -405,8 +407,8 @@ gbs_status run_adjoint(int32_t M, const double* sigma, int32_t K, int32_t flags,
     if (e == hipSuccess) e = timing_end(s);
   }
   if (e == hipSuccess)
-    e = launch_adjoint(M, K, flags, Qi, ctx->binom, m, ptab, gm, gk, d1, mbar, pbar, gsig, st, part,
-                       s);
+    e = launch_adjoint(M, K, flags, Qi, Qd, ctx->binom, m, ptab, gm, gk, d1, mbar, pbar, gsig, st, part,
+                       reinterpret_cast<double*>(b + oSup), reinterpret_cast<double*>(b + oDiag), s);
   if (e != hipSuccess) {
     (void)hipFreeAsync(scratch, s);
     return to_status(e);

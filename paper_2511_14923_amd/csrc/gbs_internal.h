@@ -174,15 +174,17 @@ hipError_t launch_forward_pairs(int M, int flags, const double* Qi, const double
 // Vector-Jacobian product given the forward correlators m and vacuum
 // probabilities ptab of every subset (orders 1..K); d1, mbar, pbar are scratch
 // of N(M, K) doubles, part scratch of kAdjointPartDoubles doubles (the partial
-// sums of superset sums split over several workgroups); gsig (2M x 2M, xxpp)
-// is overwritten.
+// sums of superset sums split over several workgroups), sup of
+// adjoint_sup_doubles(M, K) (superset sums by size), diag of 3 M^2 (the pairs'
+// shares of the diagonal blocks); gsig (2M x 2M, xxpp) is overwritten.
 constexpr int kAdjointSplitItems = 2048;  // a launch of fewer sums splits each one
 constexpr int kAdjointMaxSplit = 16;
-constexpr size_t kAdjointPartDoubles = 4 * 2 * (size_t)kAdjointSplitItems;
-hipError_t launch_adjoint(int M, int K, int flags, const double* Qi, const uint64_t* binom,
+constexpr size_t kAdjointPartDoubles = 2 * (size_t)kAdjointSplitItems;
+size_t adjoint_sup_doubles(int M, int K);
+hipError_t launch_adjoint(int M, int K, int flags, const double* Qi, const double* Qd, const uint64_t* binom,
                           const double* m, const double* ptab, const double* gm, const double* gk,
                           double* d1, double* mbar, double* pbar, double* gsig, DeviceStatus* st,
-                          double* part, hipStream_t s);
+                          double* part, double* sup, double* diag, hipStream_t s);
 
 // Stage-2 sampler (gbs_sampler.hip): nsamples patterns of M bits from the
 // parity cumulants kap (orders 1..K, K = 3 or 5), uniforms u (M x nsamples),
