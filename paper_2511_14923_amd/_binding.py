@@ -53,7 +53,9 @@ EXPORTS = (
     "gbs_sample_cumulants", "gbs_pearson", "gbs_last_error",
     "gbs_last_timings", "gbs_status_string", "gbs_cumulants_noalloc",
     "gbs_sample_scratch", "gbs_sample_in", "gbs_sample_cumulants_scratch",
-    "gbs_sample_cumulants_in",
+    "gbs_sample_cumulants_in", "gbs_cumulants_scratch", "gbs_cumulants_in",
+    "gbs_cumulant_grad_scratch", "gbs_cumulant_grad_in", "gbs_pearson_scratch",
+    "gbs_pearson_in",
 )
 
 
@@ -126,6 +128,14 @@ def lib() -> ctypes.CDLL:
     L.gbs_sample.restype = i32
     L.gbs_sample_cumulants.argtypes = [i32, i64, vp, i32, vp, i32, vp]
     L.gbs_sample_cumulants.restype = i32
+    L.gbs_cumulants_scratch.argtypes = [i32, i32, i32, i32, i32]
+    L.gbs_cumulants_scratch.restype = i64
+    L.gbs_cumulants_in.argtypes = [i32, vp, vp, i32, i32, vp, vp, vp, i64, vp]
+    L.gbs_cumulants_in.restype = i32
+    L.gbs_cumulant_grad_scratch.argtypes = [i32, i32]
+    L.gbs_cumulant_grad_scratch.restype = i64
+    L.gbs_cumulant_grad_in.argtypes = [i32, vp, i32, i32, vp, vp, vp, vp, i64, vp]
+    L.gbs_cumulant_grad_in.restype = i32
     L.gbs_sample_scratch.argtypes = [i32, i32, i64, i64]
     L.gbs_sample_scratch.restype = i64
     L.gbs_sample_in.argtypes = [i32, vp, i32, i64, vp, vp, vp, vp, vp, i64, i32, vp]
@@ -136,6 +146,10 @@ def lib() -> ctypes.CDLL:
     L.gbs_sample_cumulants_in.restype = i32
     L.gbs_pearson.argtypes = [i64, vp, vp, vp, i32, vp]
     L.gbs_pearson.restype = i32
+    L.gbs_pearson_scratch.argtypes = []
+    L.gbs_pearson_scratch.restype = i64
+    L.gbs_pearson_in.argtypes = [i64, vp, vp, vp, vp, i64, i32, vp]
+    L.gbs_pearson_in.restype = i32
     L.gbs_last_error.argtypes = [ctypes.POINTER(i32), ctypes.POINTER(i64)]
     L.gbs_last_error.restype = i32
     L.gbs_last_timings.argtypes = [i32, ctypes.POINTER(gbs_kernel_time)]
@@ -227,19 +241,37 @@ def _scratch(nbytes, stream, device):
     `stream`, or None (the library then allocates its own).  From torch's caching
     allocator: it keeps the memory for the next call, gives it back when other
     tensors need it (or on torch.cuda.empty_cache), and hands it out again only
-    to work that runs after this call's on the same stream."""
+    to work that runs after this call's on the same stream.  A stream that is
+    being captured gets None: the graph must hold memory of its own."""
     if nbytes <= 0:
         return None
-    if stream is None:
-        stream = torch.cuda.current_stream(device)
-    elif not isinstance(stream, torch.cuda.Stream):
-        stream = (torch.cuda.ExternalStream(int(stream), device) if int(stream)
-                  else torch.cuda.default_stream(device))
     try:
+        if stream is None:
+            if torch.cuda.is_current_stream_capturing():
+                return None
+            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        if not isinstance(stream, torch.cuda.Stream):
+            stream = (torch.cuda.ExternalStream(int(stream), device) if int(stream)
+                      else torch.cuda.default_stream(device))
         with torch.cuda.stream(stream):
+            if torch.cuda.is_current_stream_capturing():
+                return None
             return torch.empty(nbytes, dtype=torch.uint8, device=device)
     except torch.OutOfMemoryError:
         return None
+
+
+def _forward(M, sigma, mu, max_order, flags, corr, cum, stream, own):
+    """A forward call in lent scratch memory, or own() without any."""
+    dev = sigma.device
+    with torch.cuda.device(dev):
+        work = _scratch(lib().gbs_cumulants_scratch(M, max_order, flags, mu is not None,
+                                                    corr is not None), stream, dev)
+        if work is None:
+            return own(_stream(stream, dev))
+        return lib().gbs_cumulants_in(M, _ptr(sigma), _ptr(mu), max_order, flags, _ptr(corr),
+                                      _ptr(cum), ctypes.c_void_p(work.data_ptr()), work.numel(),
+                                      _stream(stream, dev))
 
 
 # ---- host helpers -----------------------------------------------------------
@@ -302,9 +334,8 @@ def gbs_correlators(M: int, sigma: torch.Tensor, max_order: int, flags: int = 0,
     corr = _out(corr, n, sigma)
     _need(corr, "corr", n)
     _same_device(("sigma", sigma), ("corr", corr))
-    with torch.cuda.device(sigma.device):
-        st = lib().gbs_correlators(M, _ptr(sigma), max_order, flags, _ptr(corr),
-                                   _stream(stream, sigma.device))
+    st = _forward(M, sigma, None, max_order, flags, corr, None, stream,
+                  lambda s: lib().gbs_correlators(M, _ptr(sigma), max_order, flags, _ptr(corr), s))
     _check(st, "gbs_correlators")
     return corr
 
@@ -319,9 +350,9 @@ def gbs_cumulants(M: int, sigma: torch.Tensor, max_order: int, flags: int = 0, c
     _need(corr, "corr", n, optional=True)
     _need(cum, "cum", n)
     _same_device(("sigma", sigma), ("corr", corr), ("cum", cum))
-    with torch.cuda.device(sigma.device):
-        st = lib().gbs_cumulants(M, _ptr(sigma), max_order, flags, _ptr(corr), _ptr(cum),
-                                 _stream(stream, sigma.device))
+    st = _forward(M, sigma, None, max_order, flags, corr, cum, stream,
+                  lambda s: lib().gbs_cumulants(M, _ptr(sigma), max_order, flags, _ptr(corr),
+                                                _ptr(cum), s))
     _check(st, "gbs_cumulants")
     return corr, cum
 
@@ -354,9 +385,9 @@ def gbs_cumulants_displaced(M: int, sigma: torch.Tensor, mu: torch.Tensor, max_o
     _need(corr, "corr", n, optional=True)
     _need(cum, "cum", n)
     _same_device(("sigma", sigma), ("mu", mu), ("corr", corr), ("cum", cum))
-    with torch.cuda.device(sigma.device):
-        st = lib().gbs_cumulants_displaced(M, _ptr(sigma), _ptr(mu), max_order, flags, _ptr(corr),
-                                           _ptr(cum), _stream(stream, sigma.device))
+    st = _forward(M, sigma, mu, max_order, flags, corr, cum, stream,
+                  lambda s: lib().gbs_cumulants_displaced(M, _ptr(sigma), _ptr(mu), max_order, flags,
+                                                          _ptr(corr), _ptr(cum), s))
     _check(st, "gbs_cumulants_displaced")
     return corr, cum
 
@@ -464,7 +495,14 @@ def gbs_pearson(x: torch.Tensor, y: torch.Tensor, r=None, flags: int = 0, stream
     _need(r, "r", 1)
     _same_device(("x", x), ("y", y), ("r", r))
     with torch.cuda.device(x.device):
-        st = lib().gbs_pearson(x.numel(), _ptr(x), _ptr(y), _ptr(r), flags, _stream(stream, x.device))
+        work = _scratch(lib().gbs_pearson_scratch(), stream, x.device)
+        if work is None:
+            st = lib().gbs_pearson(x.numel(), _ptr(x), _ptr(y), _ptr(r), flags,
+                                   _stream(stream, x.device))
+        else:
+            st = lib().gbs_pearson_in(x.numel(), _ptr(x), _ptr(y), _ptr(r),
+                                      ctypes.c_void_p(work.data_ptr()), work.numel(), flags,
+                                      _stream(stream, x.device))
     _check(st, "gbs_pearson")
     return r
 
@@ -480,9 +518,17 @@ def gbs_cumulant_grad(M: int, sigma: torch.Tensor, max_order: int, flags: int = 
     _sigma(M, grad_sigma, "grad_sigma")
     _same_device(("sigma", sigma), ("grad_corr", grad_corr), ("grad_cum", grad_cum),
                  ("grad_sigma", grad_sigma))
-    with torch.cuda.device(sigma.device):
-        st = lib().gbs_cumulant_grad(M, _ptr(sigma), max_order, flags, _ptr(grad_corr),
-                                     _ptr(grad_cum), _ptr(grad_sigma), _stream(stream, sigma.device))
+    dev = sigma.device
+    with torch.cuda.device(dev):
+        work = _scratch(lib().gbs_cumulant_grad_scratch(M, max_order), stream, dev)
+        if work is None:
+            st = lib().gbs_cumulant_grad(M, _ptr(sigma), max_order, flags, _ptr(grad_corr),
+                                         _ptr(grad_cum), _ptr(grad_sigma), _stream(stream, dev))
+        else:
+            st = lib().gbs_cumulant_grad_in(M, _ptr(sigma), max_order, flags, _ptr(grad_corr),
+                                            _ptr(grad_cum), _ptr(grad_sigma),
+                                            ctypes.c_void_p(work.data_ptr()), work.numel(),
+                                            _stream(stream, dev))
     _check(st, "gbs_cumulant_grad")
     return grad_sigma
 

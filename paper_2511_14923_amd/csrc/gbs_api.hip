@@ -236,19 +236,48 @@ gbs_status finish_status_device(const DeviceStatus* dev_status, int32_t flags, h
   return GBS_OK;
 }
 
-// Report the status, then release the call's stream-ordered scratch (the free
-// is queued after the status copy on the same stream).
-gbs_status finish_call(DeviceStatus* dev_status, void* scratch, int32_t flags, hipStream_t s) {
+// Scratch of one call: lent by the caller, or stream-ordered memory that is
+// released at the end of the call.
+struct CallScratch {
+  void* p = nullptr;
+  bool own = false;
+  hipError_t get(size_t bytes, void* lent, hipStream_t s) {
+    if (lent) {
+      p = lent;
+      return hipSuccess;
+    }
+    own = true;
+    return hipMallocAsync(&p, bytes, s);
+  }
+  hipError_t release(hipStream_t s) { return own ? hipFreeAsync(p, s) : hipSuccess; }
+};
+
+// Report the status, then release the call's scratch (the free is queued after
+// the status copy on the same stream).
+gbs_status finish_call(DeviceStatus* dev_status, CallScratch& scratch, int32_t flags, hipStream_t s) {
   gbs_status st = status_enqueue(dev_status, s);
-  hipError_t e = hipFreeAsync(scratch, s);
+  hipError_t e = scratch.release(s);
   if (st != GBS_OK) return st;
   if (e != hipSuccess) return to_status(e);
   return status_wait(flags, s);
 }
 
-// mu: device first moments (2M, xxpp) of a displaced state, or null.
+// Scratch bytes of a forward call: the operands, then the lower-order tables of
+// the recursive kernels (p always, m when corr is NULL).
+size_t forward_table_bytes(int32_t M, int32_t K, int32_t flags, bool has_corr) {
+  const size_t nlow = K >= 2 ? (size_t)gbs_order_offset(M, K) : 0;
+  return (flags & GBS_ALL_MINORS) ? 0 : align256(nlow * sizeof(double)) * (has_corr ? 1 : 2);
+}
+
+size_t forward_scratch(int32_t M, int32_t K, int32_t flags, bool displaced, bool has_corr) {
+  return layout_scratch(nullptr, M, (flags & GBS_MIXED) != 0, displaced).bytes +
+         forward_table_bytes(M, K, flags, has_corr);
+}
+
+// mu: device first moments (2M, xxpp) of a displaced state, or null.  lent:
+// forward_scratch bytes of the caller's, or null.
 gbs_status run_forward(int32_t M, const double* sigma, const double* mu, int32_t K, int32_t flags,
-                       double* corr, double* cum, void* stream) {
+                       double* corr, double* cum, void* lent, void* stream) {
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   hipError_t e;
   DeviceContext* ctx = current_context(&e);
@@ -256,14 +285,12 @@ gbs_status run_forward(int32_t M, const double* sigma, const double* mu, int32_t
   const bool mixed = (flags & GBS_MIXED) != 0;
   const bool rec = !(flags & GBS_ALL_MINORS);
   ForwardScratch probe = layout_scratch(nullptr, M, mixed, mu != nullptr);
-  // lower-order tables of the recursive kernel: p always, m when corr is NULL
   const size_t nlow = K >= 2 ? (size_t)gbs_order_offset(M, K) : 0;
-  const size_t tab_bytes = rec ? align256(nlow * sizeof(double)) * (corr ? 1 : 2) : 0;
-  void* scratch = nullptr;
-  e = hipMallocAsync(&scratch, probe.bytes + tab_bytes, s);
+  CallScratch scratch;
+  e = scratch.get(probe.bytes + forward_table_bytes(M, K, flags, corr != nullptr), lent, s);
   if (e != hipSuccess) return to_status(e);
-  ForwardScratch sc = layout_scratch(static_cast<char*>(scratch), M, mixed, mu != nullptr);
-  double* ptab = reinterpret_cast<double*>(static_cast<char*>(scratch) + probe.bytes);
+  ForwardScratch sc = layout_scratch(static_cast<char*>(scratch.p), M, mixed, mu != nullptr);
+  double* ptab = reinterpret_cast<double*>(static_cast<char*>(scratch.p) + probe.bytes);
   double* mtab = corr ? corr : ptab + align256(nlow * sizeof(double)) / sizeof(double);
   t_err.order = 0;
   t_err.rank = -1;
@@ -309,7 +336,7 @@ gbs_status run_forward(int32_t M, const double* sigma, const double* mu, int32_t
     if (e == hipSuccess) e = timing_end(s);
   }
   if (e != hipSuccess) {
-    (void)hipFreeAsync(scratch, s);
+    (void)scratch.release(s);
     return to_status(e);
   }
   return finish_call(sc.st, scratch, flags, s);
@@ -322,11 +349,11 @@ gbs_status run_shard(int32_t M, const double* sigma, int32_t d, int64_t rank0, i
   DeviceContext* ctx = current_context(&e);
   if (!ctx) return to_status(e);
   const size_t oQ = 0, oSt = align256(4 * (size_t)M * M * sizeof(double));
-  void* scratch = nullptr;
-  e = hipMallocAsync(&scratch, oSt + align256(sizeof(DeviceStatus)), s);
+  CallScratch scratch;
+  e = scratch.get(oSt + align256(sizeof(DeviceStatus)), nullptr, s);
   if (e != hipSuccess) return to_status(e);
-  double* Qi = reinterpret_cast<double*>(static_cast<char*>(scratch) + oQ);
-  DeviceStatus* st = reinterpret_cast<DeviceStatus*>(static_cast<char*>(scratch) + oSt);
+  double* Qi = reinterpret_cast<double*>(static_cast<char*>(scratch.p) + oQ);
+  DeviceStatus* st = reinterpret_cast<DeviceStatus*>(static_cast<char*>(scratch.p) + oSt);
   t_err.order = 0;
   t_err.rank = -1;
   timing_start_call((flags & GBS_TIMING) != 0);
@@ -343,45 +370,54 @@ gbs_status run_shard(int32_t M, const double* sigma, int32_t d, int64_t rank0, i
                              cum, st, s);
   if (e == hipSuccess) e = timing_end(s);
   if (e != hipSuccess) {
-    (void)hipFreeAsync(scratch, s);
+    (void)scratch.release(s);
     return to_status(e);
   }
   return finish_call(st, scratch, flags, s);
 }
 
+struct AdjointScratch {
+  size_t Q, Qd, p, m, d1, mbar, pbar, st, part, sup, diag, bytes;
+  static AdjointScratch make(int32_t M, int32_t K) {
+    const size_t N = (size_t)gbs_total_outputs(M, K) * sizeof(double);
+    AdjointScratch S{};
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+      const size_t at = off;
+      off += align256(bytes);
+      return at;
+    };
+    S.Q = take(4 * (size_t)M * M * sizeof(double));
+    S.Qd = take(4 * (size_t)M * sizeof(double));
+    S.p = take(N);
+    S.m = take(N);
+    S.d1 = take(N);
+    S.mbar = take(N);
+    S.pbar = take(N);
+    S.st = take(sizeof(DeviceStatus));
+    S.part = take(kAdjointPartDoubles * sizeof(double));
+    S.sup = take(adjoint_sup_doubles(M, K) * sizeof(double));
+    S.diag = take(3 * (size_t)M * M * sizeof(double));
+    S.bytes = off;
+    return S;
+  }
+};
+
 gbs_status run_adjoint(int32_t M, const double* sigma, int32_t K, int32_t flags,
-                       const double* gm, const double* gk, double* gsig, void* stream) {
+                       const double* gm, const double* gk, double* gsig, void* lent, void* stream) {
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   hipError_t e;
   DeviceContext* ctx = current_context(&e);
   if (!ctx) return to_status(e);
-  const size_t N = (size_t)gbs_total_outputs(M, K);
-  const size_t nq = 4 * (size_t)M * M;
-  size_t off = 0;
-  const size_t oQ = off; off += align256(nq * sizeof(double));
-  const size_t oQd = off; off += align256(4 * (size_t)M * sizeof(double));
-  const size_t oP = off; off += align256(N * sizeof(double));
-  const size_t oM = off; off += align256(N * sizeof(double));
-  const size_t oD = off; off += align256(N * sizeof(double));
-  const size_t oMb = off; off += align256(N * sizeof(double));
-  const size_t oPb = off; off += align256(N * sizeof(double));
-  const size_t oSt = off; off += align256(sizeof(DeviceStatus));
-  const size_t oPart = off; off += align256(kAdjointPartDoubles * sizeof(double));
-  const size_t oSup = off; off += align256(adjoint_sup_doubles(M, K) * sizeof(double));
-  const size_t oDiag = off; off += align256(3 * (size_t)M * M * sizeof(double));
-  void* scratch = nullptr;
-  e = hipMallocAsync(&scratch, off, s);
+  const AdjointScratch S = AdjointScratch::make(M, K);
+  CallScratch scratch;
+  e = scratch.get(S.bytes, lent, s);
   if (e != hipSuccess) return to_status(e);
-  char* b = static_cast<char*>(scratch);
-  double* Qi = reinterpret_cast<double*>(b + oQ);
-  double* Qd = reinterpret_cast<double*>(b + oQd);
-  double* ptab = reinterpret_cast<double*>(b + oP);
-  double* part = reinterpret_cast<double*>(b + oPart);
-  double* m = reinterpret_cast<double*>(b + oM);
-  double* d1 = reinterpret_cast<double*>(b + oD);
-  double* mbar = reinterpret_cast<double*>(b + oMb);
-  double* pbar = reinterpret_cast<double*>(b + oPb);
-  DeviceStatus* st = reinterpret_cast<DeviceStatus*>(b + oSt);
+  char* b = static_cast<char*>(scratch.p);
+  auto at = [&](size_t off) { return reinterpret_cast<double*>(b + off); };
+  double *Qi = at(S.Q), *Qd = at(S.Qd), *ptab = at(S.p), *part = at(S.part), *m = at(S.m), *d1 = at(S.d1),
+         *mbar = at(S.mbar), *pbar = at(S.pbar);
+  DeviceStatus* st = reinterpret_cast<DeviceStatus*>(b + S.st);
   t_err.order = 0;
   t_err.rank = -1;
   timing_start_call((flags & GBS_TIMING) != 0);
@@ -408,9 +444,9 @@ gbs_status run_adjoint(int32_t M, const double* sigma, int32_t K, int32_t flags,
   }
   if (e == hipSuccess)
     e = launch_adjoint(M, K, flags, Qi, Qd, ctx->binom, m, ptab, gm, gk, d1, mbar, pbar, gsig, st, part,
-                       reinterpret_cast<double*>(b + oSup), reinterpret_cast<double*>(b + oDiag), s);
+                       at(S.sup), at(S.diag), s);
   if (e != hipSuccess) {
-    (void)hipFreeAsync(scratch, s);
+    (void)scratch.release(s);
     return to_status(e);
   }
   return finish_call(st, scratch, flags, s);
@@ -479,13 +515,13 @@ gbs_status gbs_colex_unrank(int32_t d, int64_t r, int32_t* S) {
 gbs_status gbs_correlators(int32_t M, const double* sigma, int32_t max_order, int32_t flags,
                            double* corr, void* stream) {
   if (!valid_problem(M, max_order, flags) || !sigma || !corr) return GBS_E_INVALID_ARG;
-  return run_forward(M, sigma, nullptr, max_order, flags, corr, nullptr, stream);
+  return run_forward(M, sigma, nullptr, max_order, flags, corr, nullptr, nullptr, stream);
 }
 
 gbs_status gbs_cumulants(int32_t M, const double* sigma, int32_t max_order, int32_t flags,
                          double* corr, double* cum, void* stream) {
   if (!valid_problem(M, max_order, flags) || !sigma || !cum) return GBS_E_INVALID_ARG;
-  return run_forward(M, sigma, nullptr, max_order, flags, corr, cum, stream);
+  return run_forward(M, sigma, nullptr, max_order, flags, corr, cum, nullptr, stream);
 }
 
 gbs_status gbs_cumulants_displaced(int32_t M, const double* sigma, const double* mu,
@@ -493,7 +529,25 @@ gbs_status gbs_cumulants_displaced(int32_t M, const double* sigma, const double*
                                    void* stream) {
   if (!valid_problem(M, max_order, flags) || !sigma || !mu || !cum) return GBS_E_INVALID_ARG;
   if (flags & GBS_MIXED) return GBS_E_UNSUPPORTED;
-  return run_forward(M, sigma, mu, max_order, flags, corr, cum, stream);
+  return run_forward(M, sigma, mu, max_order, flags, corr, cum, nullptr, stream);
+}
+
+int64_t gbs_cumulants_scratch(int32_t M, int32_t max_order, int32_t flags, int32_t displaced,
+                              int32_t has_corr) {
+  if (!valid_problem(M, max_order, flags) || (displaced && (flags & GBS_MIXED))) return -1;
+  return (int64_t)forward_scratch(M, max_order, flags, displaced != 0, has_corr != 0);
+}
+
+gbs_status gbs_cumulants_in(int32_t M, const double* sigma, const double* mu, int32_t max_order,
+                            int32_t flags, double* corr, double* cum, void* scratch,
+                            int64_t scratch_bytes, void* stream) {
+  if (!valid_problem(M, max_order, flags) || !sigma || (!corr && !cum) || !scratch)
+    return GBS_E_INVALID_ARG;
+  if (mu && (flags & GBS_MIXED)) return GBS_E_UNSUPPORTED;
+  if (scratch_bytes < 0 ||
+      (size_t)scratch_bytes < forward_scratch(M, max_order, flags, mu != nullptr, corr != nullptr))
+    return GBS_E_OUT_OF_MEMORY;
+  return run_forward(M, sigma, mu, max_order, flags, corr, cum, scratch, stream);
 }
 
 gbs_status gbs_cumulants_shard(int32_t M, const double* sigma, int32_t order, int64_t rank0,
@@ -511,7 +565,22 @@ gbs_status gbs_cumulant_grad(int32_t M, const double* sigma, int32_t max_order, 
                              void* stream) {
   if (!valid_problem(M, max_order, flags) || !sigma || !grad_sigma) return GBS_E_INVALID_ARG;
   if (flags & GBS_MIXED) return GBS_E_UNSUPPORTED;
-  return run_adjoint(M, sigma, max_order, flags, grad_corr, grad_cum, grad_sigma, stream);
+  return run_adjoint(M, sigma, max_order, flags, grad_corr, grad_cum, grad_sigma, nullptr, stream);
+}
+
+int64_t gbs_cumulant_grad_scratch(int32_t M, int32_t max_order) {
+  return valid_problem(M, max_order, 0) ? (int64_t)AdjointScratch::make(M, max_order).bytes : -1;
+}
+
+gbs_status gbs_cumulant_grad_in(int32_t M, const double* sigma, int32_t max_order, int32_t flags,
+                                const double* grad_corr, const double* grad_cum,
+                                double* grad_sigma, void* scratch, int64_t scratch_bytes,
+                                void* stream) {
+  if (!valid_problem(M, max_order, flags) || !sigma || !grad_sigma || !scratch) return GBS_E_INVALID_ARG;
+  if (flags & GBS_MIXED) return GBS_E_UNSUPPORTED;
+  if (scratch_bytes < 0 || (size_t)scratch_bytes < AdjointScratch::make(M, max_order).bytes)
+    return GBS_E_OUT_OF_MEMORY;
+  return run_adjoint(M, sigma, max_order, flags, grad_corr, grad_cum, grad_sigma, scratch, stream);
 }
 
 // Argument checks of the sampler; GBS_OK for a valid call.
@@ -613,18 +682,33 @@ gbs_status gbs_sample_cumulants_in(int32_t M, int64_t nsamples, const uint8_t* b
   return estimate_call(M, nsamples, bits, max_order, cum, scratch, flags, stream);
 }
 
-gbs_status gbs_pearson(int64_t n, const double* x, const double* y, double* r, int32_t flags,
-                       void* stream) {
-  if (n < 2 || !x || !y || !r) return GBS_E_INVALID_ARG;
-  if (flags & ~(GBS_ASYNC | GBS_TIMING)) return GBS_E_INVALID_ARG;
+static gbs_status pearson_call(int64_t n, const double* x, const double* y, double* r, void* lent,
+                               int32_t flags, void* stream) {
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   timing_start_call((flags & GBS_TIMING) != 0);
   hipError_t e = timing_begin(s, GBS_STAGE_ESTIMATE, 0);
-  if (e == hipSuccess) e = run_pearson((uint64_t)n, x, y, r, s);
+  if (e == hipSuccess) e = run_pearson((uint64_t)n, x, y, r, lent, s);
   if (e == hipSuccess) e = timing_end(s);
   if (e != hipSuccess) return to_status(e);
   if (flags & GBS_ASYNC) return GBS_OK;
   return to_status(hipStreamSynchronize(s));
+}
+
+gbs_status gbs_pearson(int64_t n, const double* x, const double* y, double* r, int32_t flags,
+                       void* stream) {
+  if (n < 2 || !x || !y || !r) return GBS_E_INVALID_ARG;
+  if (flags & ~(GBS_ASYNC | GBS_TIMING)) return GBS_E_INVALID_ARG;
+  return pearson_call(n, x, y, r, nullptr, flags, stream);
+}
+
+int64_t gbs_pearson_scratch(void) { return (int64_t)pearson_scratch(); }
+
+gbs_status gbs_pearson_in(int64_t n, const double* x, const double* y, double* r, void* scratch,
+                          int64_t scratch_bytes, int32_t flags, void* stream) {
+  if (n < 2 || !x || !y || !r || !scratch) return GBS_E_INVALID_ARG;
+  if (flags & ~(GBS_ASYNC | GBS_TIMING)) return GBS_E_INVALID_ARG;
+  if (scratch_bytes < 0 || (size_t)scratch_bytes < pearson_scratch()) return GBS_E_OUT_OF_MEMORY;
+  return pearson_call(n, x, y, r, scratch, flags, stream);
 }
 
 gbs_status gbs_last_error(int32_t* order, int64_t* rank) {

@@ -543,6 +543,7 @@ __device__ __forceinline__ void pearson_sums(const double* __restrict__ x, const
 // second launch costs more than the one compute unit's bandwidth.
 constexpr int kPearsonThreads = 1024;
 constexpr uint64_t kPearsonOne = 16384;
+constexpr uint64_t kPearsonBlocks = 1024;  // partial sums of the two-pass kernels
 __global__ __launch_bounds__(kPearsonThreads) void pearson_one_kernel(const double* __restrict__ x,
                                                                       const double* __restrict__ y, uint64_t n,
                                                                       double* __restrict__ r) {
@@ -781,21 +782,24 @@ hipError_t run_sample_cumulants(int M, int64_t N, const uint8_t* bits, int K,
   return e != hipSuccess ? e : f;
 }
 
-hipError_t run_pearson(uint64_t n, const double* x, const double* y, double* r, hipStream_t s) {
+size_t pearson_scratch() { return 5 * (size_t)kPearsonBlocks * sizeof(double); }
+
+hipError_t run_pearson(uint64_t n, const double* x, const double* y, double* r, void* lent, hipStream_t s) {
   if (n <= kPearsonOne) {
     hipLaunchKernelGGL(pearson_one_kernel, dim3(1), dim3(kPearsonThreads), 0, s, x, y, n, r);
     return hipGetLastError();
   }
-  const int nblk = (int)std::min<uint64_t>((n + kEstThreads - 1) / kEstThreads, 1024);
-  void* scratch = nullptr;
-  hipError_t e = hipMallocAsync(&scratch, (size_t)(5 * nblk) * sizeof(double), s);
+  const int nblk = (int)std::min<uint64_t>((n + kEstThreads - 1) / kEstThreads, kPearsonBlocks);
+  void* scratch = lent;
+  hipError_t e = hipSuccess;
+  if (!lent) e = hipMallocAsync(&scratch, pearson_scratch(), s);
   if (e != hipSuccess) return e;
   double* part = static_cast<double*>(scratch);
   hipLaunchKernelGGL(pearson_means_kernel, dim3(nblk), dim3(kEstThreads), 0, s, x, y, n, part);
   hipLaunchKernelGGL(pearson_centred_kernel, dim3(nblk), dim3(kEstThreads), 0, s, x, y, n, part);
   hipLaunchKernelGGL(pearson_finish_kernel, dim3(1), dim3(kEstThreads), 0, s, part, nblk, r);
   e = hipGetLastError();
-  hipError_t f = hipFreeAsync(scratch, s);
+  hipError_t f = lent ? hipSuccess : hipFreeAsync(scratch, s);
   return e != hipSuccess ? e : f;
 }
 

@@ -203,6 +203,7 @@ hipError_t run_sampler(int M, int K, const double* kap, int64_t nsamples, const 
 size_t estimator_scratch(int M, int64_t N, int K);
 hipError_t run_sample_cumulants(int M, int64_t N, const uint8_t* bits, int K,
                                 const uint64_t* binom, double* out, void* lent, hipStream_t s);
-hipError_t run_pearson(uint64_t n, const double* x, const double* y, double* r, hipStream_t s);
+size_t pearson_scratch();
+hipError_t run_pearson(uint64_t n, const double* x, const double* y, double* r, void* lent, hipStream_t s);
 
 }  // namespace gbs
