@@ -287,8 +287,9 @@ typedef struct {
  * Many instances of uneven M in persistent launches over device work lists
  * (plus the launches that form every instance's Q): one launch over
  * (instance, order, rank range) items evaluated from all the principal minors
- * of Q_S (orders 1 and 2; every order with GBS_ALL_MINORS, and for instances
- * the group kernel does not take), then one launch per order 3..max_order over
+ * of Q_S (every order with GBS_ALL_MINORS, and for instances the group kernel
+ * does not take; orders 1 and 2 in the mixed form), or one launch over the pairs
+ * (orders 1 and 2 in FP64), then one launch per order 3..max_order over
  * the (instance, tile) items of the group kernel (FP64 or GBS_MIXED), which
  * reads each instance's lower-order tables.  FP64 results agree with n separate
  * gbs_cumulants calls (same flags) to FP64 rounding; mixed-form results agree

@@ -4,9 +4,10 @@
 // Orders 3..K, FP64 or mixed: the group kernel (gbs_forward_group.hip), one
 // persistent launch per order whose work list holds the (instance, tile) items
 // of every instance at that order; each instance reads the tables of its own
-// lower orders, which the previous launches wrote.  Orders 1 and 2, instances
-// the group kernel does not take (M too large) and GBS_ALL_MINORS:
-// one persistent launch over (instance, order, rank range) items, longest
+// lower orders, which the previous launches wrote.  Orders 1 and 2 of those
+// instances in FP64: one launch, a thread per pair.  Orders 1 and 2 in the mixed
+// form, instances the group kernel does not take (M too large) and
+// GBS_ALL_MINORS: one persistent launch over (instance, order, rank range) items, longest
 // first, each subset evaluated from all its minors (no tables needed), which
 // also stores the tables the group launches read.  In every launch a fixed grid
 // of workgroups claims items with one atomic counter until the list is
@@ -14,8 +15,8 @@
 // per-instance launches or tail effects; every workgroup leaves its loop when
 // the counter passes the end of the list, and no workgroup waits on another.
 //
-// The pipeline (counter and status reset, Q of every instance, diagonal blocks
-// or normalisation, the persistent launches) is captured once into a HIP graph
+// The pipeline (counter and status reset with Q of every instance and its diagonal
+// blocks, normalisation, the other launches) is captured once into a HIP graph
 // per instance list and replayed; the launch shapes come from the autotuner's
 // cache (the group launches fill the device unless it caps their workgroups
 // per compute unit).
@@ -62,14 +63,16 @@ namespace {
 // one counter per persistent launch: [0] all-minors items, [d] group items of order d
 constexpr int kCounters = kMaxOrder + 1;
 
-__global__ void reset_batch_kernel(unsigned* counter, DeviceStatus* st) {
-  for (int i = 0; i < kCounters; ++i) counter[i] = 0u;
-  st->flag = 0;
-  st->order = 0;
-  st->rank = -1;
-}
-
-__global__ void build_q_batched_kernel(const BatchInstance* __restrict__ inst) {
+// Counters and status reset, Q and (where asked for) its diagonal blocks of every
+// instance, in one launch.
+__global__ void prepare_batched_kernel(const BatchInstance* __restrict__ inst, unsigned* __restrict__ counter,
+                                       DeviceStatus* __restrict__ st) {
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+    for (int i = 0; i < kCounters; ++i) counter[i] = 0u;
+    st->flag = 0;
+    st->order = 0;
+    st->rank = -1;
+  }
   const BatchInstance I = inst[blockIdx.y];
   const int n = 2 * I.M;
   const size_t total = (size_t)n * n;
@@ -78,21 +81,25 @@ __global__ void build_q_batched_kernel(const BatchInstance* __restrict__ inst) {
     const int row = (int)(idx / n), col = (int)(idx - (size_t)row * n);
     const int sr = (row >> 1) + (row & 1) * I.M;
     const int sc = (col >> 1) + (col & 1) * I.M;
-    const double v = (sr >= sc) ? I.sigma[(size_t)sr * n + sc] : I.sigma[(size_t)sc * n + sr];
-    I.Qi[idx] = v + (row == col ? 0.5 : 0.0);
+    double v = (sr >= sc) ? I.sigma[(size_t)sr * n + sc] : I.sigma[(size_t)sc * n + sr];
+    v += row == col ? 0.5 : 0.0;
+    I.Qi[idx] = v;
+    if (I.Qd && (row >> 1) == (col >> 1))  // x-x, p-x, p-p, 0 per mode
+      I.Qd[2 * (size_t)(row & ~1) + (row >= col ? (row & 1) + (col & 1) : 3)] = row >= col ? v : 0.0;
   }
 }
 
-__global__ void build_qdiag_batched_kernel(const BatchInstance* __restrict__ inst) {
-  const BatchInstance I = inst[blockIdx.y];
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (!I.Qd || k >= I.M) return;
-  const size_t ldq = 2 * (size_t)I.M;
-  const double* q = I.Qi + (size_t)(2 * k) * ldq + 2 * k;
-  I.Qd[4 * (size_t)k + 0] = q[0];
-  I.Qd[4 * (size_t)k + 1] = q[ldq];
-  I.Qd[4 * (size_t)k + 2] = q[ldq + 1];
-  I.Qd[4 * (size_t)k + 3] = 0.0;
+// Orders 1 and 2 of the instances that the group launches take, FP64: one thread
+// per pair (a workgroup of the all-minors list took a whole instance's pairs:
+// 148 us for 48 instances of 40 to 144 modes).
+template <int CONV>
+__global__ __launch_bounds__(256) void pairs_batched_kernel(const BatchInstance* __restrict__ inst,
+                                                            DeviceStatus* __restrict__ st) {
+  const BatchInstance& I = inst[blockIdx.y];
+  if (!I.ptab) return;
+  const uint32_t pairs = (uint32_t)I.M * (uint32_t)(I.M - 1) / 2, r = blockIdx.x * 256 + threadIdx.x;
+  const PairOutputs o{{I.mtab, I.mtab + I.off[2]}, {I.cum, I.cum + I.off[2]}, {I.ptab, I.ptab + I.off[2]}};
+  pair_outputs<CONV>(I.Qi, I.Qd, I.M, r, pairs, o, st);
 }
 
 __global__ void build_normalised_batched_kernel(const BatchInstance* __restrict__ inst) {
@@ -256,6 +263,7 @@ struct BatchPlan {
   int max_M = 0;
   int n = 0;
   bool any_group = false;
+  bool any_pairs = false;  // orders 1 and 2 of the group instances by the pairs launch (FP64)
   // group launches, order d = 3..K
   GroupBatchInstance* d_ginst[kMaxOrder + 1] = {};
   GroupBatchItem* d_gitems[kMaxOrder + 1] = {};
@@ -321,19 +329,11 @@ double item_cost(const WorkItem& w) {
 
 hipError_t launch_pipeline(const BatchPlan& p, hipStream_t s, bool timed) {
   hipError_t e = hipSuccess;
-  hipLaunchKernelGGL(reset_batch_kernel, dim3(1), dim3(1), 0, s, p.d_counter, p.d_status);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
   const int bx = std::min(4096, (4 * p.max_M * p.max_M + 255) / 256);
   if (timed) e = timing_begin(s, GBS_STAGE_BUILD_Q, 0);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(build_q_batched_kernel, dim3(bx, p.n), dim3(256), 0, s, p.d_inst);
+  hipLaunchKernelGGL(prepare_batched_kernel, dim3(bx, p.n), dim3(256), 0, s, p.d_inst, p.d_counter, p.d_status);
   e = hipGetLastError();
-  if (e == hipSuccess && p.any_group) {
-    hipLaunchKernelGGL(build_qdiag_batched_kernel, dim3((p.max_M + 255) / 256, p.n), dim3(256), 0,
-                       s, p.d_inst);
-    e = hipGetLastError();
-  }
   if (e == hipSuccess && timed) e = timing_end(s);
   if (e == hipSuccess && (p.flags & GBS_MIXED)) {
     if (timed) e = timing_begin(s, GBS_STAGE_NORMALISE, 0);
@@ -347,6 +347,18 @@ hipError_t launch_pipeline(const BatchPlan& p, hipStream_t s, bool timed) {
   hipError_t ec;
   DeviceContext* ctx = current_context(&ec);
   if (!ctx) return ec;
+  if (p.any_pairs) {
+    if (timed) e = timing_begin(s, GBS_STAGE_BATCHED, p.n_items > 0 ? 2 : 0);
+    if (e != hipSuccess) return e;
+    const dim3 grid((unsigned)((host_binom(p.max_M, 2) + 255) / 256), (unsigned)p.n);
+    if (p.flags & GBS_PARITY)
+      hipLaunchKernelGGL(pairs_batched_kernel<GBS_PARITY>, grid, dim3(256), 0, s, p.d_inst, p.d_status);
+    else
+      hipLaunchKernelGGL(pairs_batched_kernel<GBS_CLICK>, grid, dim3(256), 0, s, p.d_inst, p.d_status);
+    e = hipGetLastError();
+    if (e == hipSuccess && timed) e = timing_end(s);
+    if (e != hipSuccess) return e;
+  }
   if (p.n_items > 0) {
     const int grid = std::max(1, ctx->cu_count * p.tuning.waves_per_cu);
     BatchedFn fn = pick_kernel(p.K, p.tuning.unroll, p.flags);
@@ -392,6 +404,7 @@ gbs_status build_plan(BatchPlan* p, int n, const gbs_instance* inst, int K, int 
   std::vector<bool> grp(n, false);
   p->max_M = 0;
   p->any_group = false;
+  p->any_pairs = false;
   // group items, largest instances first
   std::vector<int> by_M(n);
   for (int i = 0; i < n; ++i) by_M[i] = i;
@@ -439,8 +452,9 @@ gbs_status build_plan(BatchPlan* p, int n, const gbs_instance* inst, int K, int 
         bytes += a256((size_t)b.off[K] * sizeof(double));
       }
     }
+    p->any_pairs = p->any_pairs || (grp[i] && !mixed);
     for (int d = 1; d <= K; ++d) {
-      if (grp[i] && group_order(d, M, flags)) continue;
+      if (grp[i] && (group_order(d, M, flags) || (d <= 2 && !mixed))) continue;
       const uint64_t cnt = host_binom(M, d);
       for (uint64_t b0 = 0; b0 < cnt; b0 += (uint64_t)t.tile)
         items.push_back(WorkItem{i, d, b0, std::min<uint64_t>(cnt, b0 + (uint64_t)t.tile)});

@@ -315,4 +315,62 @@ __device__ __forceinline__ void stream_at(double* __restrict__ base, uint32_t id
   __builtin_nontemporal_store(v, reinterpret_cast<double*>(reinterpret_cast<char*>(base) + (idx << 3)));
 }
 
+// Where orders 1 and 2 go (each pointer may be null).
+struct PairOutputs {
+  double* m[2];
+  double* k[2];
+  double* p[2];
+};
+
+// Orders 1 and 2 of a zero-mean state in FP64: thread r takes the pair (a < b) of
+// colex rank r, forming p({a}) and p({b}) itself, and below M also mode r.
+template <int CONV>
+__device__ __forceinline__ void pair_outputs(const double* __restrict__ Qi, const double* __restrict__ Qd, int M,
+                                             uint32_t r, uint32_t pairs, const PairOutputs& o,
+                                             DeviceStatus* __restrict__ st) {
+  auto single = [&](int k, double& a00, double& a10, double& a11, double& det, double& p, double& m) -> bool {
+    const double2 d0 = *reinterpret_cast<const double2*>(Qd + 4 * (size_t)k);
+    a00 = d0.x;
+    a10 = d0.y;
+    a11 = Qd[4 * (size_t)k + 2];
+    det = fma(a00, a11, -a10 * a10);
+    p = rsqrt_f64(det);
+    m = (CONV == GBS_CLICK) ? 1.0 - p : fma(2.0, p, -1.0);
+    return a00 > 0.0 && det > 0.0 && det < INFINITY;
+  };
+  if (r < (uint32_t)M) {
+    double a00, a10, a11, det, p, m;
+    if (!single((int)r, a00, a10, a11, det, p, m)) latch_failure(st, 1, r);
+    if (o.m[0]) o.m[0][r] = m;
+    if (o.k[0]) o.k[0][r] = m;
+    if (o.p[0]) o.p[0][r] = p;
+  }
+  if (r >= pairs) return;
+  int b = (int)(0.5f * (1.0f + sqrtf(fmaf(8.0f, (float)r, 1.0f))));  // largest b with C(b, 2) <= r
+  while ((uint32_t)b * (uint32_t)(b - 1) / 2 > r) --b;
+  while ((uint32_t)b * (uint32_t)(b + 1) / 2 <= r) ++b;
+  const int a = (int)(r - (uint32_t)b * (uint32_t)(b - 1) / 2);
+  double a00, a10, a11, deta, pa, ma, b00, b10, b11, detb, pb, mb;
+  const bool oka = single(a, a00, a10, a11, deta, pa, ma), okb = single(b, b00, b10, b11, detb, pb, mb);
+  const size_t ldq = 2 * (size_t)M;
+  // G: rows of b, columns of a
+  const double2 g0 = *reinterpret_cast<const double2*>(Qi + (size_t)(2 * b) * ldq + 2 * a);
+  const double2 g1 = *reinterpret_cast<const double2*>(Qi + (size_t)(2 * b + 1) * ldq + 2 * a);
+  // Schur complement of b: A_a - G^T A_b^{-1} G
+  const double ib = 1.0 / detb;
+  const double t00 = fma(b11, g0.x, -b10 * g1.x), t01 = fma(b11, g0.y, -b10 * g1.y);
+  const double t10 = fma(b00, g1.x, -b10 * g0.x), t11 = fma(b00, g1.y, -b10 * g0.y);
+  const double s00 = fma(-ib, fma(g0.x, t00, g1.x * t10), a00);
+  const double s10 = fma(-ib, fma(g0.y, t00, g1.y * t10), a10);
+  const double s11 = fma(-ib, fma(g0.y, t01, g1.y * t11), a11);
+  const double det = fma(s00, s11, -s10 * s10);
+  // a mode that is bad by itself is reported as order 1
+  if (oka && okb && !(s00 > 0.0 && det > 0.0 && det < INFINITY)) latch_failure(st, 2, r);
+  const double pab = pb * rsqrt_f64(det);
+  const double m = (CONV == GBS_CLICK) ? mb - (pa - pab) : fma(-2.0, fma(-2.0, pab, pa), -mb);
+  if (o.m[1]) o.m[1][r] = m;
+  if (o.p[1]) o.p[1][r] = pab;
+  if (o.k[1]) o.k[1][r] = fma(-mb, ma, m);
+}
+
 }  // namespace gbs
