@@ -353,8 +353,8 @@ __global__ __launch_bounds__(256) void update_kernel(StepArgs A, uint32_t nsb, u
   const uint32_t per = nruns + (uint32_t)(n - 1);
   const uint32_t item = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (item >= per * nsb) return;
-  const uint32_t it = item % per;
-  double* blk = block_of(A, item / per) + lane;
+  const uint32_t it = item / nsb;  // the longest sums first
+  double* blk = block_of(A, item % nsb) + lane;
   const double* q = blk + (uint64_t)A.st.q[n & 1] * kSB;
   const double chi = blk[(uint64_t)(A.st.chi + (uint32_t)n) * kSB];
   const double h = blk[(uint64_t)A.st.h * kSB];

@@ -120,8 +120,8 @@ __global__ __launch_bounds__(256) void partial_kernel(StepArgs A, uint32_t nsb, 
   const int n = A.n;
   const uint32_t item = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (item >= runs * nsb) return;
-  const int l0 = 1 + (int)(item % runs) * kRun;
-  double* blk = block_of(A, item / runs) + lane;
+  const int l0 = 1 + (int)(item / nsb) * kRun;  // the longest sums first
+  double* blk = block_of(A, item % nsb) + lane;
   const double* q = blk + (uint64_t)A.st.q[n & 1] * kSB;
   const double* k2 = A.kap + A.ko.off[2] + samp_r2(n) - 1;
   double* PP = blk + (uint64_t)(A.st.PP + (uint32_t)l0 - 1) * kSB;  // p+(j-1, l0 + r) at C(j-1, 2) + l0 - 1 + r
@@ -165,8 +165,8 @@ template <bool FULL>
 __device__ __forceinline__ void update_item(const StepArgs& A, uint32_t item, uint32_t nsb, uint32_t runs, int lane) {
   const int n = A.n;
   if (item >= runs * nsb) return;
-  const int e0 = 1 + (int)(item % runs) * kRun;
-  double* blk = block_of(A, item / runs) + lane;
+  const int e0 = 1 + (int)(item / nsb) * kRun;
+  double* blk = block_of(A, item % nsb) + lane;
   const double* q = blk + (uint64_t)A.st.q[n & 1] * kSB;
   const double* k2 = A.kap + A.ko.off[2] + samp_r2(n) - 1;
   double* V = blk + (uint64_t)(A.st.V + (uint32_t)e0 - 1) * kSB;  // V(i; e0 + r) at C(i-1, 2) + e0 - 1 + r
