@@ -35,7 +35,7 @@
 // entries once in all; the U update reads C(n - 1, 3) entries at step n, C(M, 4)
 // in all, halved by taking two steps in a pass (update_kernel), and is bound by
 // memory bandwidth (4.8 TB/s; a large copy reaches 4.6).
-// M = 100, 4,096 samples: 45.4 ms (21 of them U updates, 17 products over pairs,
+// M = 100, 4,096 samples: 44.6 ms (21 of them U updates, 17 products over pairs,
 // 7 products over j) against 1,090 ms of one workgroup per 64 samples, which
 // reads every U entry several times per bit.
 //
@@ -239,6 +239,7 @@ __global__ __launch_bounds__(256 * KS) void product_kernel(StepArgs A, int rows,
 // index): 16 rows x 64 samples per workgroup, the chunks of the inner index
 // dealt to the waves, whose partial tiles are added in wave order.
 constexpr int kSlimWaves = 8;
+constexpr uint32_t kSlimRows = 128;
 __global__ __launch_bounds__(64 * kSlimWaves) void product_slim_kernel(StepArgs A, int rows, int row_blocks,
                                                                        uint32_t nprod, uint32_t nsb) {
   __shared__ double part[kSlimWaves][16][kSB];
@@ -462,10 +463,14 @@ hipError_t launch_double_sampler(int M, const double* kap, KapOffsets ko, int64_
       // Which kernel and how the inner index is split follow from the rows alone,
       // so that a sample's sums do not depend on the batch it is in.  Two parts
       // per tile: 47.2 ms at M = 100, 4,096 samples and 8.3 ms at M = 90, 200,
-      // against 48.4 and 9.6 ms in one part, 50.1 and 8.0 ms in four.
+      // against 48.4 and 9.6 ms in one part, 50.1 and 8.0 ms in four.  Up to
+      // kSlimRows rows the slim kernel: two 64-row tiles a block of samples leave
+      // units idle, each with a long serial inner index.  Slim up to 16 / 64 / 128 /
+      // 256 rows: 7.8 / 7.4 / 7.0 / 6.6 ms at M = 90, 200 samples; 100.1 / 99.3 /
+      // 98.4 / 98.2 at M = 144, 2,048; 44.8 / 44.4 / 44.5 / 44.9 at M = 100, 4,096.
       const uint32_t rows = n >= 3 ? 1 + 2 * m + samp_c2(m) : 0;
-      if (rows <= 16) {
-        const uint32_t rb = rows ? 1 : 0;
+      if (rows <= kSlimRows) {
+        const uint32_t rb = (rows + 15) / 16;
         const uint32_t extra = ((uint32_t)(M - 1) * nsb + kSlimWaves - 1) / kSlimWaves;
         hipLaunchKernelGGL(product_slim_kernel, dim3(rb * nsb + extra), dim3(64 * kSlimWaves), 0, s, A, (int)rows,
                            (int)rb, rb * nsb, nsb);

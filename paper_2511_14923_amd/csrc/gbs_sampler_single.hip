@@ -15,7 +15,7 @@
 // entries each at step n, bound by memory bandwidth.  The sum of the V update of
 // step n + 1 over i < n needs only q of step n + 1, which is known after bit n and
 // p+ of top n, so every other step takes the V sums of two steps in one pass.
-// M = 144, 65,536 samples: 110 ms, 6 MB of table reads per sample at 4 TB/s,
+// M = 144, 65,536 samples: 97.5 ms, 6 MB of table reads per sample at 4 TB/s,
 // against 325 ms of one workgroup per 64 samples that read 20 MB per sample.
 //
 // Storage as in gbs_sampler_double.hip: blocks of 64 samples, entry-major.
