@@ -31,7 +31,7 @@ struct KapOffsets {
 
 // Double elision step by step (gbs_sampler_double.hip): bytes of tables per
 // sample (a multiple of 64 samples is stored), and the launches of one batch of
-// nsamp samples on tables tab.  u, cond: row stride ldu.
+// nsamp samples on tables tab.  u, cond: row stride ldu, the samples of the whole call.
 size_t double_sampler_bytes(int M);
 hipError_t launch_double_sampler(int M, const double* kap, KapOffsets ko, int64_t nsamp, const double* u,
                                  uint64_t ldu, double* tab, uint8_t* bits, double* prob, double* cond,

@@ -112,25 +112,39 @@ __global__ __launch_bounds__(256) void bit_kernel(StepArgs A, const double* __re
   }
 }
 
-// p+(x_n..x_l) for kRun consecutive l per wave, and from it q of step n + 1.
-// Eight entries of a top are 4 KB in one piece.
-constexpr int kRun = 8;
-__global__ __launch_bounds__(256) void partial_kernel(StepArgs A, uint32_t nsb, uint32_t runs) {
-  const int lane = threadIdx.x & 63;
-  const int n = A.n;
-  const uint32_t item = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (item >= runs * nsb) return;
-  const int l0 = 1 + (int)(item / nsb) * kRun;  // the longest sums first
-  double* blk = block_of(A, item % nsb) + lane;
-  const double* q = blk + (uint64_t)A.st.q[n & 1] * kSB;
-  const double* k2 = A.kap + A.ko.off[2] + samp_r2(n) - 1;
-  double* PP = blk + (uint64_t)(A.st.PP + (uint32_t)l0 - 1) * kSB;  // p+(j-1, l0 + r) at C(j-1, 2) + l0 - 1 + r
-  const double chi = blk[(uint64_t)(A.st.chi + (uint32_t)n) * kSB];
-  const double h = blk[(uint64_t)A.st.h * kSB];
-  double acc[kRun] = {};
-  int j = l0;
+// Table passes: kRun consecutive entries (4 KB in one piece) of a top at a time.
+// With SPLIT the four waves of a workgroup take every fourth term of a run and
+// their sums are added in wave order; else a wave takes a run.  With a wave per
+// run the longest sum, n terms one after the other, is the time of a launch with
+// few blocks of samples; with many, bandwidth is, and SPLIT reads a little more
+// scattered.  M = 144, wave / SPLIT: 500 samples 9.6 / 3.5 ms, 10,000 21.8 / 16.3,
+// 20,000 34.6 / 31.0, 40,000 60.3 / 61.7, 65,536 97.3 / 103.4; M = 60: 5,000 2.4 /
+// 1.35, 100,000 13.8 / 14.1.  The rule goes by the samples of the whole call, so
+// that the sums do not depend on the parts that it is done in.
+constexpr int kRun = 8, kParts = 4, kOwn = kRun / kParts;
+constexpr uint64_t kSplitSamples = 32768;
+constexpr int kSumWords = kParts * kRun * kSB;
+
+// acc[t] = the sum over the workgroup's waves of entry w kOwn + t of the run.
+__device__ __forceinline__ void sum_waves(double (&acc)[kRun], double* red, int w, int lane) {
+#pragma unroll
+  for (int r = 0; r < kRun; ++r) red[(w * kRun + r) * kSB + lane] = acc[r];
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < kOwn; ++t) {
+    acc[t] = red[(w * kOwn + t) * kSB + lane];
+#pragma unroll
+    for (int v = 1; v < kParts; ++v) acc[t] += red[(v * kRun + w * kOwn + t) * kSB + lane];
+  }
+}
+
+// The terms j = first, first + STEP, .. < n of p+(x_n..x_l), l = l0..l0 + kRun - 1.
+template <int STEP>
+__device__ __forceinline__ void partial_terms(const double* q, const double* k2, const double* PP, int l0, int first,
+                                              int n, double (&acc)[kRun]) {
+  int j = first;
   // p+(j-1, l) is 1 for l = j and has no term for l > j
-  for (; j < l0 + kRun && j < n; ++j) {
+  for (; j < l0 + kRun && j < n; j += STEP) {
     const double c = k2[j] * q[(uint64_t)j * kSB];
     const double* p = PP + (uint64_t)samp_r2(j) * kSB;
 #pragma unroll
@@ -140,18 +154,42 @@ __global__ __launch_bounds__(256) void partial_kernel(StepArgs A, uint32_t nsb, 
     }
   }
 #pragma unroll 2
-  for (; j < n; ++j) {
+  for (; j < n; j += STEP) {
     const double c = k2[j] * q[(uint64_t)j * kSB];
     const double* p = PP + (uint64_t)samp_r2(j) * kSB;
 #pragma unroll
     for (int r = 0; r < kRun; ++r) acc[r] = fma(c, p[r * kSB], acc[r]);
   }
+}
+
+// p+(x_n..x_l), and from it q of step n + 1.
+template <bool SPLIT>
+__global__ __launch_bounds__(256) void partial_kernel(StepArgs A, uint32_t nsb, uint32_t runs) {
+  __shared__ double red[SPLIT ? kSumWords : 1];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int n = A.n;
+  const uint32_t item = SPLIT ? blockIdx.x : blockIdx.x * 4 + (uint32_t)w;
+  if (item >= runs * nsb) return;
+  const int l0 = 1 + (int)(item / nsb) * kRun;  // the longest sums first
+  double* blk = block_of(A, item % nsb) + lane;
+  const double* q = blk + (uint64_t)A.st.q[n & 1] * kSB;
+  const double* k2 = A.kap + A.ko.off[2] + samp_r2(n) - 1;
+  double* PP = blk + (uint64_t)(A.st.PP + (uint32_t)l0 - 1) * kSB;  // p+(j-1, l0 + r) at C(j-1, 2) + l0 - 1 + r
+  const double chi = blk[(uint64_t)(A.st.chi + (uint32_t)n) * kSB];
+  const double h = blk[(uint64_t)A.st.h * kSB];
+  double acc[kRun] = {};
+  if constexpr (SPLIT) {
+    partial_terms<kParts>(q, k2, PP, l0, l0 + w, n, acc);
+    sum_waves(acc, red, w, lane);
+  } else {
+    partial_terms<1>(q, k2, PP, l0, l0, n, acc);
+  }
 #pragma unroll
-  for (int r = 0; r < kRun; ++r) {
-    const int l = l0 + r;
+  for (int t = 0; t < (SPLIT ? kOwn : kRun); ++t) {
+    const int r = SPLIT ? w * kOwn + t : t, l = l0 + r;
     if (l > n) break;
     const double old = l < n ? PP[(uint64_t)(samp_r2(n) + (uint32_t)r) * kSB] : 1.0;
-    const double v = fma(0.25 * chi, acc[r], h * old);
+    const double v = fma(0.25 * chi, acc[t], h * old);
     PP[(uint64_t)(samp_r2(n + 1) + (uint32_t)r) * kSB] = v;
     if (l >= 2)
       blk[(uint64_t)(A.st.q[(n + 1) & 1] + (uint32_t)l - 1) * kSB] =
@@ -159,11 +197,44 @@ __global__ __launch_bounds__(256) void partial_kernel(StepArgs A, uint32_t nsb, 
   }
 }
 
-// V(n+1; e), e < n, for kRun consecutive e per wave; FULL takes the sums of
-// steps n and n + 1 (see gbs_sampler_double.hip).
-template <bool FULL>
-__device__ __forceinline__ void update_item(const StepArgs& A, uint32_t item, uint32_t nsb, uint32_t runs, int lane) {
+// The terms i = first, first + STEP, .. < n of V(n+1; e) (acc) and V(n+2; e)
+// (nxt), e = e0..e0 + kRun - 1.
+template <int STEP>
+__device__ __forceinline__ void update_terms(const double* q, const double* k2, const double* qn, const double* k2n,
+                                             const double* V, int e0, int first, int n, double (&acc)[kRun],
+                                             double (&nxt)[kRun]) {
+  int i = first;
+  for (; i < e0 + kRun && i < n; i += STEP) {
+    const double c = k2[i] * q[(uint64_t)i * kSB], cn = k2n[i] * qn[(uint64_t)i * kSB];
+    const double* p = V + (uint64_t)samp_r2(i) * kSB;
+#pragma unroll
+    for (int r = 0; r < kRun; ++r)
+      if (e0 + r < i) {
+        const double x = p[r * kSB];
+        acc[r] = fma(c, x, acc[r]);
+        nxt[r] = fma(cn, x, nxt[r]);
+      }
+  }
+#pragma unroll 2
+  for (; i < n; i += STEP) {
+    const double c = k2[i] * q[(uint64_t)i * kSB], cn = k2n[i] * qn[(uint64_t)i * kSB];
+    const double* p = V + (uint64_t)samp_r2(i) * kSB;
+#pragma unroll
+    for (int r = 0; r < kRun; ++r) {
+      const double x = p[r * kSB];
+      acc[r] = fma(c, x, acc[r]);
+      nxt[r] = fma(cn, x, nxt[r]);
+    }
+  }
+}
+
+// V(n+1; e), e < n; FULL takes the sums of steps n and n + 1 (see
+// gbs_sampler_double.hip), SPLIT as in partial_kernel.
+template <bool FULL, bool SPLIT>
+__device__ __forceinline__ void update_item(const StepArgs& A, uint32_t b, uint32_t nsb, uint32_t runs, int lane,
+                                            int w, double* red) {
   const int n = A.n;
+  const uint32_t item = FULL && SPLIT ? b : b * 4 + (uint32_t)w;
   if (item >= runs * nsb) return;
   const int e0 = 1 + (int)(item / nsb) * kRun;
   double* blk = block_of(A, item % nsb) + lane;
@@ -178,37 +249,22 @@ __device__ __forceinline__ void update_item(const StepArgs& A, uint32_t item, ui
     const double* qn = blk + (uint64_t)A.st.q[(n + 1) & 1] * kSB;
     const double* k2n = A.kap + A.ko.off[2] + samp_r2(n + 1) - 1;
     double acc[kRun] = {}, nxt[kRun] = {};
-    int i = e0 + 1;
-    for (; i < e0 + kRun && i < n; ++i) {
-      const double c = k2[i] * q[(uint64_t)i * kSB], cn = k2n[i] * qn[(uint64_t)i * kSB];
-      const double* p = V + (uint64_t)samp_r2(i) * kSB;
-#pragma unroll
-      for (int r = 0; r < kRun; ++r)
-        if (e0 + r < i) {
-          const double x = p[r * kSB];
-          acc[r] = fma(c, x, acc[r]);
-          nxt[r] = fma(cn, x, nxt[r]);
-        }
-    }
-#pragma unroll 2
-    for (; i < n; ++i) {
-      const double c = k2[i] * q[(uint64_t)i * kSB], cn = k2n[i] * qn[(uint64_t)i * kSB];
-      const double* p = V + (uint64_t)samp_r2(i) * kSB;
-#pragma unroll
-      for (int r = 0; r < kRun; ++r) {
-        const double x = p[r * kSB];
-        acc[r] = fma(c, x, acc[r]);
-        nxt[r] = fma(cn, x, nxt[r]);
-      }
+    if constexpr (SPLIT) {
+      update_terms<kParts>(q, k2, qn, k2n, V, e0, e0 + 1 + w, n, acc, nxt);
+      sum_waves(acc, red, w, lane);
+      __syncthreads();  // the sums of acc have been read
+      sum_waves(nxt, red, w, lane);
+    } else {
+      update_terms<1>(q, k2, qn, k2n, V, e0, e0 + 1, n, acc, nxt);
     }
     double* vs = V + (uint64_t)samp_r2(n + 2) * kSB;
 #pragma unroll
-    for (int r = 0; r < kRun; ++r) {
-      const int e = e0 + r;
+    for (int t = 0; t < (SPLIT ? kOwn : kRun); ++t) {
+      const int r = SPLIT ? w * kOwn + t : t, e = e0 + r;
       if (e >= n) break;
-      const double s = fma(q[(uint64_t)e * kSB], vo[r * kSB], acc[r]);
+      const double s = fma(q[(uint64_t)e * kSB], vo[r * kSB], acc[t]);
       vo[r * kSB] = fma(0.25 * chi, s, h * vn[r * kSB]);
-      vs[r * kSB] = fma(qn[(uint64_t)e * kSB], vs[r * kSB], nxt[r]);
+      vs[r * kSB] = fma(qn[(uint64_t)e * kSB], vs[r * kSB], nxt[t]);
     }
   } else {
     const double* vl = V + (uint64_t)samp_r2(n - 1) * kSB;
@@ -239,12 +295,14 @@ __device__ __forceinline__ void row_of(const StepArgs& A, int r, uint32_t* kap, 
 }
 
 // The V update of step n and the product with V(n; .), which are independent.
-template <bool FULL>
+template <bool FULL, bool SPLIT>
 __global__ __launch_bounds__(256) void step_kernel(StepArgs A, int rows, int row_blocks, uint32_t nprod,
                                                    uint32_t nsb, uint32_t runs) {
   __shared__ double Bs[2][1][kKC][kLdB];
+  static_assert(sizeof(Bs) >= kSumWords * sizeof(double), "the sums of a workgroup's waves fit the operand buffers");
   if (blockIdx.x >= nprod) {
-    update_item<FULL>(A, (blockIdx.x - nprod) * 4 + (threadIdx.x >> 6), nsb, runs, threadIdx.x & 63);
+    update_item<FULL, SPLIT>(A, blockIdx.x - nprod, nsb, runs, threadIdx.x & 63,
+                             __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), &Bs[0][0][0][0]);
     return;
   }
   const int n = A.n;
@@ -274,6 +332,7 @@ hipError_t launch_single_sampler(int M, const double* kap, KapOffsets ko, int64_
                                  uint64_t ldu, double* tab, uint8_t* bits, double* prob, double* cond,
                                  hipStream_t s) {
   const uint32_t nsb = (uint32_t)((nsamp + kSB - 1) / kSB);
+  const bool split = ldu <= kSplitSamples;  // the call's samples
   StepArgs A{kap, ko, tab, Store::make(M), M, 0};
   hipError_t e = hipSuccess;
   for (int n = 1; n <= M && e == hipSuccess; ++n) {
@@ -282,16 +341,17 @@ hipError_t launch_single_sampler(int M, const double* kap, KapOffsets ko, int64_
     hipLaunchKernelGGL(bit_kernel, dim3(nsb), dim3(256), 0, s, A, u, ldu, nsamp, bits, prob, cond);
     if (n < M) {
       const uint32_t pr = ((uint32_t)n + kRun - 1) / kRun;
-      hipLaunchKernelGGL(partial_kernel, dim3((pr * nsb + 3) / 4), dim3(256), 0, s, A, nsb, pr);
-      // at n = 1 the products have no terms: their slots are set to 0
-      const uint32_t rows = 2 * m - 1, rb = (rows + 63) / 64, runs = ((uint32_t)n - 1 + kRun - 1) / kRun;
-      const uint32_t nprod = rb * nsb, upd = (runs * nsb + 3) / 4;
-      if ((m & 1) == 0)
-        hipLaunchKernelGGL(step_kernel<true>, dim3(nprod + upd), dim3(256), 0, s, A, (int)rows, (int)rb, nprod, nsb,
-                           runs);
+      if (split)
+        hipLaunchKernelGGL(partial_kernel<true>, dim3(pr * nsb), dim3(256), 0, s, A, nsb, pr);
       else
-        hipLaunchKernelGGL(step_kernel<false>, dim3(nprod + upd), dim3(256), 0, s, A, (int)rows, (int)rb, nprod, nsb,
-                           runs);
+        hipLaunchKernelGGL(partial_kernel<false>, dim3((pr * nsb + 3) / 4), dim3(256), 0, s, A, nsb, pr);
+      // at n = 1 the products have no terms: their slots are set to 0
+      const bool full = (m & 1) == 0;
+      const uint32_t rows = 2 * m - 1, rb = (rows + 63) / 64, runs = ((uint32_t)n - 1 + kRun - 1) / kRun;
+      const uint32_t nprod = rb * nsb;
+      const dim3 grid(nprod + (full && split ? runs * nsb : (runs * nsb + 3) / 4));
+      const auto k = !full ? step_kernel<false, false> : split ? step_kernel<true, true> : step_kernel<true, false>;
+      hipLaunchKernelGGL(k, grid, dim3(256), 0, s, A, (int)rows, (int)rb, nprod, nsb, runs);
     }
     e = hipGetLastError();
   }

@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("K,M,n", [(5, 11, 65), (5, 12, 1), (5, 13, 64), (5, 17, 65), (5, 24, 130), (5, 40, 1500),
                                    (5, 41, 3000), (3, 23, 65), (3, 24, 1), (3, 25, 64), (3, 33, 65),
-                                   (3, 34, 129), (3, 101, 700), (3, 256, 70)])
+                                   (3, 34, 129), (3, 101, 700), (3, 256, 70),
+                                   (3, 25, 32768), (3, 26, 32769)])
 def test_against_oracle(P, K, M, n):  # noqa: F811
     _say("case: sampler by steps", K, M, n)
     if M > 144:
