@@ -38,6 +38,8 @@ PEAK_HBM_BYTES = 8e12
 
 # the sources the order-5 kernel of the headline path is compiled from
 TRAFFIC_SOURCES = ("gbs_device.h", "gbs_subset.h", "gbs_forward_group.hip", "gbs_group_tile.inc")
+# and the samplers at the sizes of the bench
+SAMPLER_SOURCES = ("gbs_sampler.h", "gbs_sampler_product.h", "gbs_sampler_single.hip", "gbs_sampler_double.hip")
 
 
 def kernel_source_hash(sources=TRAFFIC_SOURCES) -> str:
@@ -243,7 +245,7 @@ def batched_and_adjoint(P, torch, G, steps):
                                         "peak": PEAK_VALU_TFLOPS, "unit": "TFLOP/s",
                                         "frac": fl / wall / 1e12 / PEAK_VALU_TFLOPS,
                                         "algorithmic_flops": fl,
-                                        "note": "wall time per call, nine launches of "
+                                        "note": "wall time per call, eleven launches of "
                                                 "small grids: launch and latency bound"}}
     return out
 
@@ -444,7 +446,7 @@ def sampler_traffic(K_):
     except (OSError, ValueError):
         return None
     ent = rec.get(f"k{K_}")
-    if not ent or rec.get("source_hash") != kernel_source_hash(("gbs_sampler.hip",)):
+    if not ent or rec.get("source_hash") != kernel_source_hash(SAMPLER_SOURCES):
         return None
     return ent.get("bytes_per_sample")
 
@@ -459,7 +461,7 @@ def sampler_legs(P, torch, np, G, sigma, counts):
         g = torch.Generator(device="cuda:0")
         g.manual_seed(2511 + K_)
         u = torch.rand((M, n), dtype=torch.float64, device="cuda:0", generator=g)
-        if K_ == 3:  # warm-up: one workgroup (a K = 5 workgroup alone runs for seconds)
+        if K_ == 3:  # warm-up: 64 samples
             P.gbs_sample(M, kap, K_, u[:, :64].contiguous())
         torch.cuda.synchronize()
         log(f"[bench] sampler K={K_}: {n} samples")
