@@ -15,7 +15,7 @@
 // entries each at step n, bound by memory bandwidth.  The sum of the V update of
 // step n + 1 over i < n needs only q of step n + 1, which is known after bit n and
 // p+ of top n, so every other step takes the V sums of two steps in one pass.
-// M = 144, 65,536 samples: 97.5 ms, 6 MB of table reads per sample at 4 TB/s,
+// M = 144, 65,536 samples: 102 ms, 6 MB of table reads per sample at 3.9 TB/s,
 // against 325 ms of one workgroup per 64 samples that read 20 MB per sample.
 //
 // Storage as in gbs_sampler_double.hip: blocks of 64 samples, entry-major.
@@ -112,17 +112,16 @@ __global__ __launch_bounds__(256) void bit_kernel(StepArgs A, const double* __re
   }
 }
 
-// Table passes: kRun consecutive entries (4 KB in one piece) of a top at a time.
-// With SPLIT the four waves of a workgroup take every fourth term of a run and
-// their sums are added in wave order; else a wave takes a run.  With a wave per
-// run the longest sum, n terms one after the other, is the time of a launch with
-// few blocks of samples; with many, bandwidth is, and SPLIT reads a little more
-// scattered.  M = 144, wave / SPLIT: 500 samples 9.6 / 3.5 ms, 10,000 21.8 / 16.3,
-// 20,000 34.6 / 31.0, 40,000 60.3 / 61.7, 65,536 97.3 / 103.4; M = 60: 5,000 2.4 /
-// 1.35, 100,000 13.8 / 14.1.  The rule goes by the samples of the whole call, so
-// that the sums do not depend on the parts that it is done in.
+// Table passes: kRun consecutive entries (4 KB in one piece) of a top per workgroup;
+// its four waves take every fourth term of the sums, which are added in wave order.
+// With a wave per run the longest sum, n terms one after the other, is the time of a
+// launch with few blocks of samples; with many, bandwidth is, and the split reads a
+// little more scattered.  M = 144, a wave per run / split: 500 samples 9.6 / 3.5 ms,
+// 10,000 21.8 / 16.3, 20,000 34.6 / 30.4, 40,000 60.3 / 60.7, 65,536 98.0 / 102.2;
+// M = 60: 5,000 2.4 / 1.35, 100,000 13.8 / 13.7; M = 40, 200,000 9.5 / 9.7.  One form for every call: a sample's
+// sums, and so its bits, depend on its own column of uniforms alone, not on how many
+// samples are drawn with it.
 constexpr int kRun = 8, kParts = 4, kOwn = kRun / kParts;
-constexpr uint64_t kSplitSamples = 32768;
 constexpr int kSumWords = kParts * kRun * kSB;
 
 // acc[t] = the sum over the workgroup's waves of entry w kOwn + t of the run.
@@ -138,13 +137,12 @@ __device__ __forceinline__ void sum_waves(double (&acc)[kRun], double* red, int 
   }
 }
 
-// The terms j = first, first + STEP, .. < n of p+(x_n..x_l), l = l0..l0 + kRun - 1.
-template <int STEP>
+// The terms j = first, first + kParts, .. < n of p+(x_n..x_l), l = l0..l0 + kRun - 1.
 __device__ __forceinline__ void partial_terms(const double* q, const double* k2, const double* PP, int l0, int first,
                                               int n, double (&acc)[kRun]) {
   int j = first;
   // p+(j-1, l) is 1 for l = j and has no term for l > j
-  for (; j < l0 + kRun && j < n; j += STEP) {
+  for (; j < l0 + kRun && j < n; j += kParts) {
     const double c = k2[j] * q[(uint64_t)j * kSB];
     const double* p = PP + (uint64_t)samp_r2(j) * kSB;
 #pragma unroll
@@ -154,7 +152,7 @@ __device__ __forceinline__ void partial_terms(const double* q, const double* k2,
     }
   }
 #pragma unroll 2
-  for (; j < n; j += STEP) {
+  for (; j < n; j += kParts) {
     const double c = k2[j] * q[(uint64_t)j * kSB];
     const double* p = PP + (uint64_t)samp_r2(j) * kSB;
 #pragma unroll
@@ -163,13 +161,11 @@ __device__ __forceinline__ void partial_terms(const double* q, const double* k2,
 }
 
 // p+(x_n..x_l), and from it q of step n + 1.
-template <bool SPLIT>
-__global__ __launch_bounds__(256) void partial_kernel(StepArgs A, uint32_t nsb, uint32_t runs) {
-  __shared__ double red[SPLIT ? kSumWords : 1];
+__global__ __launch_bounds__(256) void partial_kernel(StepArgs A, uint32_t nsb) {
+  __shared__ double red[kSumWords];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int n = A.n;
-  const uint32_t item = SPLIT ? blockIdx.x : blockIdx.x * 4 + (uint32_t)w;
-  if (item >= runs * nsb) return;
+  const uint32_t item = blockIdx.x;
   const int l0 = 1 + (int)(item / nsb) * kRun;  // the longest sums first
   double* blk = block_of(A, item % nsb) + lane;
   const double* q = blk + (uint64_t)A.st.q[n & 1] * kSB;
@@ -178,15 +174,11 @@ __global__ __launch_bounds__(256) void partial_kernel(StepArgs A, uint32_t nsb, 
   const double chi = blk[(uint64_t)(A.st.chi + (uint32_t)n) * kSB];
   const double h = blk[(uint64_t)A.st.h * kSB];
   double acc[kRun] = {};
-  if constexpr (SPLIT) {
-    partial_terms<kParts>(q, k2, PP, l0, l0 + w, n, acc);
-    sum_waves(acc, red, w, lane);
-  } else {
-    partial_terms<1>(q, k2, PP, l0, l0, n, acc);
-  }
+  partial_terms(q, k2, PP, l0, l0 + w, n, acc);
+  sum_waves(acc, red, w, lane);
 #pragma unroll
-  for (int t = 0; t < (SPLIT ? kOwn : kRun); ++t) {
-    const int r = SPLIT ? w * kOwn + t : t, l = l0 + r;
+  for (int t = 0; t < kOwn; ++t) {
+    const int r = w * kOwn + t, l = l0 + r;
     if (l > n) break;
     const double old = l < n ? PP[(uint64_t)(samp_r2(n) + (uint32_t)r) * kSB] : 1.0;
     const double v = fma(0.25 * chi, acc[t], h * old);
@@ -197,14 +189,13 @@ __global__ __launch_bounds__(256) void partial_kernel(StepArgs A, uint32_t nsb, 
   }
 }
 
-// The terms i = first, first + STEP, .. < n of V(n+1; e) (acc) and V(n+2; e)
+// The terms i = first, first + kParts, .. < n of V(n+1; e) (acc) and V(n+2; e)
 // (nxt), e = e0..e0 + kRun - 1.
-template <int STEP>
 __device__ __forceinline__ void update_terms(const double* q, const double* k2, const double* qn, const double* k2n,
                                              const double* V, int e0, int first, int n, double (&acc)[kRun],
                                              double (&nxt)[kRun]) {
   int i = first;
-  for (; i < e0 + kRun && i < n; i += STEP) {
+  for (; i < e0 + kRun && i < n; i += kParts) {
     const double c = k2[i] * q[(uint64_t)i * kSB], cn = k2n[i] * qn[(uint64_t)i * kSB];
     const double* p = V + (uint64_t)samp_r2(i) * kSB;
 #pragma unroll
@@ -216,7 +207,7 @@ __device__ __forceinline__ void update_terms(const double* q, const double* k2, 
       }
   }
 #pragma unroll 2
-  for (; i < n; i += STEP) {
+  for (; i < n; i += kParts) {
     const double c = k2[i] * q[(uint64_t)i * kSB], cn = k2n[i] * qn[(uint64_t)i * kSB];
     const double* p = V + (uint64_t)samp_r2(i) * kSB;
 #pragma unroll
@@ -228,13 +219,14 @@ __device__ __forceinline__ void update_terms(const double* q, const double* k2, 
   }
 }
 
-// V(n+1; e), e < n; FULL takes the sums of steps n and n + 1 (see
-// gbs_sampler_double.hip), SPLIT as in partial_kernel.
-template <bool FULL, bool SPLIT>
+// V(n+1; e), e < n.  FULL takes the sums of steps n and n + 1 (see
+// gbs_sampler_double.hip), a workgroup per run; the step after it adds one term,
+// a wave per run.
+template <bool FULL>
 __device__ __forceinline__ void update_item(const StepArgs& A, uint32_t b, uint32_t nsb, uint32_t runs, int lane,
                                             int w, double* red) {
   const int n = A.n;
-  const uint32_t item = FULL && SPLIT ? b : b * 4 + (uint32_t)w;
+  const uint32_t item = FULL ? b : b * 4 + (uint32_t)w;
   if (item >= runs * nsb) return;
   const int e0 = 1 + (int)(item / nsb) * kRun;
   double* blk = block_of(A, item % nsb) + lane;
@@ -249,18 +241,14 @@ __device__ __forceinline__ void update_item(const StepArgs& A, uint32_t b, uint3
     const double* qn = blk + (uint64_t)A.st.q[(n + 1) & 1] * kSB;
     const double* k2n = A.kap + A.ko.off[2] + samp_r2(n + 1) - 1;
     double acc[kRun] = {}, nxt[kRun] = {};
-    if constexpr (SPLIT) {
-      update_terms<kParts>(q, k2, qn, k2n, V, e0, e0 + 1 + w, n, acc, nxt);
-      sum_waves(acc, red, w, lane);
-      __syncthreads();  // the sums of acc have been read
-      sum_waves(nxt, red, w, lane);
-    } else {
-      update_terms<1>(q, k2, qn, k2n, V, e0, e0 + 1, n, acc, nxt);
-    }
+    update_terms(q, k2, qn, k2n, V, e0, e0 + 1 + w, n, acc, nxt);
+    sum_waves(acc, red, w, lane);
+    __syncthreads();  // the sums of acc have been read
+    sum_waves(nxt, red, w, lane);
     double* vs = V + (uint64_t)samp_r2(n + 2) * kSB;
 #pragma unroll
-    for (int t = 0; t < (SPLIT ? kOwn : kRun); ++t) {
-      const int r = SPLIT ? w * kOwn + t : t, e = e0 + r;
+    for (int t = 0; t < kOwn; ++t) {
+      const int r = w * kOwn + t, e = e0 + r;
       if (e >= n) break;
       const double s = fma(q[(uint64_t)e * kSB], vo[r * kSB], acc[t]);
       vo[r * kSB] = fma(0.25 * chi, s, h * vn[r * kSB]);
@@ -295,13 +283,13 @@ __device__ __forceinline__ void row_of(const StepArgs& A, int r, uint32_t* kap, 
 }
 
 // The V update of step n and the product with V(n; .), which are independent.
-template <bool FULL, bool SPLIT>
+template <bool FULL>
 __global__ __launch_bounds__(256) void step_kernel(StepArgs A, int rows, int row_blocks, uint32_t nprod,
                                                    uint32_t nsb, uint32_t runs) {
   __shared__ double Bs[2][1][kKC][kLdB];
   static_assert(sizeof(Bs) >= kSumWords * sizeof(double), "the sums of a workgroup's waves fit the operand buffers");
   if (blockIdx.x >= nprod) {
-    update_item<FULL, SPLIT>(A, blockIdx.x - nprod, nsb, runs, threadIdx.x & 63,
+    update_item<FULL>(A, blockIdx.x - nprod, nsb, runs, threadIdx.x & 63,
                              __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), &Bs[0][0][0][0]);
     return;
   }
@@ -332,7 +320,6 @@ hipError_t launch_single_sampler(int M, const double* kap, KapOffsets ko, int64_
                                  uint64_t ldu, double* tab, uint8_t* bits, double* prob, double* cond,
                                  hipStream_t s) {
   const uint32_t nsb = (uint32_t)((nsamp + kSB - 1) / kSB);
-  const bool split = ldu <= kSplitSamples;  // the call's samples
   StepArgs A{kap, ko, tab, Store::make(M), M, 0};
   hipError_t e = hipSuccess;
   for (int n = 1; n <= M && e == hipSuccess; ++n) {
@@ -341,16 +328,13 @@ hipError_t launch_single_sampler(int M, const double* kap, KapOffsets ko, int64_
     hipLaunchKernelGGL(bit_kernel, dim3(nsb), dim3(256), 0, s, A, u, ldu, nsamp, bits, prob, cond);
     if (n < M) {
       const uint32_t pr = ((uint32_t)n + kRun - 1) / kRun;
-      if (split)
-        hipLaunchKernelGGL(partial_kernel<true>, dim3(pr * nsb), dim3(256), 0, s, A, nsb, pr);
-      else
-        hipLaunchKernelGGL(partial_kernel<false>, dim3((pr * nsb + 3) / 4), dim3(256), 0, s, A, nsb, pr);
+      hipLaunchKernelGGL(partial_kernel, dim3(pr * nsb), dim3(256), 0, s, A, nsb);
       // at n = 1 the products have no terms: their slots are set to 0
       const bool full = (m & 1) == 0;
       const uint32_t rows = 2 * m - 1, rb = (rows + 63) / 64, runs = ((uint32_t)n - 1 + kRun - 1) / kRun;
       const uint32_t nprod = rb * nsb;
-      const dim3 grid(nprod + (full && split ? runs * nsb : (runs * nsb + 3) / 4));
-      const auto k = !full ? step_kernel<false, false> : split ? step_kernel<true, true> : step_kernel<true, false>;
+      const dim3 grid(nprod + (full ? runs * nsb : (runs * nsb + 3) / 4));
+      const auto k = full ? step_kernel<true> : step_kernel<false>;
       hipLaunchKernelGGL(k, grid, dim3(256), 0, s, A, (int)rows, (int)rb, nprod, nsb, runs);
     }
     e = hipGetLastError();
