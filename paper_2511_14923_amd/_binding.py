@@ -4,6 +4,7 @@ compute step runs in the library's HIP kernels.  There is no fallback: if
 libgbs.so has not been built, loading raises."""
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 
@@ -240,20 +241,27 @@ def _scratch(nbytes, stream, device):
     """nbytes of device memory for the library to work in during one call on
     `stream`, or None (the library then allocates its own).  From torch's caching
     allocator: it keeps the memory for the next call, gives it back when other
-    tensors need it (or on torch.cuda.empty_cache), and hands it out again only
-    to work that runs after this call's on the same stream.  A stream that is
+    tensors need it (or on torch.cuda.empty_cache), and hands it out again to work
+    on the same stream.  It tells streams apart by their handles, so only the
+    default stream and torch's own streams get any: another handle can stand for a
+    different queue in every thread (hipStreamPerThread), or for a new stream after
+    the one that still runs this call's kernels was destroyed.  A stream that is
     being captured gets None: the graph must hold memory of its own."""
     if nbytes <= 0:
         return None
+    if stream is None:
+        own = torch.cuda.current_stream(device)
+    elif isinstance(stream, torch.cuda.Stream):
+        own = stream
+    elif int(stream):
+        return None
+    else:
+        own = torch.cuda.default_stream(device)
+    # a stream that torch did not make has its handle for an id
+    if own.cuda_stream and own.stream_id == own.cuda_stream:
+        return None
     try:
-        if stream is None:
-            if torch.cuda.is_current_stream_capturing():
-                return None
-            return torch.empty(nbytes, dtype=torch.uint8, device=device)
-        if not isinstance(stream, torch.cuda.Stream):
-            stream = (torch.cuda.ExternalStream(int(stream), device) if int(stream)
-                      else torch.cuda.default_stream(device))
-        with torch.cuda.stream(stream):
+        with contextlib.nullcontext() if stream is None else torch.cuda.stream(own):
             if torch.cuda.is_current_stream_capturing():
                 return None
             return torch.empty(nbytes, dtype=torch.uint8, device=device)
