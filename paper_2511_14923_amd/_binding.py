@@ -241,8 +241,9 @@ def _scratch(nbytes, stream, device):
     """nbytes of device memory for the library to work in during one call on
     `stream`, or None (the library then allocates its own).  From torch's caching
     allocator: it keeps the memory for the next call, gives it back when other
-    tensors need it (or on torch.cuda.empty_cache), and hands it out again to work
-    on the same stream.  It tells streams apart by their handles, so only the
+    tensors or the library's own allocations need it (_own; or on
+    torch.cuda.empty_cache), and hands it out again to work on the same stream.  It
+    tells streams apart by their handles, so only the
     default stream and torch's own streams get any: another handle can stand for a
     different queue in every thread (hipStreamPerThread), or for a new stream after
     the one that still runs this call's kernels was destroyed.  A stream that is
@@ -269,6 +270,29 @@ def _scratch(nbytes, stream, device):
         return None
 
 
+def _own(call, stream, device):
+    """call(), which runs in memory that the library allocates itself.  Memory that
+    torch keeps unused (such as what _scratch lent before) is not free for it, so a
+    call that finds too little is repeated once after torch gave that back, unless
+    the stream is being captured."""
+    st = call()
+    if st != GBS_E_OUT_OF_MEMORY or \
+            torch.cuda.memory_reserved(device) <= torch.cuda.memory_allocated(device):
+        return st
+    if stream is None:
+        on = contextlib.nullcontext()
+    elif isinstance(stream, torch.cuda.Stream):
+        on = torch.cuda.stream(stream)
+    else:
+        on = torch.cuda.stream(torch.cuda.ExternalStream(int(stream), device) if int(stream)
+                               else torch.cuda.default_stream(device))
+    with on:
+        if torch.cuda.is_current_stream_capturing():
+            return st
+    torch.cuda.empty_cache()
+    return call()
+
+
 def _forward(M, sigma, mu, max_order, flags, corr, cum, stream, own):
     """A forward call in lent scratch memory, or own() without any."""
     dev = sigma.device
@@ -276,7 +300,7 @@ def _forward(M, sigma, mu, max_order, flags, corr, cum, stream, own):
         work = _scratch(lib().gbs_cumulants_scratch(M, max_order, flags, mu is not None,
                                                     corr is not None), stream, dev)
         if work is None:
-            return own(_stream(stream, dev))
+            return _own(lambda: own(_stream(stream, dev)), stream, dev)
         return lib().gbs_cumulants_in(M, _ptr(sigma), _ptr(mu), max_order, flags, _ptr(corr),
                                       _ptr(cum), ctypes.c_void_p(work.data_ptr()), work.numel(),
                                       _stream(stream, dev))
@@ -415,8 +439,10 @@ def gbs_cumulants_shard(M: int, sigma: torch.Tensor, order: int, rank0: int, cou
     _need(cum, "cum", count, optional=True)
     _same_device(("sigma", sigma), ("corr", corr), ("cum", cum))
     with torch.cuda.device(sigma.device):
-        st = lib().gbs_cumulants_shard(M, _ptr(sigma), order, rank0, count, flags, _ptr(corr),
-                                       _ptr(cum), _stream(stream, sigma.device))
+        st = _own(lambda: lib().gbs_cumulants_shard(M, _ptr(sigma), order, rank0, count, flags,
+                                                    _ptr(corr), _ptr(cum),
+                                                    _stream(stream, sigma.device)),
+                  stream, sigma.device)
     _check(st, "gbs_cumulants_shard")
     return corr, cum
 
@@ -426,6 +452,23 @@ def _ptr_u8(t):
             or not t.is_contiguous():
         raise ValueError("contiguous uint8 device tensor required")
     return ctypes.c_void_p(t.data_ptr())
+
+
+def _sample_bytes(M, max_order, n, batch, device):
+    """gbs_sample_scratch; for an automatic batch (0) that does not hold all n samples,
+    a quarter of the free memory where what torch keeps unused counts as free, so that
+    a call gets the same whether or not another one has worked in lent memory before."""
+    nbytes = lib().gbs_sample_scratch(M, max_order, n, batch)
+    if batch != 0 or nbytes <= 0:
+        return nbytes
+    block = lib().gbs_sample_scratch(M, max_order, 64, 64)  # the tables of 64 samples
+    blocks = -(-n // 64)
+    if nbytes >= blocks * block:
+        return nbytes
+    free = torch.cuda.mem_get_info(device)[0]
+    free += torch.cuda.memory_reserved(device) - torch.cuda.memory_allocated(device)
+    parts = -(-blocks // max(1, free // 4 // block))
+    return -(-blocks // parts) * block
 
 
 def gbs_sample(M: int, kappa: torch.Tensor, max_order: int, uniforms: torch.Tensor, bits=None,
@@ -458,10 +501,11 @@ def gbs_sample(M: int, kappa: torch.Tensor, max_order: int, uniforms: torch.Tens
     _same_device(("kappa", kappa), ("uniforms", uniforms), ("bits", bits), ("prob", prob),
                  ("cond", cond))
     with torch.cuda.device(dev):
-        work = _scratch(lib().gbs_sample_scratch(M, max_order, n, batch), stream, dev)
+        work = _scratch(_sample_bytes(M, max_order, n, batch, dev), stream, dev)
         if work is None:
-            st = lib().gbs_sample(M, _ptr(kappa), max_order, n, _ptr(uniforms), _ptr_u8(bits),
-                                  _ptr(prob), _ptr(cond), batch, flags, _stream(stream, dev))
+            st = _own(lambda: lib().gbs_sample(M, _ptr(kappa), max_order, n, _ptr(uniforms),
+                                               _ptr_u8(bits), _ptr(prob), _ptr(cond), batch, flags,
+                                               _stream(stream, dev)), stream, dev)
         else:
             st = lib().gbs_sample_in(M, _ptr(kappa), max_order, n, _ptr(uniforms), _ptr_u8(bits),
                                      _ptr(prob), _ptr(cond), _ptr_u8(work), work.numel(), flags,
@@ -484,8 +528,9 @@ def gbs_sample_cumulants(bits: torch.Tensor, max_order: int, cum=None, flags: in
     with torch.cuda.device(bits.device):
         work = _scratch(lib().gbs_sample_cumulants_scratch(M, n, max_order), stream, bits.device)
         if work is None:
-            st = lib().gbs_sample_cumulants(M, n, _ptr_u8(bits), max_order, _ptr(cum), flags,
-                                            _stream(stream, bits.device))
+            st = _own(lambda: lib().gbs_sample_cumulants(M, n, _ptr_u8(bits), max_order, _ptr(cum),
+                                                         flags, _stream(stream, bits.device)),
+                      stream, bits.device)
         else:
             st = lib().gbs_sample_cumulants_in(M, n, _ptr_u8(bits), max_order, _ptr(cum),
                                                _ptr_u8(work), work.numel(), flags,
@@ -505,8 +550,8 @@ def gbs_pearson(x: torch.Tensor, y: torch.Tensor, r=None, flags: int = 0, stream
     with torch.cuda.device(x.device):
         work = _scratch(lib().gbs_pearson_scratch(), stream, x.device)
         if work is None:
-            st = lib().gbs_pearson(x.numel(), _ptr(x), _ptr(y), _ptr(r), flags,
-                                   _stream(stream, x.device))
+            st = _own(lambda: lib().gbs_pearson(x.numel(), _ptr(x), _ptr(y), _ptr(r), flags,
+                                                _stream(stream, x.device)), stream, x.device)
         else:
             st = lib().gbs_pearson_in(x.numel(), _ptr(x), _ptr(y), _ptr(r),
                                       ctypes.c_void_p(work.data_ptr()), work.numel(), flags,
@@ -530,8 +575,10 @@ def gbs_cumulant_grad(M: int, sigma: torch.Tensor, max_order: int, flags: int = 
     with torch.cuda.device(dev):
         work = _scratch(lib().gbs_cumulant_grad_scratch(M, max_order), stream, dev)
         if work is None:
-            st = lib().gbs_cumulant_grad(M, _ptr(sigma), max_order, flags, _ptr(grad_corr),
-                                         _ptr(grad_cum), _ptr(grad_sigma), _stream(stream, dev))
+            st = _own(lambda: lib().gbs_cumulant_grad(M, _ptr(sigma), max_order, flags,
+                                                      _ptr(grad_corr), _ptr(grad_cum),
+                                                      _ptr(grad_sigma), _stream(stream, dev)),
+                      stream, dev)
         else:
             st = lib().gbs_cumulant_grad_in(M, _ptr(sigma), max_order, flags, _ptr(grad_corr),
                                             _ptr(grad_cum), _ptr(grad_sigma),
@@ -567,7 +614,8 @@ def gbs_cumulants_batched(instances, max_order: int, flags: int = 0, stream=None
     arr = _instances(instances, max_order)
     dev = instances[0][1].device
     with torch.cuda.device(dev):
-        st = lib().gbs_cumulants_batched(len(instances), arr, max_order, flags, _stream(stream, dev))
+        st = _own(lambda: lib().gbs_cumulants_batched(len(instances), arr, max_order, flags,
+                                                      _stream(stream, dev)), stream, dev)
     _check(st, "gbs_cumulants_batched")
 
 
@@ -576,8 +624,9 @@ def gbs_autotune_batched(instances, max_order: int, flags: int = 0, stream=None)
     dev = instances[0][1].device
     best = gbs_tuning()
     with torch.cuda.device(dev):
-        st = lib().gbs_autotune_batched(len(instances), arr, max_order, flags, _stream(stream, dev),
-                                        ctypes.byref(best))
+        st = _own(lambda: lib().gbs_autotune_batched(len(instances), arr, max_order, flags,
+                                                     _stream(stream, dev), ctypes.byref(best)),
+                  stream, dev)
     _check(st, "gbs_autotune_batched")
     return best.as_dict()
 

@@ -114,7 +114,10 @@ DeviceContext* current_context(hipError_t* err) {
 
 gbs_status to_status(hipError_t e) {
   if (e == hipSuccess) return GBS_OK;
-  if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) return GBS_E_OUT_OF_MEMORY;
+  if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
+    (void)hipGetLastError();  // reported here: the next call's launch checks must not see it again
+    return GBS_E_OUT_OF_MEMORY;
+  }
   return GBS_E_DEVICE;
 }
 

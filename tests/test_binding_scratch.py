@@ -79,3 +79,68 @@ def test_nothing_to_lend(cuda):
     assert B._scratch(4096, None, DEV) is None
     assert B._scratch(4096, Stream(8, 1), DEV) is None
     assert cuda.lent == []
+
+
+@pytest.fixture
+def memory(cuda, monkeypatch):
+    """Device memory of `total` bytes with `reserved` held by torch, `used` of it in use."""
+    cuda.total, cuda.reserved, cuda.used, cuda.emptied = 288 << 30, 0, 0, 0
+
+    def empty_cache():
+        cuda.reserved, cuda.emptied = cuda.used, cuda.emptied + 1
+
+    monkeypatch.setattr(torch.cuda, "mem_get_info", lambda d=None: (cuda.total - cuda.reserved, cuda.total))
+    monkeypatch.setattr(torch.cuda, "memory_reserved", lambda d=None: cuda.reserved)
+    monkeypatch.setattr(torch.cuda, "memory_allocated", lambda d=None: cuda.used)
+    monkeypatch.setattr(torch.cuda, "empty_cache", empty_cache)
+    return cuda
+
+
+@pytest.mark.parametrize("stream", [None, 0, 2, Stream(8, 1)])
+def test_out_of_memory_is_tried_again_without_torchs_unused_memory(memory, stream):
+    need = 250 << 30
+
+    def call():
+        call.n += 1
+        return B.GBS_OK if memory.total - memory.reserved >= need else B.GBS_E_OUT_OF_MEMORY
+
+    call.n = 0
+    memory.reserved, memory.used = 72 << 30, 1 << 30
+    assert B._own(call, stream, DEV) == B.GBS_OK
+    assert (call.n, memory.emptied) == (2, 1)
+    # nothing unused, in use, or a stream under capture: the status stands
+    call.n = 0
+    memory.reserved = memory.used = 72 << 30
+    assert B._own(call, stream, DEV) == B.GBS_E_OUT_OF_MEMORY
+    memory.used, memory.capturing = 0, True
+    assert B._own(call, stream, DEV) == B.GBS_E_OUT_OF_MEMORY
+    assert (call.n, memory.emptied) == (2, 1)
+    call.n = 0
+    assert B._own(lambda: B.GBS_E_NOT_SPD, stream, DEV) == B.GBS_E_NOT_SPD
+
+
+def test_automatic_batch_counts_torchs_unused_memory_as_free(memory, monkeypatch):
+    per = 8_000_000  # bytes of tables per sample
+
+    class Lib:
+        @staticmethod
+        def gbs_sample_scratch(M, K, n, batch):
+            if n == 0 or batch < 0:
+                return 0 if n == 0 else -1
+            most = batch if batch else (memory.total - memory.reserved) // 4 // per
+            most = min(max(64, most // 64 * 64), -(-n // 64) * 64)
+            parts = -(-n // most)
+            return per * (-(-(-(-n // parts)) // 64) * 64)
+
+    monkeypatch.setattr(B, "lib", lambda: Lib)
+    first = B._sample_bytes(144, 5, 16384, 0, DEV)
+    assert first == per * 8192  # two equal parts
+    memory.reserved = first     # as the first call leaves it
+    assert Lib.gbs_sample_scratch(144, 5, 16384, 0) < first
+    assert B._sample_bytes(144, 5, 16384, 0, DEV) == first
+    memory.used = 60 << 30      # of it in use now: a quarter of what is left
+    assert B._sample_bytes(144, 5, 16384, 0, DEV) == per * 5504
+    assert B._sample_bytes(144, 5, 100, 0, DEV) == per * 128
+    assert B._sample_bytes(144, 5, 16384, 640, DEV) == Lib.gbs_sample_scratch(144, 5, 16384, 640)
+    assert B._sample_bytes(144, 5, 0, 0, DEV) == 0
+    assert B._sample_bytes(144, 5, 10, -1, DEV) == -1

@@ -65,3 +65,35 @@ def test_asynchronous_calls_of_two_threads(P, raw):
     for i in range(2):
         for o in out[i]:
             assert torch.equal(o[0], ref[i][0]) and torch.equal(o[1], ref[i][1])
+
+
+def test_automatic_batch_after_other_calls(P, monkeypatch):
+    """A memory-bound sampler call asks for the same scratch memory whether or not
+    torch holds memory that an earlier call has used (a third of what is free; the
+    sizes may differ by what the runtime itself takes meanwhile)."""
+    import torch
+    from paper_2511_14923_amd import _binding as B
+
+    class Asked(Exception):
+        pass
+
+    def record(nbytes, stream, device):
+        raise Asked(nbytes)
+
+    M, n = 100, 1 << 17
+    kap = torch.zeros(P.gbs_total_outputs(M, 5), dtype=torch.float64, device="cuda:0")
+    u = torch.zeros((M, n), dtype=torch.float64, device="cuda:0")
+    monkeypatch.setattr(B, "_scratch", record)
+    asked = []
+    torch.cuda.empty_cache()
+    for hold in (0, torch.cuda.mem_get_info()[0] // 3):
+        if hold:
+            work = torch.empty(hold, dtype=torch.uint8, device="cuda:0")
+            del work
+        with pytest.raises(Asked) as e:
+            P.gbs_sample(M, kap, 5, u, want_prob=False)
+        asked.append(e.value.args[0])
+    torch.cuda.empty_cache()
+    whole = P.lib().gbs_sample_scratch(M, 5, 64, 64) * (n // 64)
+    assert 0 < asked[0] < whole  # more than one part
+    assert abs(asked[1] - asked[0]) <= 0.02 * asked[0]
