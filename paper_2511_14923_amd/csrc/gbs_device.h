@@ -364,8 +364,16 @@ __device__ __forceinline__ void pair_outputs(const double* __restrict__ Qi, cons
   const double s10 = fma(-ib, fma(g0.y, t00, g1.y * t10), a10);
   const double s11 = fma(-ib, fma(g0.y, t01, g1.y * t11), a11);
   const double det = fma(s00, s11, -s10 * s10);
-  // a mode that is bad by itself is reported as order 1
-  if (oka && okb && !(s00 > 0.0 && det > 0.0 && det < INFINITY)) latch_failure(st, 2, r);
+  if (oka && okb && !(s00 > 0.0 && det > 0.0 && det < INFINITY)) {
+    // A mode that is bad by itself is reported before any pair, as by a launch of
+    // its own: a pair is latched only if no mode is bad (nor anything latched).
+    bool report = __hip_atomic_load(&st->flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
+    for (int k = 0; report && k < M; ++k) {
+      double c00, c10, c11, detc, pc, mc;
+      report = single(k, c00, c10, c11, detc, pc, mc);
+    }
+    if (report) latch_failure(st, 2, r);
+  }
   const double pab = pb * rsqrt_f64(det);
   const double m = (CONV == GBS_CLICK) ? mb - (pa - pab) : fma(-2.0, fma(-2.0, pab, pa), -mb);
   if (o.m[1]) o.m[1][r] = m;
