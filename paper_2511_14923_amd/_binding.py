@@ -4,7 +4,6 @@ compute step runs in the library's HIP kernels.  There is no fallback: if
 libgbs.so has not been built, loading raises."""
 from __future__ import annotations
 
-import contextlib
 import ctypes
 import os
 
@@ -237,35 +236,36 @@ def _stream(stream, device):
     return ctypes.c_void_p(int(stream))
 
 
-def _scratch(nbytes, stream, device):
+def _scratch(nbytes, stream, device, current=False):
     """nbytes of device memory for the library to work in during one call on
-    `stream`, or None (the library then allocates its own).  From torch's caching
-    allocator: it keeps the memory for the next call, gives it back when other
-    tensors or the library's own allocations need it (_own; or on
-    torch.cuda.empty_cache), and hands it out again to work on the same stream.  It
-    tells streams apart by their handles, so only the
-    default stream and torch's own streams get any: another handle can stand for a
-    different queue in every thread (hipStreamPerThread), or for a new stream after
-    the one that still runs this call's kernels was destroyed.  A stream that is
-    being captured gets None: the graph must hold memory of its own."""
+    `stream` (current: it is the current one), or None (the library then allocates
+    its own).  From torch's caching allocator: it keeps the memory for the next
+    call, gives it back when other tensors or the library's own allocations need it
+    (_own; or on torch.cuda.empty_cache), and hands it out again to work on the same
+    stream.  It tells streams apart by their handles, so only the default stream and
+    torch's own streams get any: another handle can stand for a different queue in
+    every thread (hipStreamPerThread), or for a new stream after the one that still
+    runs this call's kernels was destroyed.  A stream that is being captured gets
+    None: the graph must hold memory of its own."""
     if nbytes <= 0:
         return None
     if stream is None:
-        own = torch.cuda.current_stream(device)
-    elif isinstance(stream, torch.cuda.Stream):
-        own = stream
-    elif int(stream):
-        return None
-    else:
-        own = torch.cuda.default_stream(device)
+        stream, current = torch.cuda.current_stream(device), True
+    elif not isinstance(stream, torch.cuda.Stream):
+        if int(stream):
+            return None
+        stream = torch.cuda.default_stream(device)
     # a stream that torch did not make has its handle for an id
-    if own.cuda_stream and own.stream_id == own.cuda_stream:
+    handle = stream.cuda_stream
+    if handle and stream.stream_id == handle:
         return None
+    if not current:
+        with torch.cuda.stream(stream):
+            return _scratch(nbytes, stream, device, True)
     try:
-        with contextlib.nullcontext() if stream is None else torch.cuda.stream(own):
-            if torch.cuda.is_current_stream_capturing():
-                return None
-            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        if torch.cuda.is_current_stream_capturing():
+            return None
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
     except torch.OutOfMemoryError:
         return None
 
@@ -280,30 +280,37 @@ def _own(call, stream, device):
             torch.cuda.memory_reserved(device) <= torch.cuda.memory_allocated(device):
         return st
     if stream is None:
-        on = contextlib.nullcontext()
-    elif isinstance(stream, torch.cuda.Stream):
-        on = torch.cuda.stream(stream)
-    else:
-        on = torch.cuda.stream(torch.cuda.ExternalStream(int(stream), device) if int(stream)
-                               else torch.cuda.default_stream(device))
-    with on:
+        stream = torch.cuda.current_stream(device)
+    elif not isinstance(stream, torch.cuda.Stream):
+        stream = (torch.cuda.ExternalStream(int(stream), device) if int(stream)
+                  else torch.cuda.default_stream(device))
+    with torch.cuda.stream(stream):
         if torch.cuda.is_current_stream_capturing():
             return st
     torch.cuda.empty_cache()
     return call()
 
 
+def _run(nbytes, inside, own, stream, device):
+    """inside(memory, its size, stream) in nbytes() of lent memory, or own(stream)."""
+    with torch.cuda.device(device):
+        current = stream is None
+        if current:  # looked up once: the smallest calls take 30 us
+            stream = torch.cuda.current_stream(device)
+        handle = _stream(stream, device)
+        work = _scratch(nbytes(), stream, device, current)
+        if work is None:
+            return _own(lambda: own(handle), stream, device)
+        return inside(ctypes.c_void_p(work.data_ptr()), work.numel(), handle)
+
+
 def _forward(M, sigma, mu, max_order, flags, corr, cum, stream, own):
     """A forward call in lent scratch memory, or own() without any."""
-    dev = sigma.device
-    with torch.cuda.device(dev):
-        work = _scratch(lib().gbs_cumulants_scratch(M, max_order, flags, mu is not None,
-                                                    corr is not None), stream, dev)
-        if work is None:
-            return _own(lambda: own(_stream(stream, dev)), stream, dev)
-        return lib().gbs_cumulants_in(M, _ptr(sigma), _ptr(mu), max_order, flags, _ptr(corr),
-                                      _ptr(cum), ctypes.c_void_p(work.data_ptr()), work.numel(),
-                                      _stream(stream, dev))
+    return _run(lambda: lib().gbs_cumulants_scratch(M, max_order, flags, mu is not None,
+                                                    corr is not None),
+                lambda w, n, s: lib().gbs_cumulants_in(M, _ptr(sigma), _ptr(mu), max_order, flags,
+                                                       _ptr(corr), _ptr(cum), w, n, s),
+                own, stream, sigma.device)
 
 
 # ---- host helpers -----------------------------------------------------------
@@ -500,16 +507,13 @@ def gbs_sample(M: int, kappa: torch.Tensor, max_order: int, uniforms: torch.Tens
     _need(cond, "cond", M * n, optional=True)
     _same_device(("kappa", kappa), ("uniforms", uniforms), ("bits", bits), ("prob", prob),
                  ("cond", cond))
-    with torch.cuda.device(dev):
-        work = _scratch(_sample_bytes(M, max_order, n, batch, dev), stream, dev)
-        if work is None:
-            st = _own(lambda: lib().gbs_sample(M, _ptr(kappa), max_order, n, _ptr(uniforms),
-                                               _ptr_u8(bits), _ptr(prob), _ptr(cond), batch, flags,
-                                               _stream(stream, dev)), stream, dev)
-        else:
-            st = lib().gbs_sample_in(M, _ptr(kappa), max_order, n, _ptr(uniforms), _ptr_u8(bits),
-                                     _ptr(prob), _ptr(cond), _ptr_u8(work), work.numel(), flags,
-                                     _stream(stream, dev))
+    st = _run(lambda: _sample_bytes(M, max_order, n, batch, dev),
+              lambda w, size, s: lib().gbs_sample_in(M, _ptr(kappa), max_order, n, _ptr(uniforms),
+                                                     _ptr_u8(bits), _ptr(prob), _ptr(cond), w, size,
+                                                     flags, s),
+              lambda s: lib().gbs_sample(M, _ptr(kappa), max_order, n, _ptr(uniforms),
+                                         _ptr_u8(bits), _ptr(prob), _ptr(cond), batch, flags, s),
+              stream, dev)
     _check(st, "gbs_sample")
     return bits, prob, cond
 
@@ -525,16 +529,12 @@ def gbs_sample_cumulants(bits: torch.Tensor, max_order: int, cum=None, flags: in
     cum = _out(cum, nout, bits)
     _need(cum, "cum", nout)
     _same_device(("bits", bits), ("cum", cum))
-    with torch.cuda.device(bits.device):
-        work = _scratch(lib().gbs_sample_cumulants_scratch(M, n, max_order), stream, bits.device)
-        if work is None:
-            st = _own(lambda: lib().gbs_sample_cumulants(M, n, _ptr_u8(bits), max_order, _ptr(cum),
-                                                         flags, _stream(stream, bits.device)),
-                      stream, bits.device)
-        else:
-            st = lib().gbs_sample_cumulants_in(M, n, _ptr_u8(bits), max_order, _ptr(cum),
-                                               _ptr_u8(work), work.numel(), flags,
-                                               _stream(stream, bits.device))
+    st = _run(lambda: lib().gbs_sample_cumulants_scratch(M, n, max_order),
+              lambda w, size, s: lib().gbs_sample_cumulants_in(M, n, _ptr_u8(bits), max_order,
+                                                               _ptr(cum), w, size, flags, s),
+              lambda s: lib().gbs_sample_cumulants(M, n, _ptr_u8(bits), max_order, _ptr(cum), flags,
+                                                   s),
+              stream, bits.device)
     _check(st, "gbs_sample_cumulants")
     return cum
 
@@ -547,15 +547,11 @@ def gbs_pearson(x: torch.Tensor, y: torch.Tensor, r=None, flags: int = 0, stream
         r = torch.empty(1, dtype=torch.float64, device=x.device)
     _need(r, "r", 1)
     _same_device(("x", x), ("y", y), ("r", r))
-    with torch.cuda.device(x.device):
-        work = _scratch(lib().gbs_pearson_scratch(), stream, x.device)
-        if work is None:
-            st = _own(lambda: lib().gbs_pearson(x.numel(), _ptr(x), _ptr(y), _ptr(r), flags,
-                                                _stream(stream, x.device)), stream, x.device)
-        else:
-            st = lib().gbs_pearson_in(x.numel(), _ptr(x), _ptr(y), _ptr(r),
-                                      ctypes.c_void_p(work.data_ptr()), work.numel(), flags,
-                                      _stream(stream, x.device))
+    st = _run(lambda: lib().gbs_pearson_scratch(),
+              lambda w, size, s: lib().gbs_pearson_in(x.numel(), _ptr(x), _ptr(y), _ptr(r), w, size,
+                                                      flags, s),
+              lambda s: lib().gbs_pearson(x.numel(), _ptr(x), _ptr(y), _ptr(r), flags, s),
+              stream, x.device)
     _check(st, "gbs_pearson")
     return r
 
@@ -571,19 +567,13 @@ def gbs_cumulant_grad(M: int, sigma: torch.Tensor, max_order: int, flags: int = 
     _sigma(M, grad_sigma, "grad_sigma")
     _same_device(("sigma", sigma), ("grad_corr", grad_corr), ("grad_cum", grad_cum),
                  ("grad_sigma", grad_sigma))
-    dev = sigma.device
-    with torch.cuda.device(dev):
-        work = _scratch(lib().gbs_cumulant_grad_scratch(M, max_order), stream, dev)
-        if work is None:
-            st = _own(lambda: lib().gbs_cumulant_grad(M, _ptr(sigma), max_order, flags,
-                                                      _ptr(grad_corr), _ptr(grad_cum),
-                                                      _ptr(grad_sigma), _stream(stream, dev)),
-                      stream, dev)
-        else:
-            st = lib().gbs_cumulant_grad_in(M, _ptr(sigma), max_order, flags, _ptr(grad_corr),
-                                            _ptr(grad_cum), _ptr(grad_sigma),
-                                            ctypes.c_void_p(work.data_ptr()), work.numel(),
-                                            _stream(stream, dev))
+    st = _run(lambda: lib().gbs_cumulant_grad_scratch(M, max_order),
+              lambda w, size, s: lib().gbs_cumulant_grad_in(M, _ptr(sigma), max_order, flags,
+                                                            _ptr(grad_corr), _ptr(grad_cum),
+                                                            _ptr(grad_sigma), w, size, s),
+              lambda s: lib().gbs_cumulant_grad(M, _ptr(sigma), max_order, flags, _ptr(grad_corr),
+                                                _ptr(grad_cum), _ptr(grad_sigma), s),
+              stream, sigma.device)
     _check(st, "gbs_cumulant_grad")
     return grad_sigma
 

@@ -77,7 +77,7 @@ def test_automatic_batch_after_other_calls(P, monkeypatch):
     class Asked(Exception):
         pass
 
-    def record(nbytes, stream, device):
+    def record(nbytes, *where):
         raise Asked(nbytes)
 
     M, n = 100, 1 << 17
