@@ -265,7 +265,9 @@ def _scratch(nbytes, stream, device, current=False):
     try:
         if torch.cuda.is_current_stream_capturing():
             return None
-        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        # not torch.empty, which fills what it returns (gigabytes here) under
+        # torch.use_deterministic_algorithms and is seen by dispatch modes
+        return torch.UntypedStorage(nbytes, device=device)
     except torch.OutOfMemoryError:
         return None
 
@@ -301,7 +303,7 @@ def _run(nbytes, inside, own, stream, device):
         work = _scratch(nbytes(), stream, device, current)
         if work is None:
             return _own(lambda: own(handle), stream, device)
-        return inside(ctypes.c_void_p(work.data_ptr()), work.numel(), handle)
+        return inside(ctypes.c_void_p(work.data_ptr()), work.nbytes(), handle)
 
 
 def _forward(M, sigma, mu, max_order, flags, corr, cum, stream, own):

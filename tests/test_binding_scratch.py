@@ -48,7 +48,7 @@ def cuda(monkeypatch):
     monkeypatch.setattr(torch.cuda, "current_stream", lambda d=None: st.current)
     monkeypatch.setattr(torch.cuda, "default_stream", lambda d=None: Stream(0, 0))
     monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: st.capturing)
-    monkeypatch.setattr(torch, "empty", empty)
+    monkeypatch.setattr(torch, "UntypedStorage", empty)
     return st
 
 
@@ -144,3 +144,28 @@ def test_automatic_batch_counts_torchs_unused_memory_as_free(memory, monkeypatch
     assert B._sample_bytes(144, 5, 16384, 640, DEV) == Lib.gbs_sample_scratch(144, 5, 16384, 640)
     assert B._sample_bytes(144, 5, 0, 0, DEV) == 0
     assert B._sample_bytes(144, 5, 10, -1, DEV) == -1
+
+
+def test_lent_memory_is_not_filled(cuda, monkeypatch):
+    """Deterministic algorithms have torch.empty fill what it returns, gigabytes here."""
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Seen(TorchDispatchMode):
+        ops = []
+
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            self.ops.append(str(func))
+            return func(*args, **(kwargs or {}))
+
+    monkeypatch.undo()
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda d=None: Stream(0, 0))
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: False)
+    before = torch.are_deterministic_algorithms_enabled()
+    torch.use_deterministic_algorithms(True)
+    try:
+        with Seen() as seen:
+            work = B._scratch(4096, None, torch.device("cpu"))
+    finally:
+        torch.use_deterministic_algorithms(before)
+    assert seen.ops == []
+    assert work.nbytes() == 4096 and work.data_ptr()
