@@ -361,10 +361,12 @@ GBS_API gbs_status gbs_set_tuning(int32_t max_order, int32_t flags, const gbs_tu
  *   cond       device, M x nsamples FP64: p(x_n = 1 | x_<n) of every step, or NULL
  *   batch      samples per batch (rounded to a multiple of 64); 0 = as many as
  *              fit in a quarter of the free device memory.  The library allocates
- *              the per-sample tables for one batch, at most 8 x (M + 1 + C(M,2)
- *              + C(M+1,2) [+ C(M,3) for max_order 5]) bytes per sample of it (or
- *              what 64 samples need): double elision of 12 or more modes keeps
- *              about twice that per sample and takes a batch in several parts
+ *              the per-sample tables for one batch: with single elision
+ *              (max_order 3) at most 8 x (2 C(M+1,2) + 3 M + 11) bytes per sample
+ *              of it, with double elision 8 x (M + 4 + C(M,2) + C(M+1,2) + C(M,3))
+ *              (or what 64 samples need): double elision of 12 or more modes keeps
+ *              about twice that per sample and takes a batch in several parts.
+ *              A sample's results depend on its own column of uniforms alone
  *   flags      GBS_ASYNC | GBS_TIMING (other bits: GBS_E_INVALID_ARG)
  * Errors: GBS_E_INVALID_ARG for bad sizes, orders or null pointers;
  * GBS_E_UNSUPPORTED for max_order other than 3 or 5. */

@@ -353,8 +353,9 @@ hipError_t sampler_scratch(int M, int K, int64_t nsamples, int64_t batch, size_t
     hipError_t e = hipMemGetInfo(&free_b, &total_b);
     if (e != hipSuccess) return e;
     batch = (int64_t)(free_b / 4 / per);
-  } else if (by_steps(M, K)) {
-    // a batch stands for the memory of one table set per sample; the step tables are about twice that
+  } else if (by_steps(M, K) && K == 5) {
+    // a batch stands for the memory of one table set per sample; the step tables of
+    // double elision are about twice that (those of single elision 2 to 12% larger)
     batch = (int64_t)((double)batch * (double)(SampLayout::make(M, K).entries() * sizeof(double)) / (double)per);
   }
   *bytes = (size_t)per * (size_t)equal_parts(nsamples, batch);
