@@ -209,9 +209,9 @@ GBS_API gbs_status gbs_cumulants_displaced(int32_t M, const double* sigma, const
  * (M = 144, K = 5) about 0.3 ms.
  * gbs_cumulants_scratch (host): the bytes such a call needs (displaced, has_corr:
  * whether mu and corr are given), or -1 for arguments that it would refuse.
- *   scratch   device, 256-byte aligned, scratch_bytes bytes (fewer than needed:
- *             GBS_E_OUT_OF_MEMORY), not used by other work until the call's
- *             kernels have run */
+ *   scratch   device, 256-byte aligned (else GBS_E_INVALID_ARG), scratch_bytes bytes
+ *             (fewer than needed: GBS_E_OUT_OF_MEMORY), not used by other work
+ *             until the call's kernels have run */
 GBS_API int64_t gbs_cumulants_scratch(int32_t M, int32_t max_order, int32_t flags,
                                       int32_t displaced, int32_t has_corr);
 GBS_API gbs_status gbs_cumulants_in(int32_t M, const double* sigma, const double* mu,

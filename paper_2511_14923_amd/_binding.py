@@ -301,7 +301,7 @@ def _run(nbytes, inside, own, stream, device):
             stream = torch.cuda.current_stream(device)
         handle = _stream(stream, device)
         work = _scratch(nbytes(), stream, device, current)
-        if work is None:
+        if work is None or work.data_ptr() % 256:  # an allocator plugged into torch
             return _own(lambda: own(handle), stream, device)
         return inside(ctypes.c_void_p(work.data_ptr()), work.nbytes(), handle)
 

@@ -541,10 +541,14 @@ int64_t gbs_cumulants_scratch(int32_t M, int32_t max_order, int32_t flags, int32
   return (int64_t)forward_scratch(M, max_order, flags, displaced != 0, has_corr != 0);
 }
 
+// Memory lent by the caller: the kernels' 16-byte accesses and the layouts of the
+// scratch blocks rest on its alignment.
+static bool valid_lent(const void* scratch) { return scratch && ((uintptr_t)scratch & 255) == 0; }
+
 gbs_status gbs_cumulants_in(int32_t M, const double* sigma, const double* mu, int32_t max_order,
                             int32_t flags, double* corr, double* cum, void* scratch,
                             int64_t scratch_bytes, void* stream) {
-  if (!valid_problem(M, max_order, flags) || !sigma || (!corr && !cum) || !scratch)
+  if (!valid_problem(M, max_order, flags) || !sigma || (!corr && !cum) || !valid_lent(scratch))
     return GBS_E_INVALID_ARG;
   if (mu && (flags & GBS_MIXED)) return GBS_E_UNSUPPORTED;
   if (scratch_bytes < 0 ||
@@ -579,7 +583,8 @@ gbs_status gbs_cumulant_grad_in(int32_t M, const double* sigma, int32_t max_orde
                                 const double* grad_corr, const double* grad_cum,
                                 double* grad_sigma, void* scratch, int64_t scratch_bytes,
                                 void* stream) {
-  if (!valid_problem(M, max_order, flags) || !sigma || !grad_sigma || !scratch) return GBS_E_INVALID_ARG;
+  if (!valid_problem(M, max_order, flags) || !sigma || !grad_sigma || !valid_lent(scratch))
+    return GBS_E_INVALID_ARG;
   if (flags & GBS_MIXED) return GBS_E_UNSUPPORTED;
   if (scratch_bytes < 0 || (size_t)scratch_bytes < AdjointScratch::make(M, max_order).bytes)
     return GBS_E_OUT_OF_MEMORY;
@@ -637,7 +642,7 @@ gbs_status gbs_sample_in(int32_t M, const double* kappa, int32_t max_order, int6
                          void* scratch, int64_t scratch_bytes, int32_t flags, void* stream) {
   const gbs_status st = check_sample(M, kappa, max_order, nsamples, uniforms, bits, 0, flags);
   if (st != GBS_OK) return st;
-  if (nsamples > 0 && (!scratch || scratch_bytes < 0)) return GBS_E_INVALID_ARG;
+  if (nsamples > 0 && (!valid_lent(scratch) || scratch_bytes < 0)) return GBS_E_INVALID_ARG;
   return sample_call(M, kappa, max_order, nsamples, uniforms, bits, prob, cond, 0, scratch,
                      (size_t)scratch_bytes, flags, stream);
 }
@@ -678,7 +683,8 @@ int64_t gbs_sample_cumulants_scratch(int32_t M, int64_t nsamples, int32_t max_or
 gbs_status gbs_sample_cumulants_in(int32_t M, int64_t nsamples, const uint8_t* bits,
                                    int32_t max_order, double* cum, void* scratch,
                                    int64_t scratch_bytes, int32_t flags, void* stream) {
-  if (!valid_estimate(M, nsamples, max_order) || !bits || !cum || !scratch) return GBS_E_INVALID_ARG;
+  if (!valid_estimate(M, nsamples, max_order) || !bits || !cum || !valid_lent(scratch))
+    return GBS_E_INVALID_ARG;
   if (flags & ~(GBS_ASYNC | GBS_TIMING)) return GBS_E_INVALID_ARG;
   if (scratch_bytes < 0 || (size_t)scratch_bytes < estimator_scratch(M, nsamples, max_order))
     return GBS_E_OUT_OF_MEMORY;
@@ -708,7 +714,7 @@ int64_t gbs_pearson_scratch(void) { return (int64_t)pearson_scratch(); }
 
 gbs_status gbs_pearson_in(int64_t n, const double* x, const double* y, double* r, void* scratch,
                           int64_t scratch_bytes, int32_t flags, void* stream) {
-  if (n < 2 || !x || !y || !r || !scratch) return GBS_E_INVALID_ARG;
+  if (n < 2 || !x || !y || !r || !valid_lent(scratch)) return GBS_E_INVALID_ARG;
   if (flags & ~(GBS_ASYNC | GBS_TIMING)) return GBS_E_INVALID_ARG;
   if (scratch_bytes < 0 || (size_t)scratch_bytes < pearson_scratch()) return GBS_E_OUT_OF_MEMORY;
   return pearson_call(n, x, y, r, scratch, flags, stream);
