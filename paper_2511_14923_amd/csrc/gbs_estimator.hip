@@ -35,7 +35,6 @@ namespace gbs {
 namespace {
 
 constexpr int kEstThreads = 256;
-constexpr int kEstMaxModes = 256;
 constexpr int kChunkWords = 8;                    // 64-bit words per mode and chunk
 constexpr int kChunkBytes = 8 * kChunkWords;      // 512 samples
 constexpr int kPackSamples = 256;                 // samples per workgroup of the packing
@@ -45,7 +44,8 @@ __global__ __launch_bounds__(kPackSamples) void pack_columns_kernel(const uint8_
                                                                     int M, int64_t words, int wide,
                                                                     uint64_t* __restrict__ cols) {
   extern __shared__ uint8_t rows[];  // kPackSamples x M
-  const int64_t s0 = (int64_t)blockIdx.x * kPackSamples;
+  const int64_t pack = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  const int64_t s0 = pack * kPackSamples;
   const int64_t have = min((int64_t)kPackSamples, N - s0);
   const int64_t bytes = have > 0 ? have * M : 0;
   const uint8_t* src = bits + s0 * M;
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(kPackSamples) void pack_columns_kernel(const uint8_
   }
   __syncthreads();
   const int lane = threadIdx.x & 63;
-  const int64_t w = (int64_t)blockIdx.x * (kPackSamples / 64) + (threadIdx.x >> 6);
+  const int64_t w = pack * (kPackSamples / 64) + (threadIdx.x >> 6);
   if (w >= words) return;
   const bool live = w * 64 + lane < N;
   const uint8_t* row = rows + (int)threadIdx.x * M;
@@ -764,11 +764,16 @@ hipError_t run_sample_cumulants(int M, int64_t N, const uint8_t* bits, int K,
   CountTables tab{};
   for (int d = 1; d <= K; ++d) tab.cnt[d] = reinterpret_cast<uint32_t*>(b + S.cnt[d]);
   const int64_t words = S.chunks * kChunkWords;
-  const int64_t packs = (words * 64 + kPackSamples - 1) / kPackSamples;
-  hipLaunchKernelGGL(pack_columns_kernel, dim3((unsigned)packs), dim3(kPackSamples), (size_t)kPackSamples * M, s, bits,
-                     N, M, words, ((uintptr_t)bits & 3) == 0, cols);
-  hipLaunchKernelGGL(count1_kernel, dim3(M), dim3(kEstThreads), 0, s, cols, M, words, tab.cnt[1]);
+  // 2^32 threads in one dimension of a launch (N near 2^32) would be refused
+  const int64_t packs = (words * 64 + kPackSamples - 1) / kPackSamples, wide = std::min<int64_t>(packs, 1 << 20);
+  hipLaunchKernelGGL(pack_columns_kernel, dim3((unsigned)wide, (unsigned)((packs + wide - 1) / wide)),
+                     dim3(kPackSamples), (size_t)kPackSamples * M, s, bits, N, M, words, ((uintptr_t)bits & 3) == 0,
+                     cols);
   e = hipGetLastError();
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(count1_kernel, dim3(M), dim3(kEstThreads), 0, s, cols, M, words, tab.cnt[1]);
+    e = hipGetLastError();
+  }
   if (e == hipSuccess && K >= 2) e = launch_counts<1, 1>(cols, M, S.chunks, binom, tab.cnt[2], s);
   if (e == hipSuccess && K >= 3) e = launch_counts<1, 2>(cols, M, S.chunks, binom, tab.cnt[3], s);
   if (e == hipSuccess && K >= 4) e = launch_counts<2, 2>(cols, M, S.chunks, binom, tab.cnt[4], s);
