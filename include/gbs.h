@@ -77,8 +77,8 @@ enum {
                         sums (not for gbs_cumulant_grad); error per order as reported       */
     GBS_ASYNC = 4,   /* bit 2 set:   return right after the launches; a NOT_SPD pivot is then
                         reported only by gbs_last_error after the stream has completed          */
-    GBS_TIMING = 8,  /* bit 3 set:   record a HIP event pair around every kernel launch of the
-                        call, on `stream`; read them back with gbs_last_timings               */
+    GBS_TIMING = 8,  /* bit 3 set:   record HIP event pairs around the stages of the call, on
+                        `stream`; read them back with gbs_last_timings                        */
     GBS_ALL_MINORS = 16 /* bit 4 set: evaluate all 2^d principal minors of every subset from Q
                         (no lower-order tables): the kernel of the batched launch; slower    */
 };
@@ -87,17 +87,19 @@ enum {
 enum {
     GBS_STAGE_BUILD_Q = 0,    /* Q = sigma + I/2 (interleaved copy)                 */
     GBS_STAGE_NORMALISE = 1,  /* per-mode normalisation of Q (GBS_MIXED)            */
-    GBS_STAGE_FORWARD = 2,    /* one order's correlator/cumulant kernel             */
-    GBS_STAGE_ADJOINT = 3,    /* one kernel of the vector-Jacobian product          */
-    GBS_STAGE_BATCHED = 4,    /* the persistent batched kernel                      */
-    GBS_STAGE_SAMPLE = 5,     /* one launch of the sampler kernel                   */
+    GBS_STAGE_FORWARD = 2,    /* one order's correlator/cumulant kernel (orders 1 and 2
+                                 of a zero-mean state in FP64 with max_order >= 2 are
+                                 one launch, reported as order 2)                   */
+    GBS_STAGE_ADJOINT = 3,    /* one step of the vector-Jacobian product            */
+    GBS_STAGE_BATCHED = 4,    /* one launch of the batched pipeline                 */
+    GBS_STAGE_SAMPLE = 5,     /* gbs_sample (whole call)                            */
     GBS_STAGE_ESTIMATE = 6    /* gbs_sample_cumulants or gbs_pearson (whole call)   */
 };
 
 typedef struct {
     int32_t stage;  /* GBS_STAGE_*                                   */
-    int32_t order;  /* subset order of a FORWARD stage, else 0        */
-    float ms;       /* elapsed time between the launch's event pair   */
+    int32_t order;  /* subset order of the stage, 0 where it has none */
+    float ms;       /* elapsed time between the stage's event pair    */
 } gbs_kernel_time;
 
 #define GBS_MAX_ORDER 5
