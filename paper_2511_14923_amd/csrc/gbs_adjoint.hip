@@ -613,8 +613,10 @@ hipError_t launch_adjoint(int M, int K, int flags, const double* Qi, const doubl
   };
   // Workgroups per mbar sum: a launch of fewer than kAdjointSplitItems long sums
   // (the order-1 subsets) would leave compute units idle, so each sum is split into
-  // chunks of at least 16,384 terms (16 rounds of a workgroup; at 10,296 terms, M =
-  // 144, K = 3, one workgroup per sum is faster than the partial sums' second launch).
+  // chunks of at least 16,384 terms (16 rounds of a workgroup).  Gradient calls with
+  // chunks of 512 / 2,048 / 4,096 / 16,384, us: M = 144, K = 3 (10,296 terms a sum) 194 /
+  // 182 / 183 / 183, M = 30, K = 4 (4,089) 123 / 121 / 129 / 119, M = 40, K = 4 (9,919)
+  // 157 / 147 / 168 / 167, M = 60, K = 4 (34,279) 293 / 265 / 274 / 309.
   auto split_for = [](uint64_t items, uint64_t n) -> unsigned {
     if (items >= (uint64_t)kAdjointSplitItems) return 1u;
     const uint64_t want = ((uint64_t)kAdjointSplitItems + items - 1) / items;

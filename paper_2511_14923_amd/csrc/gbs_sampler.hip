@@ -317,14 +317,13 @@ __global__ __launch_bounds__(64 * kSampWaves) void sampler_kernel(
 
 // Modes from which double elision runs step by step over all samples
 // (gbs_sampler_double.hip, about four launches per bit) instead of one workgroup
-// per 64 samples here: 1,000 samples take 0.34 ms either way at M = 12, 0.13
-// (here) against 0.23 ms at M = 8, 0.69 against 0.44 ms at M = 16, 102 against
-// 4.1 ms at M = 60.
+// per 64 samples here.  Here / by steps, ms, at 1, 1,000, 20,000 and 200,000 samples:
+// M = 12 0.27 / 0.22, 0.32 / 0.23, 0.59 / 0.36, 3.9 / 2.0; M = 16 0.60 / 0.33, 0.65 /
+// 0.35, 1.7 / 0.65, 9.6 / 4.7; 1,000 samples at M = 8 0.13 / 0.23, at M = 60 102 / 4.1.
 constexpr int kStepMinModes = 12;
 // The same for single elision (gbs_sampler_single.hip, three launches per bit):
-// 1,000 samples take 0.38 (here) against 0.41 ms at M = 20, 1.04 against 0.67 ms
-// at M = 30; 200 samples 37 against 4.2 ms at M = 100; 10,000 samples 12.6
-// against 2.8 ms at M = 60.
+// M = 24 0.55 / 0.33, 0.60 / 0.34, 1.26 / 0.49, 3.4 / 2.6; M = 30 1.0 / 0.42, 1.07 /
+// 0.43, 2.2 / 0.68, 38 / 4.5; 1,000 samples at M = 20 0.38 / 0.41.
 constexpr int kSingleStepMinModes = 24;
 
 namespace {
