@@ -15,7 +15,8 @@
 // entries each at step n, bound by memory bandwidth.  The sum of the V update of
 // step n + 1 over i < n needs only q of step n + 1, which is known after bit n and
 // p+ of top n, so every other step takes the V sums of two steps in one pass.
-// M = 144, 65,536 samples: 102 ms, 6 MB of table reads per sample at 3.9 TB/s,
+// M = 144, 65,536 samples: 96.3 ms, 6 MB of table reads per sample (7.9 MB of memory
+// traffic with the products and what is written, by the counters, at 5.4 TB/s),
 // against 325 ms of one workgroup per 64 samples that read 20 MB per sample.
 //
 // Storage as in gbs_sampler_double.hip: blocks of 64 samples, entry-major.
@@ -115,12 +116,10 @@ __global__ __launch_bounds__(256) void bit_kernel(StepArgs A, const double* __re
 // Table passes: kRun consecutive entries (4 KB in one piece) of a top per workgroup;
 // its four waves take every fourth term of the sums, which are added in wave order.
 // With a wave per run the longest sum, n terms one after the other, is the time of a
-// launch with few blocks of samples; with many, bandwidth is, and the split reads a
-// little more scattered.  M = 144, a wave per run / split: 500 samples 9.6 / 3.5 ms,
-// 10,000 21.8 / 16.3, 20,000 34.6 / 30.4, 40,000 60.3 / 60.7, 65,536 98.0 / 102.2;
-// M = 60: 5,000 2.4 / 1.35, 100,000 13.8 / 13.7; M = 40, 200,000 9.5 / 9.7.  One form for every call: a sample's
-// sums, and so its bits, depend on its own column of uniforms alone, not on how many
-// samples are drawn with it.
+// launch with few blocks of samples.  M = 144, a wave per run / split: 500 samples
+// 9.6 / 3.5 ms, 10,000 21.8 / 16.3, 20,000 34.6 / 30.4; M = 60, 5,000 2.4 / 1.35.  One
+// form for every call: a sample's sums, and so its bits, depend on its own column of
+// uniforms alone, not on how many samples are drawn with it.
 constexpr int kRun = 8, kParts = 4, kOwn = kRun / kParts;
 constexpr int kSumWords = kParts * kRun * kSB;
 
@@ -135,6 +134,23 @@ __device__ __forceinline__ void sum_waves(double (&acc)[kRun], double* red, int 
 #pragma unroll
     for (int v = 1; v < kParts; ++v) acc[t] += red[(v * kRun + w * kOwn + t) * kSB + lane];
   }
+}
+
+// Run and block of samples of a pass's item: one group of the sample blocks after the
+// other, the longest sums first within a group.  The runs of a block are neighbours in
+// memory; with every block of a large call between them, the split reads them far
+// apart.  M = 144, one group / groups of about 64 / 128 / 256 / 512 / 1,024 blocks, ms:
+// 262,144 samples 423 / 386 / 383 / 384 / 389 / 408, 65,536 102.1 / 97.9 / 96.5 / 96.3 /
+// 97.4 / 102.1 (a wave per run: 417, 97.9); 20,000 samples (313 blocks) 30.4 in one
+// group, 31.3 as 256 and 57: hence groups of equal size, the nearest to kGroup.
+constexpr uint32_t kGroup = 256;
+struct Item {
+  uint32_t run, sb;
+};
+__device__ __forceinline__ Item item_of(uint32_t item, uint32_t runs, uint32_t nsb, uint32_t group) {
+  const uint32_t first = item / (runs * group) * group, m = min(group, nsb - first);
+  const uint32_t r = item - first * runs;
+  return {r / m, first + r % m};
 }
 
 // The terms j = first, first + kParts, .. < n of p+(x_n..x_l), l = l0..l0 + kRun - 1.
@@ -161,13 +177,14 @@ __device__ __forceinline__ void partial_terms(const double* q, const double* k2,
 }
 
 // p+(x_n..x_l), and from it q of step n + 1.
-__global__ __launch_bounds__(256) void partial_kernel(StepArgs A, uint32_t nsb) {
+__global__ __launch_bounds__(256) void partial_kernel(StepArgs A, uint32_t nsb, uint32_t runs,
+                                                     uint32_t group) {
   __shared__ double red[kSumWords];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int n = A.n;
-  const uint32_t item = blockIdx.x;
-  const int l0 = 1 + (int)(item / nsb) * kRun;  // the longest sums first
-  double* blk = block_of(A, item % nsb) + lane;
+  const Item it = item_of(blockIdx.x, runs, nsb, group);
+  const int l0 = 1 + (int)it.run * kRun;
+  double* blk = block_of(A, it.sb) + lane;
   const double* q = blk + (uint64_t)A.st.q[n & 1] * kSB;
   const double* k2 = A.kap + A.ko.off[2] + samp_r2(n) - 1;
   double* PP = blk + (uint64_t)(A.st.PP + (uint32_t)l0 - 1) * kSB;  // p+(j-1, l0 + r) at C(j-1, 2) + l0 - 1 + r
@@ -223,13 +240,14 @@ __device__ __forceinline__ void update_terms(const double* q, const double* k2, 
 // gbs_sampler_double.hip), a workgroup per run; the step after it adds one term,
 // a wave per run.
 template <bool FULL>
-__device__ __forceinline__ void update_item(const StepArgs& A, uint32_t b, uint32_t nsb, uint32_t runs, int lane,
+__device__ __forceinline__ void update_item(const StepArgs& A, uint32_t b, uint32_t nsb, uint32_t runs, uint32_t group, int lane,
                                             int w, double* red) {
   const int n = A.n;
   const uint32_t item = FULL ? b : b * 4 + (uint32_t)w;
   if (item >= runs * nsb) return;
-  const int e0 = 1 + (int)(item / nsb) * kRun;
-  double* blk = block_of(A, item % nsb) + lane;
+  const Item it = item_of(item, runs, nsb, group);
+  const int e0 = 1 + (int)it.run * kRun;
+  double* blk = block_of(A, it.sb) + lane;
   const double* q = blk + (uint64_t)A.st.q[n & 1] * kSB;
   const double* k2 = A.kap + A.ko.off[2] + samp_r2(n) - 1;
   double* V = blk + (uint64_t)(A.st.V + (uint32_t)e0 - 1) * kSB;  // V(i; e0 + r) at C(i-1, 2) + e0 - 1 + r
@@ -285,11 +303,11 @@ __device__ __forceinline__ void row_of(const StepArgs& A, int r, uint32_t* kap, 
 // The V update of step n and the product with V(n; .), which are independent.
 template <bool FULL>
 __global__ __launch_bounds__(256) void step_kernel(StepArgs A, int rows, int row_blocks, uint32_t nprod,
-                                                   uint32_t nsb, uint32_t runs) {
+                                                   uint32_t nsb, uint32_t runs, uint32_t group) {
   __shared__ double Bs[2][1][kKC][kLdB];
   static_assert(sizeof(Bs) >= kSumWords * sizeof(double), "the sums of a workgroup's waves fit the operand buffers");
   if (blockIdx.x >= nprod) {
-    update_item<FULL>(A, blockIdx.x - nprod, nsb, runs, threadIdx.x & 63,
+    update_item<FULL>(A, blockIdx.x - nprod, nsb, runs, group, threadIdx.x & 63,
                              __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), &Bs[0][0][0][0]);
     return;
   }
@@ -320,6 +338,7 @@ hipError_t launch_single_sampler(int M, const double* kap, KapOffsets ko, int64_
                                  uint64_t ldu, double* tab, uint8_t* bits, double* prob, double* cond,
                                  hipStream_t s) {
   const uint32_t nsb = (uint32_t)((nsamp + kSB - 1) / kSB);
+  const uint32_t groups = std::max(1u, (nsb + kGroup / 2) / kGroup), group = (nsb + groups - 1) / groups;
   StepArgs A{kap, ko, tab, Store::make(M), M, 0};
   hipError_t e = hipSuccess;
   for (int n = 1; n <= M && e == hipSuccess; ++n) {
@@ -328,14 +347,14 @@ hipError_t launch_single_sampler(int M, const double* kap, KapOffsets ko, int64_
     hipLaunchKernelGGL(bit_kernel, dim3(nsb), dim3(256), 0, s, A, u, ldu, nsamp, bits, prob, cond);
     if (n < M) {
       const uint32_t pr = ((uint32_t)n + kRun - 1) / kRun;
-      hipLaunchKernelGGL(partial_kernel, dim3(pr * nsb), dim3(256), 0, s, A, nsb);
+      hipLaunchKernelGGL(partial_kernel, dim3(pr * nsb), dim3(256), 0, s, A, nsb, pr, group);
       // at n = 1 the products have no terms: their slots are set to 0
       const bool full = (m & 1) == 0;
       const uint32_t rows = 2 * m - 1, rb = (rows + 63) / 64, runs = ((uint32_t)n - 1 + kRun - 1) / kRun;
       const uint32_t nprod = rb * nsb;
       const dim3 grid(nprod + (full ? runs * nsb : (runs * nsb + 3) / 4));
       const auto k = full ? step_kernel<true> : step_kernel<false>;
-      hipLaunchKernelGGL(k, grid, dim3(256), 0, s, A, (int)rows, (int)rb, nprod, nsb, runs);
+      hipLaunchKernelGGL(k, grid, dim3(256), 0, s, A, (int)rows, (int)rb, nprod, nsb, runs, group);
     }
     e = hipGetLastError();
   }
