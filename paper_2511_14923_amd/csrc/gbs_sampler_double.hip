@@ -467,7 +467,9 @@ hipError_t launch_double_sampler(int M, const double* kap, KapOffsets ko, int64_
       // kSlimRows rows the slim kernel: two 64-row tiles a block of samples leave
       // units idle, each with a long serial inner index.  Slim up to 16 / 64 / 128 /
       // 256 rows: 7.8 / 7.4 / 7.0 / 6.6 ms at M = 90, 200 samples; 100.1 / 99.3 /
-      // 98.4 / 98.2 at M = 144, 2,048; 44.8 / 44.4 / 44.5 / 44.9 at M = 100, 4,096.
+      // 98.4 / 98.2 at M = 144, 2,048; 44.8 / 44.4 / 44.5 / 44.9 at M = 100, 4,096: more
+      // than 128 gain with few samples and lose with many, and the rule must not go
+      // by the samples.
       const uint32_t rows = n >= 3 ? 1 + 2 * m + samp_c2(m) : 0;
       if (rows <= kSlimRows) {
         const uint32_t rb = (rows + 15) / 16;

@@ -15,9 +15,9 @@
 // entries each at step n, bound by memory bandwidth.  The sum of the V update of
 // step n + 1 over i < n needs only q of step n + 1, which is known after bit n and
 // p+ of top n, so every other step takes the V sums of two steps in one pass.
-// M = 144, 65,536 samples: 96.3 ms, 6 MB of table reads per sample (7.9 MB of memory
-// traffic with the products and what is written, by the counters, at 5.4 TB/s),
-// against 325 ms of one workgroup per 64 samples that read 20 MB per sample.
+// M = 144, 65,536 samples: 96.3 ms, 7.5 MB of memory traffic per sample by the counters
+// (7.1 read) at 5.1 TB/s, against 325 ms of one workgroup per 64 samples that read
+// 20 MB per sample.
 //
 // Storage as in gbs_sampler_double.hip: blocks of 64 samples, entry-major.
 // B(n, e) waits in the slot of V(n+1; e); Z3(n, a) in that of p+(x_n..x_a).
